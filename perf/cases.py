@@ -54,8 +54,8 @@ def listed():
         _gather("resident pipelined", 1 << 21, 1 << 25, 128, 900_000, 8192, "15,10,5", 1 << 19, 0, 4, "pipelined", 4,
                 8, resident=True),
         # fp16 x 1024 rows in ordinary host memory, copied by the library's
-        # host threads; lookahead 16, about nine of ten requests hit.
-        _gather("pageable pipelined", 1 << 19, 1 << 23, 128, 100_000, 1024, "15,10,5", 40960, 16384, 16, "pipelined", 4, 24,
+        # host threads; lookahead 16, about four of five rows hit.
+        _gather("pageable pipelined", 1 << 19, 1 << 23, 128, 100_000, 1024, "15,10,5", 16384, 16384, 16, "pipelined", 4, 24,
                 pageable=True),
         # The paper's own victim-buffer form (queues with prefetch) and update
         # period 4, fp32 x 768 rows (not a power of two), no pipelining.
