@@ -10,10 +10,13 @@
 //   dedup       byte map over node IDs marked with plain stores, per-chunk
 //               popcount, chunk scan, ascending compaction that records each
 //               node's unique index; the inverse index is one lookup
-//   group       per-set counts with atomics, segment allocation, placement and
-//               ranking so each touched set sees its IDs in ascending order
-//   set walk    one lane per touched set walks its IDs in ascending order over
-//               the 8 ways held in registers: tag probe, then on a fill the
+//   probe       each unique ID's set looked up in the batch-start state (the
+//               misses this already fixes are listed for the host fetch) and
+//               counted; a set whose IDs are all resident is settled here, since
+//               hits change nothing
+//   group       segment allocation and placement of the other sets' IDs
+//   set walk    eight lanes per set (one per way) order its IDs and walk them in
+//               ascending order: tag probe, then on a fill the
 //               empty way or the minimum (level, static score, way) victim
 //               (Sec. 4.2 levels; Sec. 4.3.2 swap when the victim ring is on)
 //   ring        exclusive scan of enqueue flags gives FIFO sequence numbers in
@@ -28,8 +31,6 @@
 #include "internal.h"
 
 namespace lsm {
-
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------- helpers
 // set index: SplitMix64 output for state x (Steele, Lea, Flood 2014), reduced
@@ -61,6 +62,30 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t &t
   for (int w = 0; w < kBlock / 64; ++w) {
     const uint32_t sw = wsum[w];
     base += (w < wid) ? sw : 0u;
+    tot += sw;
+  }
+  __syncthreads();
+  total = tot;
+  return base + x - v;
+}
+
+// The same for 64-bit values.
+__device__ __forceinline__ uint64_t block_exclusive_scan64(uint64_t v, uint64_t &total) {
+  __shared__ uint64_t wsum[kBlock / 64];
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  uint64_t x = v;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint64_t y = __shfl_up(x, d);
+    if (lane >= d) x += y;
+  }
+  if (lane == 63) wsum[wid] = x;
+  __syncthreads();
+  uint64_t base = 0, tot = 0;
+#pragma unroll
+  for (int w = 0; w < kBlock / 64; ++w) {
+    const uint64_t sw = wsum[w];
+    base += (w < wid) ? sw : 0ull;
     tot += sw;
   }
   __syncthreads();
@@ -160,7 +185,7 @@ __global__ __launch_bounds__(kBlock) void k_finish(Counters *cn, Counters *host,
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    c.hits = sums[kStHits];
+    c.hits = sums[kStHits] + sums[kStSettled];
     c.fills = sums[kStFills];
     c.evictions = sums[kStEvictions];
     c.enqueued = sums[kStEnqueued];
@@ -306,7 +331,7 @@ __global__ __launch_bounds__(kBlock) void k_chunk_scan(uint32_t *chunk_sums, uin
 // earlier chunks' counts, added up by the block itself (few chunks: this
 // saves the separate one-block scan), and the last chunk's block publishes
 // the unique count; otherwise chunk_off holds the scanned offsets.  Each
-// node's own unique index is written later (k_unique_index).
+// node's own unique index is written later (k_place).
 template <bool kFused>
 __global__ __launch_bounds__(kBlock) void k_compact(uint8_t *present, const uint32_t *chunk_off, uint32_t *uniq,
                                                     int64_t *uniq_out, Counters *cn, uint32_t nchunks,
@@ -381,21 +406,6 @@ void launch_dedup(const DevState &d, const int64_t *ids, uint64_t n, const int64
   }
 }
 
-// Each unique ID's index, uidx[uniq[u]] = u, read by the inverse index and the
-// per-request counts.  Kept out of the compaction: these scattered 4-byte
-// writes (one per unique ID over an N-entry array) cost the compaction most
-// of its time beside the host-link reads, and the early-miss list, which
-// needs only the unique list, need not wait for them.
-__global__ __launch_bounds__(kBlock) void k_unique_index(const uint32_t *uniq, uint32_t *uidx, const Counters *cn) {
-  if (cn->err) return;
-  const uint32_t U = cn->n_unique;
-  for (uint32_t u = blockIdx.x * kBlock + threadIdx.x; u < U; u += gridDim.x * kBlock) uidx[uniq[u]] = u;
-}
-
-void launch_unique_index(const DevState &d, uint64_t n, const Scratch &sc, const Counters *cn, hipStream_t s) {
-  hipLaunchKernelGGL(k_unique_index, dim3(grid_for(n, kBlock, kMaxGrid)), dim3(kBlock), 0, s, sc.uniq, d.uidx, cn);
-}
-
 // ------------------------------------------------------------ group by set
 // Every thread of the block must call this; returns the list index for
 // threads with pred set (one atomic per block).
@@ -416,177 +426,150 @@ __device__ __forceinline__ void block_count(uint32_t v, uint32_t *part, int slot
   if (threadIdx.x == 0) part[slot * kMaxGrid + blockIdx.x] = tot;
 }
 
-// Inverse index of every request (the compaction recorded each node's unique
-// index), then per-set counts of the unique IDs.
-__global__ __launch_bounds__(kBlock) void k_inverse_claim(const DevState d, Scratch sc, const int64_t *ids,
-                                                          uint32_t n, int64_t *inv, Counters *cn) {
+// Per unique ID, right after the dedup: its set, its arrival order among the
+// set's IDs, and what the batch-start state says about it.
+//
+// Misses known from the batch-start state are listed here, so that their rows
+// start crossing the link while the rest of the metadata runs: a unique ID x
+// that no way of its set holds at batch start is filled at its turn (only x
+// itself inserts x), and with no entry for it in the victim buffer (FIFO: no
+// ring entry naming x; queues: no entry in the queue of this iteration) the
+// fill is a miss, whatever the walk decides.  The resolve, which finds the
+// same outcome, leaves these out of its list.
+//
+// A set none of whose IDs is missing changes nothing in this gather, so its
+// IDs' outcomes are settled by this probe alone; the others are marked for the
+// walk (set_dirty holds 1 + the gather index).  Where nearly every row is
+// resident this leaves nothing to group: 365 us per gather against 409 with
+// every touched set walked (900 K requests, 235 K unique 2 KiB rows, pipelined);
+// where nearly every set misses it costs nothing measurable.
+//
+// Bound by latency: a 128-byte set record and an atomic on the set's counter
+// per unique ID, both in flight together.
+__global__ __launch_bounds__(kBlock) void k_probe(const DevState d, Scratch sc, uint64_t t, const Counters *cn) {
   if (cn->err) return;
-  if (inv) {
-    for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
-      inv[i] = (int64_t)d.uidx[ids[i]];
-    }
-  }
   const uint32_t U = cn->n_unique;
+  uint32_t c_early = 0;
   for (uint32_t base = blockIdx.x * kBlock; base < U; base += gridDim.x * kBlock) {
     const uint32_t u = base + threadIdx.x;
-    bool claim = false;
-    uint32_t s = 0;
+    bool early = false;
+    uint32_t x = 0;
     if (u < U) {
-      const uint32_t x = sc.uniq[u];
-      s = set_index(x, d.S);
+      x = sc.uniq[u];
+      const uint32_t s = set_index(x, d.S);
+      const u32x4 *tp = reinterpret_cast<const u32x4 *>(d.sets[s].tag);
+      const u32x4 a = tp[0], b = tp[1];
+      sc.arrival[u] = atomicAdd(&d.set_count[s], 1u);
       sc.uset[u] = s;
-      const uint32_t old = atomicAdd(&d.set_count[s], 1u);
-      sc.arrival[u] = old;
-      claim = (old == 0);
-      sc.flags[u] = 0;
-      sc.dead[u] = 0;
-      sc.this_q[u] = 0;
-      sc.fill_dst[u] = 0;
-      d.present[x] = 0;  // the map's last reader (the compaction) is done
-    }
-    const uint32_t i = block_append(claim, &cn->n_touched);
-    if (claim) {
-      sc.touched[i] = s;
-      d.set_idx[s] = i;
-    }
-  }
-}
-
-__global__ __launch_bounds__(kBlock) void k_seg_alloc(const DevState d, Scratch sc, Counters *cn) {
-  if (cn->err) return;
-  const uint32_t T = cn->n_touched;
-  __shared__ uint32_t boff;
-  for (uint32_t base = blockIdx.x * kBlock; base < T; base += gridDim.x * kBlock) {
-    const uint32_t i = base + threadIdx.x;
-    const uint32_t c = i < T ? d.set_count[sc.touched[i]] : 0u;
-    uint32_t tot;
-    const uint32_t ex = block_exclusive_scan(c, tot);
-    if (threadIdx.x == 0) boff = atomicAdd(&cn->seg_cursor, tot);
-    __syncthreads();
-    if (i < T) sc.seg_off[i] = boff + ex;
-    __syncthreads();
-    // sets with more than kSmallSet IDs are ordered by k_big_sort
-    const bool big = c > kSmallSet;
-    const uint32_t j = block_append(big, &cn->n_big);
-    if (big) sc.big[j] = i;
-  }
-}
-
-__global__ void k_place(const DevState d, Scratch sc, const Counters *cn) {
-  if (cn->err) return;
-  const uint32_t U = cn->n_unique;
-  for (uint32_t u = blockIdx.x * kBlock + threadIdx.x; u < U; u += gridDim.x * kBlock)
-    sc.seg[sc.seg_off[d.set_idx[sc.uset[u]]] + sc.arrival[u]] = u;
-}
-
-// Rank of u among the IDs of its set (all smaller unique indices come first)
-// in a set of at most kSmallSet IDs, by counting (at most kSmallSet loads);
-// lays out (u, ID, static score) contiguously per set for the walk.
-__global__ void k_rank(const DevState d, Scratch sc, const Counters *cn) {
-  if (cn->err) return;
-  const uint32_t U = cn->n_unique;
-  for (uint32_t u = blockIdx.x * kBlock + threadIdx.x; u < U; u += gridDim.x * kBlock) {
-    const uint32_t s = sc.uset[u];
-    const uint32_t off = sc.seg_off[d.set_idx[s]];
-    const uint32_t k = d.set_count[s];
-    if (k > kSmallSet) continue;
-    uint32_t r = 0;
-    if (k > 1)
-      for (uint32_t j = 0; j < k; ++j) r += sc.seg[off + j] < u ? 1u : 0u;
-    const uint32_t x = sc.uniq[u];
-    sc.seg_u[off + r] = u;
-    sc.seg_x[off + r] = x;
-    sc.seg_st[off + r] = d.stat[x];
-  }
-}
-
-// A set with more than kSmallSet IDs: one block sorts its segment (distinct
-// unique indices, in arrival order) ascending with an LSD radix sort over
-// 8-bit digits of the index, in O(k) per pass, ping-ponging between seg and
-// seg_u.  Each pass: digit histogram in LDS, exclusive scan, then the scatter
-// in index order, 256 entries at a time: an entry's place among the chunk's
-// entries with the same digit comes from eight ballots per wave (the lanes
-// whose digit matches) and the counts of the lower waves.
-__global__ __launch_bounds__(kBlock) void k_big_sort(const DevState d, Scratch sc, const Counters *cn) {
-  if (cn->err) return;
-  const uint32_t nbig = cn->n_big;
-  const uint32_t U = cn->n_unique;
-  const uint32_t bits = U > 1 ? 32u - (uint32_t)__builtin_clz(U - 1u) : 1u;
-  const uint32_t passes = (bits + 7u) / 8u;
-  __shared__ uint32_t base[256];
-  __shared__ uint32_t wcnt[kBlock / 64][256];
-  const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
-  const uint64_t lt = lane ? (~0ull >> (64u - lane)) : 0ull;
-  for (uint32_t b = blockIdx.x; b < nbig; b += gridDim.x) {
-    const uint32_t i = sc.big[b];
-    const uint32_t off = sc.seg_off[i];
-    const uint32_t k = d.set_count[sc.touched[i]];
-    uint32_t *src = sc.seg + off, *dst = sc.seg_u + off;
-    for (uint32_t p = 0; p < passes; ++p) {
-      const uint32_t shift = 8u * p;
-      base[threadIdx.x] = 0;
-      __syncthreads();
-      for (uint32_t j = threadIdx.x; j < k; j += kBlock) atomicAdd(&base[(src[j] >> shift) & 255u], 1u);
-      __syncthreads();
-      uint32_t tot;
-      const uint32_t ex = block_exclusive_scan(base[threadIdx.x], tot);
-      __syncthreads();
-      base[threadIdx.x] = ex;
-      for (uint32_t c0 = 0; c0 < k; c0 += kBlock) {
+      uint32_t m = 0;  // the ways that hold x
 #pragma unroll
-        for (int w = 0; w < kBlock / 64; ++w) wcnt[w][threadIdx.x] = 0;
-        __syncthreads();
-        const uint32_t j = c0 + threadIdx.x;
-        const bool valid = j < k;
-        const uint32_t v = valid ? src[j] : 0u;
-        const uint32_t dg = (v >> shift) & 255u;
-        uint64_t m = __ballot(valid);
-#pragma unroll
-        for (int bit = 0; bit < 8; ++bit) {
-          const bool on = (dg >> bit) & 1u;
-          const uint64_t bb = __ballot(valid && on);
-          m &= on ? bb : ~bb;
+      for (int w = 0; w < 4; ++w) m |= (a[w] == x ? 1u << w : 0u) | (b[w] == x ? 16u << w : 0u);
+      if (m) {
+        sc.slot[u] = s * kWays + (uint32_t)__builtin_ctz(m);
+      } else {
+        d.set_dirty[s] = (uint32_t)t + 1u;
+        bool entry = false;
+        if (d.V) {
+          const uint64_t vp = d.vpos[x];
+          if (d.qmode)
+            entry = (vp >> 32) == t + 1;
+          else if (vp)
+            entry = d.ring_tag[(vp - 1) % d.V] == x;
         }
-        if (valid && (m & lt) == 0) wcnt[wid][dg] = (uint32_t)__popcll(m);
-        __syncthreads();
-        if (valid) {
-          uint32_t r = base[dg] + (uint32_t)__popcll(m & lt);
-          for (uint32_t w = 0; w < wid; ++w) r += wcnt[w][dg];
-          dst[r] = v;
-        }
-        __syncthreads();
-        uint32_t add = 0;
-#pragma unroll
-        for (int w = 0; w < kBlock / 64; ++w) add += wcnt[w][threadIdx.x];
-        base[threadIdx.x] += add;
+        early = !entry;
       }
-      __syncthreads();
-      uint32_t *tmp = src;
-      src = dst;
-      dst = tmp;
+      sc.early[u] = early ? 1 : 0;
+      c_early += early;
     }
-    // the sorted indices are in src; lay out (u, ID, static score)
-    for (uint32_t j = threadIdx.x; j < k; j += kBlock) {
-      const uint32_t u = src[j];
-      const uint32_t x = sc.uniq[u];
-      sc.seg_u[off + j] = u;
-      sc.seg_x[off + j] = x;
-      sc.seg_st[off + j] = d.stat[x];
+    const uint32_t i = block_append(early, &sc.gate->n_early);
+    if (early) {
+      sc.host_list[i] = u;
+      sc.host_src[i] = kSrcStore | x;
+    }
+  }
+  block_count(c_early, sc.stat_part, kStEarly);
+}
+
+void launch_probe(const DevState &d, uint64_t n, uint64_t t, Scratch &sc, Counters *cn, StatGrids &grids,
+                  hipStream_t s) {
+  const unsigned g = grid_for(n, kBlock, kMaxGrid);
+  hipLaunchKernelGGL(k_probe, dim3(g), dim3(kBlock), 0, s, d, sc, t, cn);
+  grids.g[kStEarly] = g;
+}
+
+// Per touched set (its first arrival's thread): a segment for the IDs of a set
+// to be walked, and its entry in the work list its size calls for; a settled
+// set gets none.  Resets the set's counter.
+__global__ __launch_bounds__(kBlock) void k_seg_alloc(const DevState d, Scratch sc, uint32_t t, Counters *cn) {
+  if (cn->err) return;
+  const uint32_t U = cn->n_unique;
+  __shared__ uint32_t boff, bwork;
+  for (uint32_t base = blockIdx.x * kBlock; base < U; base += gridDim.x * kBlock) {
+    const uint32_t u = base + threadIdx.x;
+    uint32_t s = 0, k = 0;
+    bool walk = false;
+    if (u < U && sc.arrival[u] == 0) {
+      s = sc.uset[u];
+      k = d.set_count[s];
+      d.set_count[s] = 0;
+      walk = d.set_dirty[s] == t + 1u;
+      if (!walk) d.set_off[s] = kSettled;
+    }
+    const bool small = walk && k <= kSmallSet;
+    uint64_t tot;  // segment entries below 2^40, small sets above
+    const uint64_t ex = block_exclusive_scan64((walk ? (uint64_t)k : 0u) | (small ? 1ull << 40 : 0ull), tot);
+    if (threadIdx.x == 0 && tot) {
+      boff = atomicAdd(&cn->seg_cursor, (uint32_t)tot);
+      bwork = atomicAdd(&cn->n_work, (uint32_t)(tot >> 40));
+    }
+    __syncthreads();
+    if (walk) {
+      const WorkSet e{s, boff + (uint32_t)ex, k};
+      d.set_off[s] = e.off;
+      if (small)
+        sc.work[bwork + (uint32_t)(ex >> 40)] = e;
+      else if (k <= kMidSet)
+        sc.work_mid[atomicAdd(&cn->n_mid, 1u)] = e;
+      else
+        sc.work_big[atomicAdd(&cn->n_big, 1u)] = e;
     }
     __syncthreads();
   }
 }
 
-void launch_group_by_set(const DevState &d, const int64_t *ids, uint64_t n, int64_t *inverse, Scratch &sc,
-                         Counters *cn, hipStream_t s) {
+// Per unique ID: the node's unique index (read by the inverse index), the
+// dedup map cleared behind the compaction, the per-ID state reset; then a hit
+// for an ID of a settled set, else its entry in the set's segment, in arrival
+// order.
+__global__ __launch_bounds__(kBlock) void k_place(const DevState d, Scratch sc, const Counters *cn) {
+  if (cn->err) return;
+  const uint32_t U = cn->n_unique;
+  uint32_t c_hit = 0;
+  for (uint32_t u = blockIdx.x * kBlock + threadIdx.x; u < U; u += gridDim.x * kBlock) {
+    const uint32_t x = sc.uniq[u];
+    const uint32_t off = d.set_off[sc.uset[u]];
+    d.uidx[x] = u;
+    d.present[x] = 0;
+    sc.flags[u] = 0;
+    sc.dead[u] = 0;
+    sc.this_q[u] = 0;
+    sc.fill_dst[u] = 0;
+    if (off == kSettled) {
+      sc.kind[u] = kKindHit;
+      ++c_hit;
+    } else {
+      sc.ent[off + sc.arrival[u]] = u32x4{x, u, d.stat[x], 0};
+    }
+  }
+  block_count(c_hit, sc.stat_part, kStSettled);
+}
+
+void launch_group_by_set(const DevState &d, uint64_t n, uint32_t t, Scratch &sc, Counters *cn, StatGrids &grids,
+                         hipStream_t s) {
   const unsigned g = grid_for(n, kBlock, kMaxGrid);
-  hipLaunchKernelGGL(k_inverse_claim, dim3(g), dim3(kBlock), 0, s, d, sc, ids, (uint32_t)n, inverse, cn);
-  hipLaunchKernelGGL(k_seg_alloc, dim3(g), dim3(kBlock), 0, s, d, sc, cn);
+  hipLaunchKernelGGL(k_seg_alloc, dim3(g), dim3(kBlock), 0, s, d, sc, t, cn);
   hipLaunchKernelGGL(k_place, dim3(g), dim3(kBlock), 0, s, d, sc, cn);
-  hipLaunchKernelGGL(k_rank, dim3(g), dim3(kBlock), 0, s, d, sc, cn);
-  // sets of more than kSmallSet IDs exist only if n does
-  if (n > kSmallSet)
-    hipLaunchKernelGGL(k_big_sort, dim3(grid_for(n / (kSmallSet + 1), 1, 256)), dim3(kBlock), 0, s, d, sc, cn);
+  grids.g[kStSettled] = g;
 }
 
 // ---------------------------------------------------------------- set walk
@@ -665,136 +648,311 @@ __device__ __forceinline__ uint64_t group_min(uint64_t v) {
   return v;
 }
 
-// One set per group of 8 lanes, lane w owning way w.  The group walks the
-// set's IDs in ascending order (the per-set order of the definition); each
-// step is a ballot for the tag probe, a ballot for an empty way, and on a full
+// Orders stores and loads of the wave's LDS entries: the lanes of a wave run
+// in lockstep and its LDS operations complete in order, so only the compiler
+// has to be held back.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// A set's IDs in ascending order, in LDS: entry j at index j * S.
+template <uint32_t S>
+struct SetEntries {
+  uint32_t *x, *u, *st;
+  __device__ __forceinline__ void get(uint32_t j, uint32_t &xo, uint32_t &uo, uint32_t &so) const {
+    xo = x[j * S];
+    uo = u[j * S];
+    so = st[j * S];
+  }
+};
+
+// Brings a segment of k <= 8 * G entries (arrival order) into LDS in ascending
+// ID order, by G lanes of one wave (`l` this lane's number among them): each
+// lane keeps up to eight entries in registers and ranks them against all k IDs.
+template <uint32_t G, uint32_t S>
+__device__ __forceinline__ void order_entries(const u32x4 *seg, uint32_t k, uint32_t l, const SetEntries<S> &e) {
+  u32x4 v[8];
+  uint32_t r[8];
+#pragma unroll
+  for (uint32_t q = 0; q < 8; ++q) {
+    r[q] = 0;
+    v[q] = u32x4{0, 0, 0, 0};
+    if (l + q * G < k) {
+      v[q] = seg[l + q * G];
+      e.x[(l + q * G) * S] = v[q].x;
+    }
+  }
+  wave_lds_fence();
+  if (k > G) {
+    for (uint32_t j = 0; j < k; ++j) {
+      const uint32_t y = e.x[j * S];
+#pragma unroll
+      for (uint32_t q = 0; q < 8; ++q) r[q] += y < v[q].x ? 1u : 0u;
+    }
+  } else {
+    for (uint32_t j = 0; j < k; ++j) r[0] += e.x[j * S] < v[0].x ? 1u : 0u;
+  }
+  wave_lds_fence();
+#pragma unroll
+  for (uint32_t q = 0; q < 8; ++q) {
+    if (l + q * G < k) {
+      e.x[r[q] * S] = v[q].x;
+      e.u[r[q] * S] = v[q].y;
+      e.st[r[q] * S] = v[q].z;
+    }
+  }
+  wave_lds_fence();
+}
+
+// A set of more than kMidSet IDs: one block sorts its segment ascending with
+// an LSD radix sort over 8-bit digits of the unique index, in O(k) per pass,
+// ping-ponging between seg and seg_u.  Each pass: digit histogram in LDS,
+// exclusive scan, then the scatter in index order, 256 entries at a time: an
+// entry's place among the chunk's entries with the same digit comes from eight
+// ballots per wave (the lanes whose digit matches) and the counts of the lower
+// waves.  lds: (1 + kBlock / 64) * 256 words.
+__device__ __forceinline__ void sort_big_segment(const DevState &d, const Scratch &sc, uint32_t off, uint32_t k,
+                                                 uint32_t U, uint32_t *lds) {
+  const uint32_t bits = U > 1 ? 32u - (uint32_t)__builtin_clz(U - 1u) : 1u;
+  const uint32_t passes = (bits + 7u) / 8u;
+  uint32_t *base = lds;
+  uint32_t(*wcnt)[256] = reinterpret_cast<uint32_t(*)[256]>(lds + 256);
+  const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
+  const uint64_t lt = lane ? (~0ull >> (64u - lane)) : 0ull;
+  uint32_t *src = sc.seg + off, *dst = sc.seg_u + off;
+  for (uint32_t j = threadIdx.x; j < k; j += kBlock) src[j] = sc.ent[off + j].y;
+  __syncthreads();
+  for (uint32_t p = 0; p < passes; ++p) {
+    const uint32_t shift = 8u * p;
+    base[threadIdx.x] = 0;
+    __syncthreads();
+    for (uint32_t j = threadIdx.x; j < k; j += kBlock) atomicAdd(&base[(src[j] >> shift) & 255u], 1u);
+    __syncthreads();
+    uint32_t tot;
+    const uint32_t ex = block_exclusive_scan(base[threadIdx.x], tot);
+    __syncthreads();
+    base[threadIdx.x] = ex;
+    for (uint32_t c0 = 0; c0 < k; c0 += kBlock) {
+#pragma unroll
+      for (int w = 0; w < kBlock / 64; ++w) wcnt[w][threadIdx.x] = 0;
+      __syncthreads();
+      const uint32_t j = c0 + threadIdx.x;
+      const bool valid = j < k;
+      const uint32_t v = valid ? src[j] : 0u;
+      const uint32_t dg = (v >> shift) & 255u;
+      uint64_t m = __ballot(valid);
+#pragma unroll
+      for (int bit = 0; bit < 8; ++bit) {
+        const bool on = (dg >> bit) & 1u;
+        const uint64_t bb = __ballot(valid && on);
+        m &= on ? bb : ~bb;
+      }
+      if (valid && (m & lt) == 0) wcnt[wid][dg] = (uint32_t)__popcll(m);
+      __syncthreads();
+      if (valid) {
+        uint32_t r = base[dg] + (uint32_t)__popcll(m & lt);
+        for (uint32_t w = 0; w < wid; ++w) r += wcnt[w][dg];
+        dst[r] = v;
+      }
+      __syncthreads();
+      uint32_t add = 0;
+#pragma unroll
+      for (int w = 0; w < kBlock / 64; ++w) add += wcnt[w][threadIdx.x];
+      base[threadIdx.x] += add;
+    }
+    __syncthreads();
+    uint32_t *tmp = src;
+    src = dst;
+    dst = tmp;
+  }
+  // the sorted indices are in src
+  for (uint32_t j = threadIdx.x; j < k; j += kBlock) {
+    const uint32_t u = src[j];
+    const uint32_t x = sc.uniq[u];
+    sc.ent[off + j] = u32x4{x, u, d.stat[x], 0};
+  }
+  __syncthreads();
+}
+
+struct WalkCounts {
+  uint32_t hit = 0, fill = 0, evict = 0, enq = 0, drop = 0, fin = 0;
+};
+
+// One set walked by a group of 8 lanes, lane w owning way w.  The group walks
+// the set's k IDs in ascending order (the per-set order of the definition);
+// `get(j, x, u, st)` gives the j-th to all its lanes.  Each step is a ballot
+// for the tag probe, a ballot for an empty way, and on a full
 // set the policy's victim: for the hybrid order (Sec. 4.2) a 3-step shuffle
 // minimum of (level, static score, way); for the evaluation's ablations
 // (Sec. 5) the minimum of (static score, way), of (no announced use first,
 // then the furthest next use; way), or the set's round-robin pointer.
-template <int P>
-__global__ __launch_bounds__(kBlock) void k_set_walk(const DevState d, Scratch sc, uint32_t t, Counters *cn) {
-  if (cn->err) return;
-  const uint32_t Tn = cn->n_touched;
+template <int P, typename Get>
+__device__ __forceinline__ void walk_set(const DevState &d, const Scratch &sc, uint32_t t, uint32_t s, uint32_t k,
+                                         uint32_t lane, WalkCounts &c, const Get &get) {
   const bool ring_on = d.V > 0;
   const uint32_t recent_lvl = level_of(kClsRecent, ring_on);
-  const uint32_t lane = threadIdx.x & 63u;
   const uint32_t w = lane & (kWays - 1);   // the way this lane owns
   const uint32_t gsh = lane & ~(kWays - 1);  // first lane of the group in the wave
   const bool lead = w == 0;
-  uint32_t c_hit = 0, c_fill = 0, c_evict = 0, c_enq = 0, c_drop = 0, c_final = 0;
-  const uint32_t groups = gridDim.x * (kBlock / kWays);
-  for (uint32_t i = blockIdx.x * (kBlock / kWays) + (threadIdx.x / kWays); i < Tn; i += groups) {
-    const uint32_t s = sc.touched[i];
-    const uint32_t off = sc.seg_off[i];
-    const uint32_t k = d.set_count[s];
-    SetRec *rec = d.sets + s;
-    uint32_t tag = rec->tag[w], st = rec->stat[w], ins = rec->ins[w];
-    uint32_t cls = kClsNone, lvl = 0, dist = 0;
-    bool known = false;  // class (and next-use distance) of this way for this gather computed
-    uint32_t rr = 0;     // round-robin pointer (the record holds its complement)
-    if constexpr (P == kPolicyRoundRobin) rr = ~rec->rr_inv & (kWays - 1);
-    const uint32_t rr0 = rr;
-    int32_t last = -1;   // unique index of this way's last fill
-    bool dirty = false;
-    uint32_t pu = 0, px = 0, ps = 0;  // entry (j & ~7) + w of the segment, loaded 8 at a time
-    for (uint32_t j = 0; j < k; ++j) {
-      if ((j & (kWays - 1)) == 0 && j + w < k) {
-        pu = sc.seg_u[off + j + w];
-        px = sc.seg_x[off + j + w];
-        ps = sc.seg_st[off + j + w];
-      }
-      const int src = (int)(j & (kWays - 1));
-      const uint32_t u = __shfl(pu, src, kWays);
-      const uint32_t x = __shfl(px, src, kWays);
-      const uint32_t xs = __shfl(ps, src, kWays);
-      const uint32_t hitm = (uint32_t)(__ballot(tag == x) >> gsh) & 0xffu;
-      if (hitm) {
-        if (lead) {
-          sc.kind[u] = kKindHit;
-          sc.slot[u] = s * kWays + (uint32_t)__builtin_ctz(hitm);
-          ++c_hit;
-        }
-        continue;
-      }
-      dirty = true;
-      const uint32_t emptym = (uint32_t)(__ballot(tag == kEmpty) >> gsh) & 0xffu;
-      uint32_t pick, z = kEmpty;
-      uint8_t f = 0;
-      if (emptym) {
-        pick = (uint32_t)__builtin_ctz(emptym);
-      } else {
-        if (!known) {  // batch-start resident
-          if (d.U > 1) {  // from the information recorded at the last update
-            class_from_record(d.lreuse[s * kWays + w], ins, t, t - t % d.U, d.T, cls, dist);
-          } else {        // exact: from its announced-use bits
-            const uint32_t m = d.mask[tag];
-            cls = (ins == t) ? kClsRecent : class_from_bits(m, t, d.L, d.T);
-            if (P == kPolicyDynamic || d.qmode) dist = dist_from_bits(m, t, d.L);
-          }
-          lvl = level_of(cls, ring_on);
-          known = true;
-        }
-        if constexpr (P == kPolicyHybrid) {
-          pick = (uint32_t)(group_min(((uint64_t)lvl << 35) | ((uint64_t)st << 3) | w) & 7u);
-        } else if constexpr (P == kPolicyStatic) {
-          pick = (uint32_t)(group_min(((uint64_t)st << 3) | w) & 7u);
-        } else if constexpr (P == kPolicyDynamic) {
-          pick = (uint32_t)(group_min((uint64_t)((dist ? 32u - dist : 0u) << 3) | w) & 7u);
-        } else {
-          pick = rr;
-          rr = (rr + 1u) & (kWays - 1);
-        }
-        z = __shfl(tag, (int)pick, kWays);
-        const uint32_t pc = __shfl(cls, (int)pick, kWays);
-        const uint32_t pd = __shfl(dist, (int)pick, kWays);
-        if (lead) {
-          ++c_evict;
-          if (ring_on && (pc == kClsFar || pc == kClsNear)) {
-            f = (uint8_t)(kFlagEnqueue | (pd << kFlagDistShift));
-            ++c_enq;
-          } else {
-            ++c_drop;
-          }
-        }
-      }
+  SetRec *rec = d.sets + s;
+  uint32_t tag = rec->tag[w], st = rec->stat[w], ins = rec->ins[w];
+  uint32_t cls = kClsNone, lvl = 0, dist = 0;
+  bool known = false;  // class (and next-use distance) of this way for this gather computed
+  uint32_t rr = 0;     // round-robin pointer (the record holds its complement)
+  if constexpr (P == kPolicyRoundRobin) rr = ~rec->rr_inv & (kWays - 1);
+  const uint32_t rr0 = rr;
+  int32_t last = -1;   // unique index of this way's last fill
+  bool dirty = false;
+  for (uint32_t j = 0; j < k; ++j) {
+    uint32_t x, u, xs;
+    get(j, x, u, xs);
+    const uint32_t hitm = (uint32_t)(__ballot(tag == x) >> gsh) & 0xffu;
+    if (hitm) {
       if (lead) {
-        ++c_fill;
-        sc.kind[u] = kKindFill;
-        sc.slot[u] = s * kWays + pick;
-        sc.evicted[u] = z;
-        sc.flags[u] = f;
+        sc.kind[u] = kKindHit;
+        sc.slot[u] = s * kWays + (uint32_t)__builtin_ctz(hitm);
+        ++c.hit;
       }
-      if (w == pick) {
-        tag = x;
-        st = xs;
-        ins = t;
-        cls = kClsRecent;
-        lvl = recent_lvl;
-        dist = 0;  // a line inserted by this gather has no dynamic information yet
+      continue;
+    }
+    dirty = true;
+    const uint32_t emptym = (uint32_t)(__ballot(tag == kEmpty) >> gsh) & 0xffu;
+    uint32_t pick, z = kEmpty;
+    uint8_t f = 0;
+    if (emptym) {
+      pick = (uint32_t)__builtin_ctz(emptym);
+    } else {
+      if (!known) {  // batch-start resident
+        if (d.U > 1) {  // from the information recorded at the last update
+          class_from_record(d.lreuse[s * kWays + w], ins, t, t - t % d.U, d.T, cls, dist);
+        } else {        // exact: from its announced-use bits
+          const uint32_t m = d.mask[tag];
+          cls = (ins == t) ? kClsRecent : class_from_bits(m, t, d.L, d.T);
+          if (P == kPolicyDynamic || d.qmode) dist = dist_from_bits(m, t, d.L);
+        }
+        lvl = level_of(cls, ring_on);
         known = true;
-        last = (int32_t)u;
+      }
+      if constexpr (P == kPolicyHybrid) {
+        pick = (uint32_t)(group_min(((uint64_t)lvl << 35) | ((uint64_t)st << 3) | w) & 7u);
+      } else if constexpr (P == kPolicyStatic) {
+        pick = (uint32_t)(group_min(((uint64_t)st << 3) | w) & 7u);
+      } else if constexpr (P == kPolicyDynamic) {
+        pick = (uint32_t)(group_min((uint64_t)((dist ? 32u - dist : 0u) << 3) | w) & 7u);
+      } else {
+        pick = rr;
+        rr = (rr + 1u) & (kWays - 1);
+      }
+      z = __shfl(tag, (int)pick, kWays);
+      const uint32_t pc = __shfl(cls, (int)pick, kWays);
+      const uint32_t pd = __shfl(dist, (int)pick, kWays);
+      if (lead) {
+        ++c.evict;
+        if (ring_on && (pc == kClsFar || pc == kClsNear)) {
+          f = (uint8_t)(kFlagEnqueue | (pd << kFlagDistShift));
+          ++c.enq;
+        } else {
+          ++c.drop;
+        }
       }
     }
-    if (last >= 0) {  // the way's final occupant refills the cache row
-      sc.fill_dst[last] = s * kWays + w + 1;
-      ++c_final;
+    if (lead) {
+      ++c.fill;
+      sc.kind[u] = kKindFill;
+      sc.slot[u] = s * kWays + pick;
+      sc.evicted[u] = z;
+      sc.flags[u] = f;
     }
-    if (dirty) {
-      rec->tag[w] = tag;
-      rec->stat[w] = st;
-      rec->ins[w] = ins;
+    if (w == pick) {
+      tag = x;
+      st = xs;
+      ins = t;
+      cls = kClsRecent;
+      lvl = recent_lvl;
+      dist = 0;  // a line inserted by this gather has no dynamic information yet
+      known = true;
+      last = (int32_t)u;
     }
-    if constexpr (P == kPolicyRoundRobin)
-      if (lead && rr != rr0) rec->rr_inv = ~rr;
-    if (lead) d.set_count[s] = 0;
   }
-  block_count(c_hit, sc.stat_part, kStHits);
-  block_count(c_fill, sc.stat_part, kStFills);
-  block_count(c_evict, sc.stat_part, kStEvictions);
-  block_count(c_enq, sc.stat_part, kStEnqueued);
-  block_count(c_drop, sc.stat_part, kStDropped);
-  block_count(c_final, sc.stat_part, kStFinal);
+  if (last >= 0) {  // the way's final occupant refills the cache row
+    sc.fill_dst[last] = s * kWays + w + 1;
+    ++c.fin;
+  }
+  if (dirty) {
+    rec->tag[w] = tag;
+    rec->stat[w] = st;
+    rec->ins[w] = ins;
+  }
+  if constexpr (P == kPolicyRoundRobin)
+    if (lead && rr != rr0) rec->rr_inv = ~rr;
+}
+
+// The sets to walk, by size: more than kMidSet IDs, a block sorts the segment
+// in memory and its first 8 lanes walk it; more than kSmallSet, a wave orders
+// the IDs in LDS (512 entries, 6 KB per wave) and its first 8 lanes walk them;
+// the others, 8 lanes each, the wave's LDS shared by its 8 groups (64 entries
+// each).  Ordering here instead of in kernels of its own (a rank pass that
+// loaded every segment k times, and a sort launched for the large sets whether
+// there were any or not) took the probe, the grouping and the walk from eight
+// launches to four: a blocking gather of 250 requests 144 -> 135 us, of 9 K
+// requests 189 -> 171 us.
+template <int P>
+__global__ __launch_bounds__(kBlock) void k_set_walk(const DevState d, Scratch sc, uint32_t t, Counters *cn) {
+  if (cn->err) return;
+  __shared__ uint32_t lds[3 * kMidSet * (kBlock / 64)];
+  static_assert(sizeof(lds) >= (1 + kBlock / 64) * 256 * 4, "the large-set sort works in the same LDS");
+  static_assert(kMidSet == 8 * 64 && kSmallSet == 8 * kWays, "eight entries per ordering lane");
+  const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
+  WalkCounts c;
+  for (uint32_t i = blockIdx.x; i < cn->n_big; i += gridDim.x) {
+    const WorkSet e = sc.work_big[i];
+    sort_big_segment(d, sc, e.off, e.k, cn->n_unique, lds);
+    if (threadIdx.x < kWays) {
+      u32x4 v{};  // entry (j & ~7) + lane, loaded 8 at a time
+      walk_set<P>(d, sc, t, e.set, e.k, lane, c, [&](uint32_t j, uint32_t &x, uint32_t &u, uint32_t &st) {
+        if ((j & (kWays - 1)) == 0 && j + lane < e.k) v = sc.ent[e.off + j + lane];
+        const int src = (int)(j & (kWays - 1));
+        x = __shfl(v.x, src, kWays);
+        u = __shfl(v.y, src, kWays);
+        st = __shfl(v.z, src, kWays);
+      });
+    }
+    __syncthreads();
+  }
+  uint32_t *wl = lds + 3 * kMidSet * wid;  // this wave's
+  const SetEntries<1> mid{wl, wl + kMidSet, wl + 2 * kMidSet};
+  const uint32_t waves = gridDim.x * (kBlock / 64);
+  for (uint32_t i = blockIdx.x * (kBlock / 64) + wid; i < cn->n_mid; i += waves) {
+    const WorkSet e = sc.work_mid[i];
+    order_entries<64>(sc.ent + e.off, e.k, lane, mid);
+    if (lane < kWays)
+      walk_set<P>(d, sc, t, e.set, e.k, lane, c, [&](uint32_t j, uint32_t &x, uint32_t &u, uint32_t &st) {
+        mid.get(j, x, u, st);
+      });
+    wave_lds_fence();
+  }
+  // the wave's groups interleave their entries, so that they read different
+  // LDS banks at the same step
+  const uint32_t g0 = lane / kWays;
+  const SetEntries<kWays> small{wl + g0, wl + kMidSet + g0, wl + 2 * kMidSet + g0};
+  const uint32_t groups = gridDim.x * (kBlock / kWays);
+  const uint32_t nw = cn->n_work;
+  for (uint32_t i = blockIdx.x * (kBlock / kWays) + (threadIdx.x / kWays); i < nw; i += groups) {
+    const WorkSet e = sc.work[i];
+    order_entries<kWays>(sc.ent + e.off, e.k, lane & (kWays - 1), small);
+    walk_set<P>(d, sc, t, e.set, e.k, lane, c, [&](uint32_t j, uint32_t &x, uint32_t &u, uint32_t &st) {
+      small.get(j, x, u, st);
+    });
+    wave_lds_fence();
+  }
+  block_count(c.hit, sc.stat_part, kStHits);
+  block_count(c.fill, sc.stat_part, kStFills);
+  block_count(c.evict, sc.stat_part, kStEvictions);
+  block_count(c.enq, sc.stat_part, kStEnqueued);
+  block_count(c.drop, sc.stat_part, kStDropped);
+  block_count(c.fin, sc.stat_part, kStFinal);
 }
 
 #ifndef LSM_WALK_GRID
@@ -1037,57 +1195,6 @@ __global__ __launch_bounds__(kBlock) void k_qplace(const DevState d, Scratch sc,
   block_count(c_copy, sc.stat_part, kStEnqCopy);
 }
 
-// Misses known from the batch-start state, listed right after the dedup so
-// that their rows start crossing the link while the rest of the metadata
-// runs: a unique ID x that no way of its set holds at batch start is filled
-// at its turn (only x itself inserts x), and with no entry for it in the
-// victim buffer (FIFO: no ring entry naming x; queues: no entry in the queue
-// of this iteration) the fill is a miss, whatever the walk decides.  The
-// resolve, which finds the same outcome, leaves these out of its list.
-__global__ __launch_bounds__(kBlock) void k_early(const DevState d, Scratch sc, uint64_t t, const Counters *cn) {
-  if (cn->err) return;
-  const uint32_t U = cn->n_unique;
-  uint32_t c_early = 0;
-  for (uint32_t base = blockIdx.x * kBlock; base < U; base += gridDim.x * kBlock) {
-    const uint32_t u = base + threadIdx.x;
-    bool early = false;
-    uint32_t x = 0;
-    if (u < U) {
-      x = sc.uniq[u];
-      const u32x4 *tp = reinterpret_cast<const u32x4 *>(d.sets[set_index(x, d.S)].tag);
-      const u32x4 a = tp[0], b = tp[1];
-      const bool resident = a.x == x || a.y == x || a.z == x || a.w == x || b.x == x || b.y == x || b.z == x ||
-                            b.w == x;
-      if (!resident) {
-        bool entry = false;
-        if (d.V) {
-          const uint64_t vp = d.vpos[x];
-          if (d.qmode)
-            entry = (vp >> 32) == t + 1;
-          else if (vp)
-            entry = d.ring_tag[(vp - 1) % d.V] == x;
-        }
-        early = !entry;
-      }
-      sc.early[u] = early ? 1 : 0;
-      c_early += early;
-    }
-    const uint32_t i = block_append(early, &sc.gate->n_early);
-    if (early) {
-      sc.host_list[i] = u;
-      sc.host_src[i] = kSrcStore | x;
-    }
-  }
-  block_count(c_early, sc.stat_part, kStEarly);
-}
-
-void launch_early(const DevState &d, uint64_t n, uint64_t t, Scratch &sc, Counters *cn, StatGrids &grids,
-                  hipStream_t s) {
-  const unsigned g = grid_for(n, kBlock, kMaxGrid);
-  hipLaunchKernelGGL(k_early, dim3(g), dim3(kBlock), 0, s, d, sc, t, cn);
-  grids.g[kStEarly] = g;
-}
-
 // Victim-ring probe of every fill and the row source of every unique ID.  Builds
 // the gather's row-copy lists: the rest of the host fetch's (rows from pinned
 // host memory, after the early misses; dense, in arbitrary order), the hit
@@ -1103,7 +1210,7 @@ __global__ __launch_bounds__(kBlock) void k_resolve(const DevState d, Scratch sc
   // in that order in its staging buffer
   const uint64_t q_lo_prev = tail0 - ((tail0 - tail_prev) < d.V ? (tail0 - tail_prev) : d.V);
   const uint64_t stage_prev = d.stage_row0 + ((t + 1u) & 1u) * d.stage_rows;
-  const uint32_t n_early = sc.gate->n_early;  // the list's first entries, written by k_early
+  const uint32_t n_early = sc.gate->n_early;  // the list's first entries, written by k_probe
   uint32_t c_vhit = 0, c_miss = 0, c_hbm = 0, c_host = 0, c_vring = 0, c_vstaged = 0, c_vsame = 0;
   for (uint32_t base = blockIdx.x * kBlock; base < U; base += gridDim.x * kBlock) {
     const uint32_t u = base + threadIdx.x;
@@ -1220,13 +1327,15 @@ __global__ __launch_bounds__(kBlock) void k_resolve(const DevState d, Scratch sc
   block_count(c_vsame, sc.stat_part, kStVhSame);
 }
 
-// Outcomes per raw request: each request takes its unique ID's outcome (the
-// compaction recorded every requested node's unique index).
-__device__ __forceinline__ void request_counts(const DevState &d, const Scratch &sc, const int64_t *ids,
-                                               uint32_t n) {
+// One pass over the raw requests: the inverse index (if asked for), and the
+// outcome counts (each request takes its unique ID's outcome).
+__device__ __forceinline__ void request_counts(const DevState &d, const Scratch &sc, const int64_t *ids, uint32_t n,
+                                               int64_t *inv) {
   uint32_t c_hit = 0, c_vhit = 0;
   for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
-    const uint8_t o = sc.oc[d.uidx[ids[i]]];
+    const uint32_t u = d.uidx[ids[i]];
+    if (inv) inv[i] = (int64_t)u;
+    const uint8_t o = sc.oc[u];
     c_hit += o == 0;   // LSMGNN_HIT
     c_vhit += o == 1;  // LSMGNN_VICTIM_HIT
   }
@@ -1235,11 +1344,10 @@ __device__ __forceinline__ void request_counts(const DevState &d, const Scratch 
 }
 
 __global__ __launch_bounds__(kBlock) void k_request_counts(const DevState d, Scratch sc, const int64_t *ids,
-                                                           uint32_t n, const Counters *cn) {
+                                                           uint32_t n, int64_t *inv, const Counters *cn) {
   if (cn->err) return;
-  request_counts(d, sc, ids, n);
+  request_counts(d, sc, ids, n, inv);
 }
-
 
 // Ring bookkeeping for this batch's enqueues; lists the row copies of the
 // entries that are still in the ring at the end of the batch.  Those entries
@@ -1247,7 +1355,7 @@ __global__ __launch_bounds__(kBlock) void k_request_counts(const DevState d, Scr
 // enqueues, and their rows are staged in that order (entries removed again in
 // this batch leave a hole that nothing reads).
 __global__ __launch_bounds__(kBlock) void k_enq_finalize(const DevState d, Scratch sc, const int64_t *ids, uint32_t n,
-                                                         Counters *cn) {
+                                                         int64_t *inv, Counters *cn) {
   if (cn->err) return;
   const uint32_t U = cn->n_unique;
   const uint64_t tail0 = d.tail[0];
@@ -1281,8 +1389,8 @@ __global__ __launch_bounds__(kBlock) void k_enq_finalize(const DevState d, Scrat
     }
   }
   block_count(c_copy, sc.stat_part, kStEnqCopy);
-  // the per-request outcome counts, in the same launch
-  request_counts(d, sc, ids, n);
+  // the pass over the requests, in the same launch
+  request_counts(d, sc, ids, n, inv);
 }
 
 void launch_ring_resolve(const DevState &d, uint64_t n, uint64_t t, Scratch &sc, uint8_t *outcome, Counters *cn,
@@ -1309,20 +1417,20 @@ void launch_ring_resolve(const DevState &d, uint64_t n, uint64_t t, Scratch &sc,
   for (int st = kStVhRing; st <= kStVhSame; ++st) grids.g[st] = g;
 }
 
-void launch_ring_enqueue(const DevState &d, const int64_t *ids, uint64_t n, uint64_t t, Scratch &sc, Counters *cn,
-                         StatGrids &grids, hipStream_t s) {
+void launch_ring_enqueue(const DevState &d, const int64_t *ids, uint64_t n, uint64_t t, int64_t *inverse, Scratch &sc,
+                         Counters *cn, StatGrids &grids, hipStream_t s) {
   const unsigned g = grid_for(n, kBlock, kMaxGrid);
   const bool ring = d.V && !d.qmode;
   const bool queues = d.V && d.qmode && d.L > 0;
-  if (ring) {  // with the per-request counts
-    hipLaunchKernelGGL(k_enq_finalize, dim3(g), dim3(kBlock), 0, s, d, sc, ids, (uint32_t)n, cn);
+  if (ring) {  // with the pass over the requests
+    hipLaunchKernelGGL(k_enq_finalize, dim3(g), dim3(kBlock), 0, s, d, sc, ids, (uint32_t)n, inverse, cn);
     grids.g[kStEnqCopy] = g;
   } else {
     if (queues) {
       hipLaunchKernelGGL(k_qplace, dim3(g), dim3(kBlock), 0, s, d, sc, t, cn);
       grids.g[kStEnqCopy] = g;
     }
-    hipLaunchKernelGGL(k_request_counts, dim3(g), dim3(kBlock), 0, s, d, sc, ids, (uint32_t)n, cn);
+    hipLaunchKernelGGL(k_request_counts, dim3(g), dim3(kBlock), 0, s, d, sc, ids, (uint32_t)n, inverse, cn);
   }
   grids.g[kStReqHits] = g;
   grids.g[kStReqVictimHits] = g;

@@ -16,7 +16,10 @@ constexpr int kChunkBytes = kBlock * kBytesPerThread;  // dedup map bytes (nodes
 constexpr int kScanPerThread = 8;    // flags per thread in the enqueue scan
 constexpr int kScanChunk = kBlock * kScanPerThread;
 constexpr int kMaxQueues = 32;       // victim-queue slots: L + 1 <= 32
-constexpr uint32_t kSmallSet = 64;   // sets with more unique IDs in a batch are sorted by a block each
+// sets by their unique IDs in a batch: up to kSmallSet walked and ordered by 8
+// lanes, up to kMidSet ordered by a wave, larger ones sorted by a block
+constexpr uint32_t kSmallSet = 64, kMidSet = 512;
+constexpr uint32_t kSettled = 0xffffffffu;  // set_off of a set that needs no walk
 
 // dynamic classes of a resident line while a gather runs
 enum : uint32_t { kClsNone = 0, kClsFar = 1, kClsRecent = 2, kClsNear = 3 };
@@ -64,6 +67,7 @@ enum StatSlot : int {
   kStReqHits, kStReqVictimHits,                                        // per-request outcomes
   kStVhRing, kStVhStaged, kStVhSame,                                   // victim hits by row source
   kStEarly,                                                            // misses listed before the walk
+  kStSettled,                                                          // hits in sets that need no walk
   kNumStat
 };
 constexpr unsigned kMaxGrid = 8192;  // grid cap of every grid-stride kernel
@@ -76,7 +80,7 @@ struct StatGrids {
 struct Counters {
   uint32_t err;         // nonzero once any ID was out of range
   uint32_t n_unique;
-  uint32_t n_touched;   // distinct sets touched by the batch
+  uint32_t n_work;      // sets to walk with at most kSmallSet unique IDs
   uint32_t seg_cursor;
   uint32_t hits, fills, evictions, enqueued, dropped, victim_hits, misses;
   uint32_t n_hbm, n_host, n_enq_copy, n_fill;  // rows per data kernel
@@ -86,13 +90,13 @@ struct Counters {
   // previous gather's staged evicted rows (HBM), the cache row of a line
   // evicted earlier in the same gather
   uint32_t vh_ring, vh_staged, vh_same;
-  uint32_t n_big;       // touched sets with more than kSmallSet unique IDs
+  uint32_t n_mid, n_big;  // sets to walk with up to kMidSet unique IDs, and with more
   // victim queues (queue mode): enqueue candidates that found their queue
   // full, and per queue slot the entries before this gather and those it placed
   uint32_t q_overflow;
   uint32_t q_before[kMaxQueues];
   uint32_t q_placed[kMaxQueues];
-  uint32_t pad[11];
+  uint32_t pad[10];
 };
 
 // Dedup result of a gather, written by the chunk scan to pinned host memory:
@@ -132,6 +136,13 @@ struct RowList {
   uint32_t *dst;
 };
 
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// A set to be walked: its segment of Scratch::ent and its number of unique IDs.
+struct WorkSet {
+  uint32_t set, off, k;
+};
+
 // Per-call scratch, every array sized for max_batch entries unless noted.
 // The row-copy lists, the gate and the staging rows are read by the row copies
 // of a gather while the next gather's metadata kernels run, so the runtime
@@ -140,19 +151,18 @@ struct Scratch {
   uint32_t *uniq;       // ascending unique IDs
   uint32_t *uset;       // set of uniq[u]
   uint32_t *arrival;    // arrival order of u within its set
-  uint32_t *touched;    // touched set list (arbitrary order)
-  uint32_t *seg_off;    // segment offset of touched[i]
-  uint32_t *seg;        // u grouped by set, arrival order
-  uint32_t *seg_u;      // u grouped by set, ascending within the set
-  uint32_t *seg_x;      // uniq[seg_u[.]]
-  uint32_t *seg_st;     // static score of seg_x[.]
-  uint32_t *big;        // [max_batch / (kSmallSet + 1) + 1] touched-set indices of sets with more than kSmallSet IDs
+  WorkSet *work;        // sets to walk (arbitrary order) with at most kSmallSet IDs
+  WorkSet *work_mid;    // [max_batch / (kSmallSet + 1) + 1] with at most kMidSet
+  WorkSet *work_big;    // [max_batch / (kMidSet + 1) + 1] with more
+  u32x4 *ent;           // (ID, u, static score, -) grouped by set, arrival order
+  uint32_t *seg;        // u of the large sets' entries, sorted between seg and seg_u
+  uint32_t *seg_u;
   uint8_t *kind;
   uint8_t *flags;
   uint8_t *oc;          // outcome of u (LSMGNN_HIT / _VICTIM_HIT / _MISS)
   uint8_t *dead;        // enqueue entry whose line was victim-hit in the same batch
   uint8_t *early;       // 1: u's row is fetched by the early host fetch (a miss known at batch start)
-  uint32_t *slot;       // cache slot (set*8+way) hit or filled by u
+  uint32_t *slot;       // cache slot (set*8+way) hit or filled by u (first, the one that holds it at batch start)
   uint32_t *evicted;    // node evicted by u's fill, or kEmpty
   uint32_t *enq_before; // enqueues by unique IDs below u in this batch
   uint32_t *scan_part;  // ceil(max_batch / kScanChunk) + 2 partial sums
@@ -184,7 +194,8 @@ struct DevState {
   uint8_t *present;      // [nchunks * kChunkBytes] dedup byte map (all zero between calls)
   uint32_t *chunk_sums;  // [nchunks]
   uint32_t *set_count;   // [S] (all zero between calls)
-  uint32_t *set_idx;     // [S]
+  uint32_t *set_dirty;   // [S] 1 + index of the last gather that missed in the set
+  uint32_t *set_off;     // [S] segment of the set's IDs in the current batch, or kSettled
   uint32_t *uidx;        // [N] unique index of the node in the current batch
                          //     (meaningful only where uniq[uidx[x]] == x)
   uint64_t *tail;        // [2] ring entries ever enqueued (the FIFO tail), and
@@ -239,8 +250,8 @@ void launch_finish(Counters *cn, Counters *host, const uint32_t *stat_part, cons
 void launch_dedup(const DevState &d, const int64_t *ids, uint64_t n, const int64_t *ann_ids, uint64_t ann_n,
                   const int64_t *clear_ids, uint64_t clear_n, uint32_t clear_bit, Scratch &sc, int64_t *unique_out,
                   Counters *cn, DedupResult *dd, hipStream_t s);
-void launch_group_by_set(const DevState &d, const int64_t *ids, uint64_t n, int64_t *inverse, Scratch &sc,
-                         Counters *cn, hipStream_t s);
+void launch_group_by_set(const DevState &d, uint64_t n, uint32_t t, Scratch &sc, Counters *cn, StatGrids &grids,
+                         hipStream_t s);
 void launch_set_walk(const DevState &d, uint64_t n, uint32_t t, Scratch &sc, Counters *cn, StatGrids &grids,
                      hipStream_t s);
 // U > 1, before every U-th gather's set walk: record every resident line's next reuse iteration
@@ -251,10 +262,10 @@ void launch_refresh(const DevState &d, uint32_t t, const Counters *cn, hipStream
 void launch_ring_resolve(const DevState &d, uint64_t n, uint64_t t, Scratch &sc, uint8_t *outcome, Counters *cn,
                          StatGrids &grids, hipStream_t s);
 // after the resolve: the enqueues' ring (or queue) entries and the staging
-// list, and the outcome counts per raw request (each request takes its
-// unique ID's outcome)
-void launch_ring_enqueue(const DevState &d, const int64_t *ids, uint64_t n, uint64_t t, Scratch &sc, Counters *cn,
-                         StatGrids &grids, hipStream_t s);
+// list; and per raw request the inverse index (`inverse` may be NULL) and the
+// outcome counts (each request takes its unique ID's outcome)
+void launch_ring_enqueue(const DevState &d, const int64_t *ids, uint64_t n, uint64_t t, int64_t *inverse, Scratch &sc,
+                         Counters *cn, StatGrids &grids, hipStream_t s);
 // Queue mode: copy the queue of gather t+1 (slot `slot`) into prefetch buffer
 // `par`: entries placed by gathers up to t-1 from the pinned host queue, those
 // placed by gather t from its staging rows; sizes from gather t's gate.
@@ -271,13 +282,12 @@ void launch_window_rollback(const int64_t *ids, uint64_t n, uint64_t N, uint32_t
 void launch_copy_plain(const void *src, void *dst, uint64_t bytes, bool device_to_device, hipStream_t s);
 // pageable store: a host-fetch list length in the gate (0 for a rejected gather) to pinned host memory
 void launch_publish_count(const Gate *gate, const uint32_t *count, uint32_t *dst, hipStream_t s);
-// right after the dedup: list the misses known from the batch-start state
-// (no way of the set holds the ID and the victim buffer has no entry for it)
-// as the first entries of the host-fetch list
-void launch_early(const DevState &d, uint64_t n, uint64_t t, Scratch &sc, Counters *cn, StatGrids &grids,
+// right after the dedup: each unique ID's set and batch-start probe; lists the
+// misses known from the batch-start state (no way of the set holds the ID and
+// the victim buffer has no entry for it) as the first entries of the
+// host-fetch list
+void launch_probe(const DevState &d, uint64_t n, uint64_t t, Scratch &sc, Counters *cn, StatGrids &grids,
                   hipStream_t s);
-// uidx[uniq[u]] = u for the gather's unique IDs (n bounds their count)
-void launch_unique_index(const DevState &d, uint64_t n, const Scratch &sc, const Counters *cn, hipStream_t s);
 
 // host twin of the device set-index function
 uint64_t set_of_host(uint64_t x, uint64_t num_sets);

@@ -690,13 +690,12 @@ lsmgnn_status issue_gather(lsmgnn_cache *c, const int64_t *ids, uint64_t n, cons
     // the misses known at batch start first: their rows cross the link while
     // the rest of the metadata runs (pageable store: the host threads copy
     // them meanwhile)
-    lsm::launch_early(d, n, t, f.sc, c->cn, grids, c->meta);
+    lsm::launch_probe(d, n, t, f.sc, c->cn, grids, c->meta);
     if (c->pageable) lsm::launch_publish_count(f.sc.gate, &f.sc.gate->n_early, f.hcount_dev, c->meta);
     (void)hipEventRecord(f.early_done, c->meta);
     if (!c->pageable) host_fetch_early();
-    lsm::launch_unique_index(d, n, f.sc, c->cn, c->meta);
     if (refresh) lsm::launch_refresh(d, (uint32_t)t, c->cn, c->meta);
-    lsm::launch_group_by_set(d, ids, n, inverse, f.sc, c->cn, c->meta);
+    lsm::launch_group_by_set(d, n, (uint32_t)t, f.sc, c->cn, grids, c->meta);
     lsm::launch_set_walk(d, n, (uint32_t)t, f.sc, c->cn, grids, c->meta);
     lsm::launch_ring_resolve(d, n, t, f.sc, outcome, c->cn, grids, c->meta);
     if (c->pageable) {
@@ -714,7 +713,7 @@ lsmgnn_status issue_gather(lsmgnn_cache *c, const int64_t *ids, uint64_t n, cons
     host_fetch_late();
   }
   if (n) {
-    lsm::launch_ring_enqueue(d, ids, n, t, f.sc, c->cn, grids, c->meta);
+    lsm::launch_ring_enqueue(d, ids, n, t, inverse, f.sc, c->cn, grids, c->meta);
   }
   lsm::QueueFinish qf;
   if (queues) {
@@ -950,7 +949,7 @@ lsmgnn_status lsmgnn_cache_create(const lsmgnn_config *cfg, lsmgnn_cache **out) 
             dev_alloc(c, &d.mask, N) &&
             dev_alloc(c, &d.stat, N) && dev_alloc(c, &d.present, map_bytes) &&
             dev_alloc(c, &d.chunk_sums, d.nchunks) &&
-            dev_alloc(c, &d.set_count, S) && dev_alloc(c, &d.set_idx, S) && dev_alloc(c, &d.uidx, N) &&
+            dev_alloc(c, &d.set_count, S) && dev_alloc(c, &d.set_dirty, S) && dev_alloc(c, &d.set_off, S) && dev_alloc(c, &d.uidx, N) &&
             dev_alloc(c, &d.tail, 2) &&
             (V == 0 || (dev_alloc(c, &d.vpos, N) && dev_alloc(c, &d.ring_tag, V))) &&
             (d.U == 1 || dev_alloc(c, &d.lreuse, S * lsm::kWays)) &&
@@ -958,9 +957,11 @@ lsmgnn_status lsmgnn_cache_create(const lsmgnn_config *cfg, lsmgnn_cache **out) 
                          dev_alloc(c, &sc.qpart, (uint64_t)lsm::kMaxQueues * (B / lsm::kBlock + 1)))) &&
             dev_alloc(c, &c->win_ids, (uint64_t)(d.L + 1) * B) && dev_alloc(c, &c->cn, 1) &&
             dev_alloc(c, &sc.uniq, B) && dev_alloc(c, &sc.uset, B) &&
-            dev_alloc(c, &sc.arrival, B) && dev_alloc(c, &sc.touched, B) && dev_alloc(c, &sc.seg_off, B) &&
-            dev_alloc(c, &sc.seg, B) && dev_alloc(c, &sc.seg_u, B) && dev_alloc(c, &sc.seg_x, B) &&
-            dev_alloc(c, &sc.seg_st, B) && dev_alloc(c, &sc.big, B / (lsm::kSmallSet + 1) + 1) && dev_alloc(c, &sc.kind, B) && dev_alloc(c, &sc.flags, B) &&
+            dev_alloc(c, &sc.arrival, B) && dev_alloc(c, &sc.work, B) &&
+            dev_alloc(c, &sc.work_mid, B / (lsm::kSmallSet + 1) + 1) &&
+            dev_alloc(c, &sc.work_big, B / (lsm::kMidSet + 1) + 1) && dev_alloc(c, &sc.ent, B) &&
+            dev_alloc(c, &sc.seg, B) && dev_alloc(c, &sc.seg_u, B) && dev_alloc(c, &sc.kind, B) &&
+            dev_alloc(c, &sc.flags, B) &&
             dev_alloc(c, &sc.oc, B) &&
             dev_alloc(c, &sc.dead, B) && dev_alloc(c, &sc.early, B) && dev_alloc(c, &sc.evicted, B) && dev_alloc(c, &sc.enq_before, B) &&
             dev_alloc(c, &sc.scan_part, B / lsm::kScanChunk + 2) && dev_alloc(c, &sc.this_q, B) &&
@@ -1019,7 +1020,7 @@ lsmgnn_status lsmgnn_cache_create(const lsmgnn_config *cfg, lsmgnn_cache **out) 
   // initial state: all ways empty, nothing announced, ring empty, counters zero
   ok = ok && hipMemset(d.sets, 0xff, S * sizeof(lsm::SetRec)) == hipSuccess &&
        hipMemset(d.mask, 0, N * 4) == hipSuccess && hipMemset(d.present, 0, map_bytes) == hipSuccess &&
-       hipMemset(d.set_count, 0, S * 4) == hipSuccess && hipMemset(d.tail, 0, 16) == hipSuccess &&
+       hipMemset(d.set_count, 0, S * 4) == hipSuccess && hipMemset(d.set_dirty, 0, S * 4) == hipSuccess && hipMemset(d.tail, 0, 16) == hipSuccess &&
        hipMemset(c->cn, 0, sizeof(Counters)) == hipSuccess &&
        hipMemcpy(d.stat, cfg->static_score, N * 4, hipMemcpyHostToDevice) == hipSuccess &&
        (V == 0 || (hipMemset(d.vpos, 0, N * 8) == hipSuccess && hipMemset(d.ring_tag, 0xff, V * 4) == hipSuccess)) &&
