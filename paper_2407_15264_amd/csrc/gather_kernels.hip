@@ -19,7 +19,7 @@
 //               ascending order: tag probe, then on a fill the
 //               empty way or the minimum (level, static score, way) victim
 //               (Sec. 4.2 levels; Sec. 4.3.2 swap when the victim ring is on)
-//   ring        exclusive scan of enqueue flags gives FIFO sequence numbers in
+//   ring        the resolve scans the enqueue flags into FIFO sequence numbers in
 //               ascending-ID order; victim hits are resolved arithmetically:
 //               an entry with sequence q is still in the ring at x's turn iff
 //               q + V >= tail0 + (enqueues before x)  (Sec. 4.3.1)
@@ -384,7 +384,7 @@ __global__ __launch_bounds__(kBlock) void k_compact(uint8_t *present, const uint
   }
 }
 
-constexpr uint32_t kFusedScanMax = 2048;  // at most this many partial sums are added up by each block
+constexpr uint32_t kFusedChunkMax = 2048;  // at most this many chunk sums are added up by each block
 
 void launch_dedup(const DevState &d, const int64_t *ids, uint64_t n, const int64_t *ann_ids, uint64_t ann_n,
                   const int64_t *clear_ids, uint64_t clear_n, uint32_t clear_bit, Scratch &sc, int64_t *unique_out,
@@ -395,7 +395,7 @@ void launch_dedup(const DevState &d, const int64_t *ids, uint64_t n, const int64
   hipLaunchKernelGGL(k_mark, dim3(g), dim3(kBlock), 0, s, ids, (uint32_t)n, ann_ids, (uint32_t)ann_n, d.N,
                      d.present, clear_ids, (uint32_t)clear_n, clear_bit, d.mask, cn);
   hipLaunchKernelGGL(k_chunk_popc, dim3((unsigned)d.nchunks), dim3(kBlock), 0, s, d.present, d.chunk_sums, cn);
-  if (d.nchunks <= kFusedScanMax) {
+  if (d.nchunks <= kFusedChunkMax) {
     hipLaunchKernelGGL(k_compact<true>, dim3((unsigned)d.nchunks), dim3(kBlock), 0, s, d.present, d.chunk_sums,
                        sc.uniq, unique_out, cn, (uint32_t)d.nchunks, dd, sc.gate);
   } else {
@@ -454,6 +454,7 @@ __global__ __launch_bounds__(kBlock) void k_probe(const DevState d, Scratch sc, 
     const uint32_t u = base + threadIdx.x;
     bool early = false;
     uint32_t x = 0;
+    if (threadIdx.x == 0) sc.scan_part[base / kScanChunk] = 0;  // counted up by the walk
     if (u < U) {
       x = sc.uniq[u];
       const uint32_t s = set_index(x, d.S);
@@ -552,7 +553,6 @@ __global__ __launch_bounds__(kBlock) void k_place(const DevState d, Scratch sc, 
     d.present[x] = 0;
     sc.flags[u] = 0;
     sc.dead[u] = 0;
-    sc.this_q[u] = 0;
     sc.fill_dst[u] = 0;
     if (off == kSettled) {
       sc.kind[u] = kKindHit;
@@ -805,6 +805,12 @@ __device__ __forceinline__ void walk_set(const DevState &d, const Scratch &sc, u
   const uint32_t rr0 = rr;
   int32_t last = -1;   // unique index of this way's last fill
   bool dirty = false;
+  // the way's batch-start line, and the unique index whose fill sent it to the
+  // victim ring (only batch-start lines go there): an ID requested later in
+  // the batch than its line was evicted finds its entry through these
+  const uint32_t tag0 = tag;
+  uint32_t sent = kEmpty;
+  const bool fifo = ring_on && !d.qmode;
   for (uint32_t j = 0; j < k; ++j) {
     uint32_t x, u, xs;
     get(j, x, u, xs);
@@ -821,6 +827,11 @@ __device__ __forceinline__ void walk_set(const DevState &d, const Scratch &sc, u
     const uint32_t emptym = (uint32_t)(__ballot(tag == kEmpty) >> gsh) & 0xffu;
     uint32_t pick, z = kEmpty;
     uint8_t f = 0;
+    if (fifo) {
+      const uint32_t em = (uint32_t)(__ballot(sent != kEmpty && tag0 == x) >> gsh) & 0xffu;
+      const uint32_t e = __shfl(sent, em ? (int)__builtin_ctz(em) : 0, kWays);
+      if (lead) sc.this_enq[u] = em ? e : kEmpty;
+    }
     if (emptym) {
       pick = (uint32_t)__builtin_ctz(emptym);
     } else {
@@ -848,11 +859,14 @@ __device__ __forceinline__ void walk_set(const DevState &d, const Scratch &sc, u
       z = __shfl(tag, (int)pick, kWays);
       const uint32_t pc = __shfl(cls, (int)pick, kWays);
       const uint32_t pd = __shfl(dist, (int)pick, kWays);
+      const bool enq = ring_on && (pc == kClsFar || pc == kClsNear);
+      if (enq && w == pick) sent = u;
       if (lead) {
         ++c.evict;
-        if (ring_on && (pc == kClsFar || pc == kClsNear)) {
+        if (enq) {
           f = (uint8_t)(kFlagEnqueue | (pd << kFlagDistShift));
           ++c.enq;
+          if (fifo) atomicAdd(&sc.scan_part[u / kScanChunk], 1u);
         } else {
           ++c.drop;
         }
@@ -978,88 +992,62 @@ void launch_set_walk(const DevState &d, uint64_t n, uint32_t t, Scratch &sc, Cou
 }
 
 // ---------------------------------------------------------- ring sequences
-__global__ __launch_bounds__(kBlock) void k_scan_partial(const uint8_t *flags, uint32_t *part, const Counters *cn) {
-  if (cn->err) return;
-  const uint32_t U = cn->n_unique;
-  const uint32_t nb = (U + kScanChunk - 1) / kScanChunk;
-  for (uint32_t b = blockIdx.x; b < nb; b += gridDim.x) {
-    const uint32_t base = b * kScanChunk + threadIdx.x * kScanPerThread;
-    uint32_t c = 0;
-#pragma unroll
-    for (int k = 0; k < kScanPerThread; ++k)
-      if (base + k < U) c += flags[base + k] & kFlagEnqueue;
-    const uint32_t tot = block_sum(c);
-    if (threadIdx.x == 0) part[b] = tot;
-  }
-}
-
+// The exclusive scan of the enqueue flags in ascending-ID order gives each
+// enqueue its ring sequence number.  The walk counts the enqueues per chunk of
+// kScanChunk unique IDs; the resolve adds up the counts of the chunks before
+// its own, unless there are more than kFusedScanMax of them: then this one
+// block scans them first.
 __global__ __launch_bounds__(kBlock) void k_scan_top(uint32_t *part, Counters *cn) {
   if (cn->err) return;
   const uint32_t U = cn->n_unique;
   const uint32_t nb = (U + kScanChunk - 1) / kScanChunk;
+  constexpr int kPer = 8;
   uint32_t carry = 0;
-  for (uint32_t base = 0; base < nb; base += kBlock) {
-    const uint32_t i = base + threadIdx.x;
-    const uint32_t v = i < nb ? part[i] : 0u;
+  for (uint32_t base = 0; base < nb; base += kBlock * kPer) {
+    const uint32_t i = base + threadIdx.x * kPer;
+    uint32_t v[kPer], sum = 0;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) sum += v[q] = i + q < nb ? part[i + q] : 0u;
     uint32_t tot;
-    const uint32_t ex = block_exclusive_scan(v, tot);
-    if (i < nb) part[i] = carry + ex;
+    uint32_t run = carry + block_exclusive_scan(sum, tot);
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      if (i + q < nb) part[i + q] = run;
+      run += v[q];
+    }
     carry += tot;
   }
   if (threadIdx.x == 0) cn->enq_total = carry;
 }
 
-// Exclusive scan of the enqueue flags in ascending-ID order gives each
-// enqueue its ring sequence number.  An enqueued line requested later in the
-// same batch is told where its entry went.
-// kFused: the chunk's offset is the sum of the earlier chunks' partial counts,
-// added up by the block itself, and the last chunk's block records the total
-// (few chunks: this saves the one-block scan); otherwise scan_part holds the
-// scanned offsets.
-template <bool kFused>
-__global__ __launch_bounds__(kBlock) void k_scan_final(const DevState d, Scratch sc, Counters *cn) {
-  if (cn->err) return;
-  const uint32_t U = cn->n_unique;
-  const uint64_t tail0 = d.tail[0];
-  const uint32_t nb = (U + kScanChunk - 1) / kScanChunk;
-  for (uint32_t b = blockIdx.x; b < nb; b += gridDim.x) {
-    const uint32_t base = b * kScanChunk + threadIdx.x * kScanPerThread;
-    uint32_t f[kScanPerThread];
-    uint32_t c = 0;
-#pragma unroll
-    for (int k = 0; k < kScanPerThread; ++k) {
-      f[k] = (base + k < U) ? (sc.flags[base + k] & kFlagEnqueue) : 0u;
-      c += f[k];
-    }
-    uint32_t tot;
-    const uint32_t ex = block_exclusive_scan(c, tot);
-    uint32_t off;
-    if constexpr (kFused) {
-      uint32_t v = 0;
-      for (uint32_t j = threadIdx.x; j < b; j += kBlock) v += sc.scan_part[j];
-      off = block_sum(v);
-      if (b == nb - 1 && threadIdx.x == 0) cn->enq_total = off + tot;
-    } else {
-      off = sc.scan_part[b];
-    }
-    uint32_t run = off + ex;
-#pragma unroll
-    for (int k = 0; k < kScanPerThread; ++k) {
-      const uint32_t u = base + k;
-      if (u < U) {
-        sc.enq_before[u] = run;
-        if (f[k]) {
-          const uint32_t z = sc.evicted[u];
-          const uint32_t v = d.uidx[z];  // stale unless z is requested in this batch
-          if (v < U && v > u && sc.uniq[v] == z) {
-            sc.this_q[v] = tail0 + run + 1;
-            sc.this_enq[v] = u;
-          }
-        }
-      }
-      run += f[k];
-    }
-  }
+// Enqueue flags set in [a, b).
+__device__ __forceinline__ uint32_t count_enqueues(const uint8_t *flags, uint32_t a, uint32_t b) {
+  uint32_t c = 0;
+  for (; a < b && (a & 3u); ++a) c += flags[a] & kFlagEnqueue;
+  for (; a + 4 <= b; a += 4)
+    c += (uint32_t)__popc(*reinterpret_cast<const uint32_t *>(flags + a) & (0x01010101u * kFlagEnqueue));
+  for (; a < b; ++a) c += flags[a] & kFlagEnqueue;
+  return c;
+}
+
+// At most this many chunk counts are added up by each block of the resolve (16
+// loads per thread); beyond, one block scans them first.
+constexpr uint32_t kFusedScanMax = 4096;
+
+// Where the resolve finds the enqueue counts of the chunks.
+enum : int { kScanNone, kScanCounts, kScanOffsets };
+
+// Whether at most V lines were sent to the ring from the fill of unique index
+// e up to, not including, that of u > e (the entry e made is then still there
+// at u's turn).  before: u's rank among the enqueues of its chunk.
+__device__ __forceinline__ bool at_most_enqueued(const Scratch &sc, uint64_t V, uint32_t e, uint32_t u, int scan,
+                                                 uint32_t before) {
+  const uint32_t ce = e / kScanChunk, cu = u / kScanChunk;
+  if (ce == cu) return count_enqueues(sc.flags, e, u) <= V;
+  uint64_t c = (uint64_t)before + count_enqueues(sc.flags, e, (ce + 1) * kScanChunk);
+  if (scan == kScanOffsets) return c + (sc.scan_part[cu] - sc.scan_part[ce + 1]) <= V;
+  for (uint32_t j = ce + 1; j < cu && c <= V; ++j) c += sc.scan_part[j];
+  return c <= V;
 }
 
 // ------------------------------------------------------------ victim queues
@@ -1200,12 +1188,20 @@ __global__ __launch_bounds__(kBlock) void k_qplace(const DevState d, Scratch sc,
 // host memory, after the early misses; dense, in arbitrary order), the hit
 // copy's (one entry per unique ID: its HBM row, or none) and the fills' (each
 // way's final occupant; dense, in arbitrary order).
+//
+// Ring mode: the enqueues' sequence numbers are scanned here (`scan`): each
+// block adds up all chunks' counts once, those before its own chunk apart, and
+// scans its own chunk's flags.  With the scan in two kernels of its own and a
+// scattered record of every evicted line requested later in the batch (which
+// the walk now knows by itself), a blocking gather of 9 K requests took 171 us
+// against 160.
 __global__ __launch_bounds__(kBlock) void k_resolve(const DevState d, Scratch sc, uint64_t t, uint8_t *outcome,
-                                                    Counters *cn) {
+                                                    int scan, Counters *cn) {
   if (cn->err) return;
+  static_assert(kScanChunk == kBlock, "one chunk of enqueue flags per block pass");
   const uint32_t U = cn->n_unique;
   const uint64_t tail0 = d.tail[0], tail_prev = d.tail[1];
-  const uint64_t tail_end = tail0 + cn->enq_total;
+  uint32_t enq_total = scan == kScanOffsets ? cn->enq_total : 0u;
   // the previous gather's surviving entries, [q_lo_prev, tail0), were staged
   // in that order in its staging buffer
   const uint64_t q_lo_prev = tail0 - ((tail0 - tail_prev) < d.V ? (tail0 - tail_prev) : d.V);
@@ -1217,6 +1213,29 @@ __global__ __launch_bounds__(kBlock) void k_resolve(const DevState d, Scratch sc
     bool from_host = false, from_hbm = false, refill = false;
     uint64_t code = 0;
     uint32_t fd = 0;
+    uint32_t rank = 0, enq_before = 0;  // u's enqueues before it: in its chunk, in the batch
+    if (scan != kScanNone) {
+      const uint32_t chunk = base / kScanChunk;
+      uint32_t off, tot;
+      if (scan == kScanCounts) {
+        const uint32_t nb = (U + kScanChunk - 1) / kScanChunk;
+        uint64_t v = 0, sum;  // all chunks' enqueues, those before this chunk in the upper half
+        for (uint32_t j = threadIdx.x; j < nb; j += kBlock) {
+          const uint64_t p = sc.scan_part[j];
+          v += p | (j < chunk ? p << 32 : 0ull);
+        }
+        (void)block_exclusive_scan64(v, sum);
+        enq_total = (uint32_t)sum;
+        off = (uint32_t)(sum >> 32);
+        if (base == 0 && threadIdx.x == 0) cn->enq_total = enq_total;
+      } else {
+        off = sc.scan_part[chunk];
+      }
+      rank = block_exclusive_scan(u < U ? sc.flags[u] & kFlagEnqueue : 0u, tot);
+      enq_before = off + rank;
+      if (u < U) sc.enq_before[u] = enq_before;
+    }
+    const uint64_t tail_end = tail0 + enq_total;
     if (u < U) {
       const uint8_t kind = sc.kind[u];
       uint8_t oc = 0;  // LSMGNN_HIT
@@ -1246,27 +1265,24 @@ __global__ __launch_bounds__(kBlock) void k_resolve(const DevState d, Scratch sc
       } else {
         const uint32_t x = sc.uniq[u];
         uint64_t q = 0;
-        bool valid = false, same_batch = false;
-        const uint64_t tq = sc.this_q[u];
-        if (tq) {
-          q = tq - 1;
-          valid = true;
-          same_batch = true;
+        bool live = false;
+        const uint32_t e = d.V ? sc.this_enq[u] : kEmpty;
+        const bool same_batch = e != kEmpty;
+        if (same_batch) {
+          live = enq_total <= d.V || u - e <= d.V || at_most_enqueued(sc, d.V, e, u, scan, rank);
         } else if (d.V) {
           const uint64_t vp = d.vpos[x];
           if (vp) {
             q = vp - 1;
-            valid = d.ring_tag[q % d.V] == x;
+            live = d.ring_tag[q % d.V] == x && q + d.V >= tail0 + enq_before;
           }
         }
-        const bool live = valid && q + d.V >= tail0 + sc.enq_before[u];
         if (live) {
           ++c_vhit;
           oc = 1;  // LSMGNN_VICTIM_HIT
           if (same_batch) {
             // evicted earlier in this batch: its row is still in the cache slot
             // the evicting fill took, which no copy has overwritten yet
-            const uint32_t e = sc.this_enq[u];
             code = kSrcHbm | sc.slot[e];
             sc.dead[e] = 1;
             ++c_hbm;
@@ -1396,23 +1412,18 @@ __global__ __launch_bounds__(kBlock) void k_enq_finalize(const DevState d, Scrat
 void launch_ring_resolve(const DevState &d, uint64_t n, uint64_t t, Scratch &sc, uint8_t *outcome, Counters *cn,
                          StatGrids &grids, hipStream_t s) {
   const unsigned g = grid_for(n, kBlock, kMaxGrid);
-  const unsigned gs = grid_for(n, kScanChunk, kMaxGrid);
   const bool ring = d.V && !d.qmode;
   const bool queues = d.V && d.qmode && d.L > 0;  // with L = 0 no line has a reuse iteration
+  int scan = kScanNone;
   if (ring) {
-    hipLaunchKernelGGL(k_scan_partial, dim3(gs), dim3(kBlock), 0, s, sc.flags, sc.scan_part, cn);
-    if ((n + kScanChunk - 1) / kScanChunk <= kFusedScanMax) {
-      hipLaunchKernelGGL(k_scan_final<true>, dim3(gs), dim3(kBlock), 0, s, d, sc, cn);
-    } else {
-      hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kBlock), 0, s, sc.scan_part, cn);
-      hipLaunchKernelGGL(k_scan_final<false>, dim3(gs), dim3(kBlock), 0, s, d, sc, cn);
-    }
+    scan = (n + kScanChunk - 1) / kScanChunk <= kFusedScanMax ? kScanCounts : kScanOffsets;
+    if (scan == kScanOffsets) hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kBlock), 0, s, sc.scan_part, cn);
   }
   if (queues) {
     hipLaunchKernelGGL(k_qcount, dim3(g), dim3(kBlock), 0, s, d, sc, t, cn);
     hipLaunchKernelGGL(k_qtop, dim3(1), dim3(kBlock), 0, s, d, sc, cn);
   }
-  hipLaunchKernelGGL(k_resolve, dim3(g), dim3(kBlock), 0, s, d, sc, t, outcome, cn);
+  hipLaunchKernelGGL(k_resolve, dim3(g), dim3(kBlock), 0, s, d, sc, t, outcome, scan, cn);
   for (int st = kStVictimHits; st <= kStHost; ++st) grids.g[st] = g;
   for (int st = kStVhRing; st <= kStVhSame; ++st) grids.g[st] = g;
 }

@@ -13,8 +13,7 @@ constexpr int kBlock = 256;          // threads per block for every kernel
 constexpr int kBytesPerThread = 64;  // dedup map bytes per thread
 constexpr int kWordsPerThread = kBytesPerThread / 4;
 constexpr int kChunkBytes = kBlock * kBytesPerThread;  // dedup map bytes (nodes) per block
-constexpr int kScanPerThread = 8;    // flags per thread in the enqueue scan
-constexpr int kScanChunk = kBlock * kScanPerThread;
+constexpr uint32_t kScanChunk = kBlock;  // enqueue flags (unique IDs) per partial count
 constexpr int kMaxQueues = 32;       // victim-queue slots: L + 1 <= 32
 // sets by their unique IDs in a batch: up to kSmallSet walked and ordered by 8
 // lanes, up to kMidSet ordered by a wave, larger ones sorted by a block
@@ -165,9 +164,8 @@ struct Scratch {
   uint32_t *slot;       // cache slot (set*8+way) hit or filled by u (first, the one that holds it at batch start)
   uint32_t *evicted;    // node evicted by u's fill, or kEmpty
   uint32_t *enq_before; // enqueues by unique IDs below u in this batch
-  uint32_t *scan_part;  // ceil(max_batch / kScanChunk) + 2 partial sums
-  uint64_t *this_q;     // 1 + ring sequence of u's own enqueue in this batch, or 0
-  uint32_t *this_enq;   // the unique index that enqueued u in this batch
+  uint32_t *scan_part;  // ceil(max_batch / kScanChunk) + 2 enqueue counts
+  uint32_t *this_enq;   // the unique index whose fill enqueued u's line in this batch, or kEmpty (fills only)
   uint32_t *fill_dst;   // 1 + cache slot that out row u refills (the way's final fill), or 0
   uint32_t *stat_part;  // [kNumStat][kMaxGrid] per-block partial counts
   Gate *gate;           // [1]

@@ -964,7 +964,7 @@ lsmgnn_status lsmgnn_cache_create(const lsmgnn_config *cfg, lsmgnn_cache **out) 
             dev_alloc(c, &sc.flags, B) &&
             dev_alloc(c, &sc.oc, B) &&
             dev_alloc(c, &sc.dead, B) && dev_alloc(c, &sc.early, B) && dev_alloc(c, &sc.evicted, B) && dev_alloc(c, &sc.enq_before, B) &&
-            dev_alloc(c, &sc.scan_part, B / lsm::kScanChunk + 2) && dev_alloc(c, &sc.this_q, B) &&
+            dev_alloc(c, &sc.scan_part, B / lsm::kScanChunk + 2) &&
             dev_alloc(c, &sc.this_enq, B) && dev_alloc(c, &sc.slot, B) && dev_alloc(c, &sc.fill_dst, B) &&
             dev_alloc(c, &sc.stat_part, (uint64_t)lsm::kNumStat * lsm::kMaxGrid) &&
             host_alloc(c, &c->dd, &c->dd_dev, sizeof(DedupResult), true) &&

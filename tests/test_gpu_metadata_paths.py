@@ -1,6 +1,7 @@
 """GPU <-> oracle parity at the sizes where the metadata kernels change path:
 the number of a batch's IDs in one set (ordered by 8 lanes, by a wave, by a
-block), and sets that are settled by the probe beside sets that are walked.
+block), sets that are settled by the probe beside sets that are walked, and
+ring sizes on both sides of what one chunk, and a whole batch, enqueues.
 Every integer and byte output must match exactly (tests/parity_driver.py).
 """
 import numpy as np
@@ -54,3 +55,28 @@ def test_settled_and_walked_sets(sets, victim):
     stat = rng.integers(0, 9, n).astype(np.uint32)
     run_parity(store, stat, sets, victim, 4, batches, rows="all", label="settled")
     run_async_parity(store, stat, sets, victim, 4, batches, rows="all", label="settled pipelined")
+
+
+@pytest.mark.parametrize("victim", [1, 100, 255, 256, 257, 700, 5000])
+def test_ring_liveness_within_a_batch(victim):
+    """Lines evicted to the ring and requested again later in the same batch, with rings that the batch's enqueues
+    overrun before, at and after that request."""
+    log(f"case: same-batch ring liveness, V={victim}")
+    n, sets = 6000, 300
+    rng = np.random.default_rng(victim)
+    batches = [rng.choice(n, 4000) for _ in range(8)]
+    store = Store.random_bytes(n, 16, 2)
+    stat = rng.integers(0, 3, n).astype(np.uint32)
+    run_parity(store, stat, sets, victim, 5, batches, rows="all", label=f"V={victim}")
+
+
+@pytest.mark.parametrize("requests", [(1 << 20) - 255, (1 << 20) + 1])
+def test_enqueue_scan_limit(requests):
+    """Request lists on both sides of the size beyond which the chunks' enqueue counts are scanned by their own kernel."""
+    log(f"case: {requests} requests")
+    n = 700_000
+    rng = np.random.default_rng(requests)
+    batches = [rng.integers(0, n, requests) for _ in range(3)]
+    store = Store.random_bytes(n, 16, 3)
+    stat = rng.integers(0, 50, n).astype(np.uint32)
+    run_parity(store, stat, 20_000, 30_000, 3, batches, rows="all", label="scan limit")
