@@ -1585,12 +1585,18 @@ __global__ __launch_bounds__(kBlock) void k_host_fetch(const DevState d, Scratch
 #ifndef LSM_HBM_GRID
 #define LSM_HBM_GRID 65536  // the HBM-side copies: the largest grid of the measured sweep
 #endif
+// Staging and fills move the evicted and the missed rows, often few or none of
+// the batch's, while their grid is sized for all of it: blocks that find
+// nothing cost 20 us per launch at 65536 of them, under 5 us at 8192, and a
+// long list moves as fast with either.
+constexpr unsigned kListGrid = 8192;
 
 template <CopyMode M>
 static void launch_list(const uint8_t *src, const RowList &l, uint8_t *dst, const Gate *gate, const uint32_t *count,
                         uint64_t n, uint64_t R, hipStream_t s) {
   const uint32_t nvec = (uint32_t)(R / 16);
-  const unsigned g = grid_for(n * nvec, (uint64_t)kBlock * kListUnroll, LSM_HBM_GRID);
+  const unsigned g = grid_for(n * nvec, (uint64_t)kBlock * kListUnroll,
+                              M == CopyMode::kHbmToOut ? LSM_HBM_GRID : kListGrid);
   if ((nvec & (nvec - 1)) == 0)
     hipLaunchKernelGGL((k_list_copy<M, true>), dim3(g), dim3(kBlock), 0, s, src, l.src, dst, l.dst, gate, count, R,
                        nvec, (uint32_t)__builtin_ctz(nvec));
