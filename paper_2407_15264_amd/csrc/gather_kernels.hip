@@ -108,6 +108,11 @@ __device__ __forceinline__ Gate gate_with(uint32_t err, uint32_t n_unique) {
   return g;
 }
 
+// The dedup's result for the host, which polls for it.
+__device__ __forceinline__ void publish_dedup(DedupResult *dd, uint32_t tag, uint32_t err, uint32_t n_unique) {
+  __hip_atomic_store(&dd->word, dedup_word(tag, err, n_unique), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 static inline unsigned grid_for(uint64_t work, uint64_t per_block, unsigned cap) {
   uint64_t b = (work + per_block - 1) / per_block;
   if (b < 1) b = 1;
@@ -223,7 +228,10 @@ __global__ __launch_bounds__(kBlock) void k_finish(Counters *cn, Counters *host,
   }
   __syncthreads();
   if (threadIdx.x < kWords) {
-    reinterpret_cast<uint32_t *>(host)[threadIdx.x] = reinterpret_cast<const uint32_t *>(&c)[threadIdx.x];
+    // written through: the host reads them once a later kernel's word is there
+    __hip_atomic_store(reinterpret_cast<uint32_t *>(host) + threadIdx.x,
+                       reinterpret_cast<const uint32_t *>(&c)[threadIdx.x], __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
     reinterpret_cast<uint32_t *>(cn)[threadIdx.x] = 0u;
   }
 }
@@ -301,12 +309,12 @@ __global__ __launch_bounds__(kBlock) void k_chunk_popc(const uint8_t *present, u
 }
 
 __global__ __launch_bounds__(kBlock) void k_chunk_scan(uint32_t *chunk_sums, uint32_t nchunks, Counters *cn,
-                                                       DedupResult *dd, Gate *gate) {
+                                                       DedupResult *dd, uint32_t tag, Gate *gate) {
   const uint32_t err = cn->err;
   if (err) {
     if (threadIdx.x == 0) {
       *gate = gate_with(err, 0);
-      *dd = DedupResult{err, 0, {0, 0}};
+      publish_dedup(dd, tag, err, 0);
     }
     return;
   }
@@ -322,7 +330,7 @@ __global__ __launch_bounds__(kBlock) void k_chunk_scan(uint32_t *chunk_sums, uin
   if (threadIdx.x == 0) {
     cn->n_unique = carry;
     *gate = gate_with(0, carry);
-    *dd = DedupResult{0, carry, {0, 0}};
+    publish_dedup(dd, tag, 0, carry);
   }
 }
 
@@ -335,7 +343,7 @@ __global__ __launch_bounds__(kBlock) void k_chunk_scan(uint32_t *chunk_sums, uin
 template <bool kFused>
 __global__ __launch_bounds__(kBlock) void k_compact(uint8_t *present, const uint32_t *chunk_off, uint32_t *uniq,
                                                     int64_t *uniq_out, Counters *cn, uint32_t nchunks,
-                                                    DedupResult *dd, Gate *gate) {
+                                                    DedupResult *dd, uint32_t tag, Gate *gate) {
   uint32_t w[kWordsPerThread];
   load_words(present, w);
   const size_t b0 = ((size_t)blockIdx.x * kBlock + threadIdx.x) * kBytesPerThread;  // first byte of this thread
@@ -346,7 +354,7 @@ __global__ __launch_bounds__(kBlock) void k_compact(uint8_t *present, const uint
       if (w[k]) reinterpret_cast<uint32_t *>(present + b0)[k] = 0;
     if (kFused && blockIdx.x == 0 && threadIdx.x == 0) {
       *gate = gate_with(err, 0);
-      *dd = DedupResult{err, 0, {0, 0}};
+      publish_dedup(dd, tag, err, 0);
     }
     return;
   }
@@ -364,7 +372,7 @@ __global__ __launch_bounds__(kBlock) void k_compact(uint8_t *present, const uint
       const uint32_t total = first + tot;
       cn->n_unique = total;
       *gate = gate_with(0, total);
-      *dd = DedupResult{0, total, {0, 0}};
+      publish_dedup(dd, tag, 0, total);
     }
   } else {
     first = chunk_off[blockIdx.x];
@@ -388,7 +396,7 @@ constexpr uint32_t kFusedChunkMax = 2048;  // at most this many chunk sums are a
 
 void launch_dedup(const DevState &d, const int64_t *ids, uint64_t n, const int64_t *ann_ids, uint64_t ann_n,
                   const int64_t *clear_ids, uint64_t clear_n, uint32_t clear_bit, Scratch &sc, int64_t *unique_out,
-                  Counters *cn, DedupResult *dd, hipStream_t s) {
+                  Counters *cn, DedupResult *dd, uint32_t tag, hipStream_t s) {
   uint64_t work = n > clear_n ? n : clear_n;
   work = work > ann_n ? work : ann_n;
   const unsigned g = grid_for(work, kBlock, kMaxGrid);
@@ -397,12 +405,12 @@ void launch_dedup(const DevState &d, const int64_t *ids, uint64_t n, const int64
   hipLaunchKernelGGL(k_chunk_popc, dim3((unsigned)d.nchunks), dim3(kBlock), 0, s, d.present, d.chunk_sums, cn);
   if (d.nchunks <= kFusedChunkMax) {
     hipLaunchKernelGGL(k_compact<true>, dim3((unsigned)d.nchunks), dim3(kBlock), 0, s, d.present, d.chunk_sums,
-                       sc.uniq, unique_out, cn, (uint32_t)d.nchunks, dd, sc.gate);
+                       sc.uniq, unique_out, cn, (uint32_t)d.nchunks, dd, tag, sc.gate);
   } else {
     hipLaunchKernelGGL(k_chunk_scan, dim3(1), dim3(kBlock), 0, s, d.chunk_sums, (uint32_t)d.nchunks, cn, dd,
-                       sc.gate);
+                       tag, sc.gate);
     hipLaunchKernelGGL(k_compact<false>, dim3((unsigned)d.nchunks), dim3(kBlock), 0, s, d.present, d.chunk_sums,
-                       sc.uniq, unique_out, cn, (uint32_t)d.nchunks, dd, sc.gate);
+                       sc.uniq, unique_out, cn, (uint32_t)d.nchunks, dd, tag, sc.gate);
   }
 }
 
@@ -1511,17 +1519,18 @@ __global__ __launch_bounds__(kBlock) void k_list_copy(const uint8_t *src, const 
 #endif
 //
 // The list has two parts: its first n_early entries (misses known at batch
-// start, `late` false) and the n_host entries after them (the resolve's,
-// `late` true); each launch moves one part.
+// start) and the n_host entries after them (the resolve's); a launch moves one
+// part (M = kHostEarly, kHostLate) or both (kHostAll).
 template <bool kPow2>
 __global__ __launch_bounds__(kBlock) void k_host_fetch(const DevState d, Scratch sc, uint8_t *out, uint32_t nvec,
-                                                       uint32_t vshift, int late) {
+                                                       uint32_t vshift, CopyMode part) {
   constexpr int kU = LSM_HOST_UNROLL;
   const Gate g = *sc.gate;
   if (g.err) return;
   const uint64_t R = d.R;
-  const uint32_t first = late ? g.n_early : 0u;
-  const uint64_t total = (uint64_t)(late ? g.n_host : g.n_early) * nvec;
+  const uint32_t first = part == CopyMode::kHostLate ? g.n_early : 0u;
+  const uint32_t end = part == CopyMode::kHostEarly ? g.n_early : g.n_early + g.n_host;
+  const uint64_t total = (uint64_t)(end - first) * nvec;
   const uint64_t stride = (uint64_t)gridDim.x * kBlock;
   const uint32_t *list = sc.host_list + first;
   const uint64_t *src = sc.host_src + first;
@@ -1609,13 +1618,12 @@ void launch_copy(CopyMode mode, const DevState &d, uint64_t n, const Scratch &sc
   const uint32_t nvec = (uint32_t)(d.R / 16);
   const bool pow2 = (nvec & (nvec - 1)) == 0;
   const uint32_t vshift = pow2 ? (uint32_t)__builtin_ctz(nvec) : 0u;
-  if (mode == CopyMode::kHostToOut || mode == CopyMode::kHostEarly) {
+  if (mode == CopyMode::kHostLate || mode == CopyMode::kHostEarly || mode == CopyMode::kHostAll) {
     const unsigned g = grid_for(n * nvec, (uint64_t)kBlock * kUnroll, d.host_grid ? d.host_grid : LSM_HOST_GRID);
-    const int late = mode == CopyMode::kHostToOut;
     if (pow2)
-      hipLaunchKernelGGL((k_host_fetch<true>), dim3(g), dim3(kBlock), 0, s, d, sc, out, nvec, vshift, late);
+      hipLaunchKernelGGL((k_host_fetch<true>), dim3(g), dim3(kBlock), 0, s, d, sc, out, nvec, vshift, mode);
     else
-      hipLaunchKernelGGL((k_host_fetch<false>), dim3(g), dim3(kBlock), 0, s, d, sc, out, nvec, vshift, late);
+      hipLaunchKernelGGL((k_host_fetch<false>), dim3(g), dim3(kBlock), 0, s, d, sc, out, nvec, vshift, mode);
     return;
   }
   switch (mode) {
@@ -1747,7 +1755,8 @@ __global__ void k_window_set(const int64_t *ids, uint32_t n, uint64_t N, uint32_
       if (!(m & b)) mask[x] = m | b;
     }
   }
-  if (__ballot(bad) && __lane_id() == 0) *err = 1u;  // every writer stores the same value
+  if (__ballot(bad) && __lane_id() == 0)  // every writer stores the same value
+    __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // After a rejected announcement (the host launches it only then): clear the

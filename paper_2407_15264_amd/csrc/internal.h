@@ -98,13 +98,16 @@ struct Counters {
   uint32_t pad[10];
 };
 
-// Dedup result of a gather, written by the chunk scan to pinned host memory:
-// the host reads the unique count and the error flag from it.
+// Dedup result of a gather, written by the dedup's last kernel to pinned host
+// memory: one word, so that the host, which polls it, reads the unique count
+// and the error flag of the dedup it waits for (`tag`) or none.
 struct DedupResult {
-  uint32_t err;
-  uint32_t n_unique;
-  uint32_t pad[2];
+  uint64_t word;
 };
+__host__ __device__ inline uint64_t dedup_word(uint32_t tag, uint32_t err, uint32_t n_unique) {
+  return ((uint64_t)tag << 33) | ((uint64_t)(err ? 1u : 0u) << 32) | n_unique;
+}
+constexpr uint32_t kDedupTagMask = 0x7fffffffu;
 
 // The gather's gate in device memory: the error flag and unique count (set by
 // the chunk scan) and the lengths of the row-copy lists (appended by the
@@ -217,9 +220,9 @@ struct DevState {
   uint64_t stage_rows;   // rows per staging buffer: min(max_batch, V)
 };
 
-// kHostEarly / kHostToOut: the host fetch of the host-fetch list's first
-// n_early entries, and of the rest
-enum class CopyMode { kHbmToOut, kHostToOut, kCacheToStage, kOutToCache, kHostEarly };
+// kHostEarly / kHostLate / kHostAll: the host fetch of the host-fetch list's
+// first n_early entries, of the rest, of all
+enum class CopyMode { kHbmToOut, kHostLate, kCacheToStage, kOutToCache, kHostEarly, kHostAll };
 
 // What the last kernel of a gather does for the victim queues: empty the
 // served slot `cur` and record in the gate what the prefetch of slot `next`
@@ -247,7 +250,7 @@ void launch_finish(Counters *cn, Counters *host, const uint32_t *stat_part, cons
 // ann_ids/ann_n: the list announced with this gather (validated here), or NULL/0
 void launch_dedup(const DevState &d, const int64_t *ids, uint64_t n, const int64_t *ann_ids, uint64_t ann_n,
                   const int64_t *clear_ids, uint64_t clear_n, uint32_t clear_bit, Scratch &sc, int64_t *unique_out,
-                  Counters *cn, DedupResult *dd, hipStream_t s);
+                  Counters *cn, DedupResult *dd, uint32_t tag, hipStream_t s);
 void launch_group_by_set(const DevState &d, uint64_t n, uint32_t t, Scratch &sc, Counters *cn, StatGrids &grids,
                          hipStream_t s);
 void launch_set_walk(const DevState &d, uint64_t n, uint32_t t, Scratch &sc, Counters *cn, StatGrids &grids,

@@ -21,10 +21,16 @@
 //           less than a copy kernel of ours writing over the host link), and
 //           after each ring write the fills of the next gather; without a
 //           victim buffer, the hit copy of pipelined gathers too
+// A gather expected to fetch little over the link (queue_serial below) runs on
+// the meta stream alone: there is nothing to overlap, and each hand-over
+// between streams costs 10-15 us.
+//
 // The host queues all of a gather's kernels at once (every batch-dependent
 // size, and the ring tail, stay in device memory) and then waits only for the
 // dedup result, to report the unique count or reject the batch; a rejected
-// batch's kernels are already queued and do nothing.  A runtime copy needs its
+// batch's kernels are already queued and do nothing.  It polls for that result
+// in pinned memory: an event behind the dedup would be one more packet, about
+// 6 us, on every gather's critical path.  A runtime copy needs its
 // size on the host, so gather t's ring write is queued once its counters are
 // known: by the next call's dedup wait, or by any call that synchronises.
 // The metadata of gather t+1 depends only on the metadata of gather t, so it
@@ -56,6 +62,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <thread>
 #include <vector>
 
 #include "host_pool.h"
@@ -116,7 +123,8 @@ struct Flight {
   bool dma_pending = false;    // staged rows not yet queued for the ring
   bool dma_used = false;       // dma_done has been recorded at least once
   uint64_t dma_seq = 0, fill_seq = 0;  // positions of the ring write and the fill among the cache's dma submissions
-  bool fill_host = false;              // the fills ran on the host-link stream (blocking gather), not the dma one
+  enum Fill { kDma, kHost, kMeta };
+  Fill fill = kDma;                    // the stream the fills ran on
   bool hit_dma = false;                // the hit copy ran on the dma stream
   uint64_t t = 0, requests = 0;
   uint64_t enq_total = 0, tail_end = 0;  // enqueues of the gather, ring tail after it
@@ -136,6 +144,7 @@ struct PerfSet {
   bool pf = false;       // the prefetch this gather issued for the next one was timed
   uint64_t t = 0, requests = 0;
   uint32_t n_hbm = 0, n_host = 0, n_enq = 0, n_fill = 0, n_pf = 0;
+  uint32_t host_launches = 2;
 };
 
 // The per-device stream triple, created with the first cache on a device and
@@ -201,6 +210,8 @@ struct lsmgnn_cache {
   // a separate announcement's error flag (pinned), set by the window kernel
   uint32_t *adv_err = nullptr, *adv_err_dev = nullptr;
   DedupResult *dd = nullptr, *dd_dev = nullptr;
+  uint32_t dd_tag = 0;           // of the last dedup queued
+  uint64_t host_rows = ~0ull, rows = ~0ull;  // rows the last accounted gather fetched over the link, and in all
   Flight fl[2];
   PerfSet ps[kPerfSets];
   hipStream_t meta = nullptr, host = nullptr, dma = nullptr;  // the device's shared streams
@@ -209,7 +220,7 @@ struct lsmgnn_cache {
   bool pageable = false;         // the backing store is pageable: host threads copy its rows
   const uint8_t *store_host = nullptr;
   lsm::HostPool *pool = nullptr;
-  hipEvent_t ev_in = nullptr, ev_dedup = nullptr, ev_adv = nullptr;
+  hipEvent_t ev_in = nullptr, ev_adv = nullptr;
   hipEvent_t ev_q = nullptr;  // queue mode: the queue writes queued so far have landed
   uint64_t t = 0;  // gathers issued
   // Submissions of this cache to the in-order dma stream are numbered; the
@@ -242,7 +253,7 @@ void release(lsmgnn_cache *c) {
   for (PerfSet &p : c->ps)
     for (hipEvent_t e : p.e)
       if (e) (void)hipEventDestroy(e);
-  for (hipEvent_t e : {c->ev_in, c->ev_dedup, c->ev_adv, c->ev_q})
+  for (hipEvent_t e : {c->ev_in, c->ev_adv, c->ev_q})
     if (e) (void)hipEventDestroy(e);
   if (c->has_streams) release_streams(c->device);
   c->has_streams = false;
@@ -322,6 +333,8 @@ void harvest_stats(lsmgnn_cache *c, Flight &f) {
   c->total.victim_rows_staged += st.victim_rows_staged;
   c->total.victim_rows_cache += st.victim_rows_cache;
   c->total.victim_rows_prefetched += st.victim_rows_prefetched;
+  c->host_rows = h.n_host;
+  c->rows = h.n_unique;
   c->tail += h.enq_total;
   f.enq_total = h.enq_total;
   f.tail_end = c->tail;
@@ -367,12 +380,35 @@ bool after_caller(lsmgnn_cache *c, hipStream_t s) {
   return hipEventRecord(c->ev_in, s) == hipSuccess && hipStreamWaitEvent(c->meta, c->ev_in, 0) == hipSuccess;
 }
 
-// Make the meta stream wait for gather G's fills.
+// Make the meta stream wait for gather G's fills (they may be on it).
 void meta_wait_fills(lsmgnn_cache *c, const Flight &G) {
-  if (G.fill_host)
+  if (G.fill == Flight::kHost)
     (void)hipStreamWaitEvent(c->meta, G.data_done, 0);
-  else
+  else if (G.fill == Flight::kDma)
     meta_wait_dma(c, G.data_done, G.fill_seq);
+}
+
+// Wait for the result of the last dedup queued.  false: the stream failed, or
+// ended without it.
+bool wait_dedup(lsmgnn_cache *c, uint32_t *err, uint32_t *n_unique) {
+  const uint32_t tag = c->dd_tag & lsm::kDedupTagMask;
+  auto there = [&] {
+    const uint64_t w = __atomic_load_n(&c->dd->word, __ATOMIC_ACQUIRE);
+    *err = (uint32_t)(w >> 32) & 1u;
+    *n_unique = (uint32_t)w;
+    return (uint32_t)(w >> 33) == tag;
+  };
+  for (uint32_t spin = 1; !there(); ++spin) {
+    _mm_pause();
+    if (spin & 0x3ffu) continue;
+    // every 1024 polls: an idle stream has written its last word
+    const hipError_t q = hipStreamQuery(c->meta);
+    if (q == hipSuccess) return there();
+    (void)hipGetLastError();
+    if (q != hipErrorNotReady) return false;
+    std::this_thread::yield();
+  }
+  return true;
 }
 
 // Queue a harvested gather's ring write: its E enqueues have the sequence
@@ -393,11 +429,15 @@ void issue_dma(lsmgnn_cache *c, Flight &f, hipEvent_t after = nullptr) {
   const uint64_t V = c->d.V, R = c->d.R;
   PerfSet &p = c->ps[f.t % kPerfSets];
   const bool prof = p.pending && p.t == f.t;
-  (void)hipStreamWaitEvent(c->dma, f.stage_done, 0);
-  // the gather's own host fetch may read ring rows this write overwrites
-  // (victim hits on older entries in slots its enqueues take); a blocking
-  // gather's fills follow its host fetch on the host-link stream
-  (void)hipStreamWaitEvent(c->dma, f.fill_host ? f.data_done : f.host_done, 0);
+  // the staging, and the gather's own host fetch, which may read ring rows
+  // this write overwrites (victim hits on older entries in slots its enqueues
+  // take); fills on another stream follow both
+  if (f.fill == Flight::kDma) {
+    (void)hipStreamWaitEvent(c->dma, f.stage_done, 0);
+    (void)hipStreamWaitEvent(c->dma, f.host_done, 0);
+  } else {
+    (void)hipStreamWaitEvent(c->dma, f.data_done, 0);
+  }
   if (after) (void)hipStreamWaitEvent(c->dma, after, 0);
   if (prof) (void)hipEventRecord(p.e[kEvEnq0], c->dma);
   if (c->d.qmode) {
@@ -490,7 +530,7 @@ void harvest_profile(lsmgnn_cache *c, PerfSet &p) {
       c->acc.enqueue_rows += p.n_enq;
     }
     c->acc.host_fetch_ms += el(kEvHost0, kEvHostMid) + el(kEvHostLate, kEvHost1);  // not the wait between them
-    c->acc.host_fetch_launches += 2;
+    c->acc.host_fetch_launches += p.host_launches;
     c->acc.host_fetch_rows += p.n_host;
     c->acc.fill_ms += el(kEvFill0, kEvFill1);
     c->acc.fill_launches += 1;
@@ -510,14 +550,15 @@ void harvest_profile(lsmgnn_cache *c, PerfSet &p) {
 // survive in the victim buffer, copied to its staging rows, once gather g-1's
 // fills (the cache rows) and gather g-2's ring write (the staging rows of
 // parity g) have landed.  Without a victim buffer there is nothing to stage.
-void queue_stage(lsmgnn_cache *c, uint64_t g) {
+// `event`: record stage_done (fills on another stream than the dma one imply it).
+void queue_stage(lsmgnn_cache *c, uint64_t g, bool event) {
   DevState &d = c->d;
   Flight &G = c->fl[g & 1], &P = c->fl[(g + 1) & 1];
   if (d.V) {
     if (P.used) meta_wait_fills(c, P);
     if (G.dma_used) meta_wait_dma(c, G.dma_done, G.dma_seq);
     if (G.data_n) lsm::launch_copy(CopyMode::kCacheToStage, d, G.data_n, G.sc, G.data_out, c->meta);
-    (void)hipEventRecord(G.stage_done, c->meta);
+    if (event) (void)hipEventRecord(G.stage_done, c->meta);
   }
   G.used = true;
 }
@@ -534,15 +575,18 @@ void queue_stage(lsmgnn_cache *c, uint64_t g) {
 // gathers of 900 K requests (235 K resident 2 KiB rows each) took 1191 us
 // against 1465.  With a victim buffer the copy would wait there for the
 // previous gather's ring write, which can take as long as the host fetch.
-void queue_hit(lsmgnn_cache *c, uint64_t g, bool on_dma) {
+//
+// `event`: record hit_done (for fills on another stream).
+void queue_hit(lsmgnn_cache *c, uint64_t g, bool on_dma, bool event) {
   DevState &d = c->d;
   Flight &G = c->fl[g & 1], &P = c->fl[(g + 1) & 1];
   PerfSet &ps = c->ps[g % kPerfSets];
   const bool queues = d.qmode && d.V && d.L > 0;
   const hipStream_t st = on_dma ? c->dma : c->meta;
   // behind gather g-1's fills: in order on the dma stream (a blocking gather's,
-  // on the host-link stream, ended with its call); on the meta stream the
-  // staging has waited for them, if there is one
+  // on the host-link stream, ended with its call, and those on the meta stream
+  // precede the resolve); on the meta stream the staging has waited for them,
+  // if there is one
   if (on_dma)
     (void)hipStreamWaitEvent(st, G.meta_done, 0);
   else if (!d.V && P.used)
@@ -553,27 +597,27 @@ void queue_hit(lsmgnn_cache *c, uint64_t g, bool on_dma) {
   if (G.data_prof) (void)hipEventRecord(ps.e[kEvHbm0], st);
   if (G.data_n) lsm::launch_copy(CopyMode::kHbmToOut, d, G.data_n, G.sc, G.data_out, st);
   if (G.data_prof) (void)hipEventRecord(ps.e[kEvHbm1], st);
-  if (!on_dma) (void)hipEventRecord(G.hit_done, st);
+  if (event) (void)hipEventRecord(G.hit_done, st);
   G.hit_dma = on_dma;
 }
 
 // Fills of gather g, once its host fetch, staging and hit copy are done.
 // Pipelined gathers queue them on the dma stream, behind the ring writes
 // queued there so far, so that the next host fetch need not wait for them.
-// A blocking gather (`on_host`) queues them on the host-link stream right
-// behind its own host fetch: its caller waits for them, and on the dma stream
-// they would wait for the previous gather's ring write, which runs beside the
-// host fetch and often ends after it.
-void queue_fills(lsmgnn_cache *c, uint64_t g, bool on_host) {
+// A blocking gather queues them on the host-link stream right behind its own
+// host fetch: its caller waits for them, and on the dma stream they would wait
+// for the previous gather's ring write, which runs beside the host fetch and
+// often ends after it.  A gather on the meta stream alone has everything there.
+void queue_fills(lsmgnn_cache *c, uint64_t g, Flight::Fill where) {
   Flight &G = c->fl[g & 1];
   PerfSet &ps = c->ps[g % kPerfSets];
-  const hipStream_t st = on_host ? c->host : c->dma;
-  if (!on_host) (void)hipStreamWaitEvent(st, G.host_done, 0);
+  const hipStream_t st = where == Flight::kDma ? c->dma : where == Flight::kHost ? c->host : c->meta;
+  if (where == Flight::kDma) (void)hipStreamWaitEvent(st, G.host_done, 0);
   // on the meta stream the hit copy follows the staging and all the metadata;
   // on the dma stream it is ahead of these fills, and the metadata's last
   // outputs (the inverse index) are waited for here: whoever waits for the
   // fills has every output
-  (void)hipStreamWaitEvent(st, G.hit_dma ? G.finish_done : G.hit_done, 0);
+  if (where != Flight::kMeta) (void)hipStreamWaitEvent(st, G.hit_dma ? G.finish_done : G.hit_done, 0);
   if (G.data_prof) (void)hipEventRecord(ps.e[kEvFill0], st);
   if (G.data_n) lsm::launch_copy(CopyMode::kOutToCache, c->d, G.data_n, G.sc, G.data_out, st);
   if (G.data_prof) {
@@ -581,8 +625,8 @@ void queue_fills(lsmgnn_cache *c, uint64_t g, bool on_host) {
     (void)hipEventRecord(ps.e[kEvAll1], st);
   }
   (void)hipEventRecord(G.data_done, st);
-  G.fill_host = on_host;
-  G.fill_seq = on_host ? 0 : ++c->dma_subs;
+  G.fill = where;
+  G.fill_seq = where == Flight::kDma ? ++c->dma_subs : 0;
 }
 
 // Queue the latest gather's hit copy and fills if they were deferred.
@@ -592,8 +636,8 @@ void flush_deferred(lsmgnn_cache *c) {
   Flight &G = c->fl[g & 1];
   if (!G.data_deferred) return;
   G.data_deferred = false;
-  queue_hit(c, g, false);
-  queue_fills(c, g, false);
+  queue_hit(c, g, false, true);
+  queue_fills(c, g, Flight::kDma);
 }
 
 // Wait for every queued kernel and copy, then account everything in issue
@@ -619,6 +663,24 @@ struct Announce {
   const int64_t *ids = nullptr;
   uint64_t n = 0;
 };
+
+// Whether a gather runs on the meta stream alone: when it is expected to fetch
+// at most kSerialBytes over the link, judged by the last gather accounted (the
+// first one by its request list).  The fetch, up to 18 us for 1 MiB, then no
+// longer runs beside the rest of the metadata (30-50 us), but the gather has
+// no hand-over to the host-link stream and back (10-15 us each): a blocking
+// gather of 250 requests took 63 us against 123, of 9 K requests 117 against
+// 160.  A pipelined gather moves at most kSerialRowBytes of rows this way (6 us
+// of hit copy): more of them are better copied beside the next gather's
+// metadata (four gathers of 480 MB each 1191 us, on one stream 1303).  Not
+// with a pageable store or queues, whose rows the host or the prefetch stream
+// brings.
+constexpr uint64_t kSerialBytes = 1ull << 20, kSerialRowBytes = 16ull << 20;
+bool queue_serial(const lsmgnn_cache *c, uint64_t n, bool queues, bool pipelined) {
+  const uint64_t host_rows = n < c->host_rows ? n : c->host_rows, rows = n < c->rows ? n : c->rows;
+  return n && !c->pageable && !queues && host_rows <= kSerialBytes / c->d.R &&
+         (!pipelined || rows <= kSerialRowBytes / c->d.R);
+}
 
 // Queue one gather (and the announcement after it).  Returns once its unique
 // count is known; its metadata and row movement may still be running on the
@@ -662,8 +724,11 @@ lsmgnn_status issue_gather(lsmgnn_cache *c, const int64_t *ids, uint64_t n, cons
   };
   uint8_t *outp = static_cast<uint8_t *>(out);
   const bool blocking = !defer;  // the caller waits for this gather's rows
-  const bool overlap = defer && d.V == 0;  // the hit copy beside the next gather's metadata
-  if (queues || overlap) defer = false;    // queues: the prefetch of the next queue follows this gather's staging
+  const bool serial = queue_serial(c, n, queues, defer);
+  const bool overlap = defer && !serial && d.V == 0;  // the hit copy beside the next gather's metadata
+  // queues: the prefetch of the next queue follows this gather's staging
+  if (queues || overlap || serial) defer = false;
+  const Flight::Fill fill = serial ? Flight::kMeta : blocking ? Flight::kHost : Flight::kDma;
 
   // inputs are ready once the caller's queued work is; this parity's arrays
   // are free once gather t-2's rows have moved
@@ -694,11 +759,19 @@ lsmgnn_status issue_gather(lsmgnn_cache *c, const int64_t *ids, uint64_t n, cons
     (void)hipStreamWaitEvent(c->host, f.meta_done, 0);
     if (!c->pageable && f.dma_used) (void)hipStreamWaitEvent(c->host, f.dma_done, 0);
     rec(kEvHostLate, c->host);
-    if (n) lsm::launch_copy(CopyMode::kHostToOut, d, n, f.sc, outp, c->host);
+    if (n) lsm::launch_copy(CopyMode::kHostLate, d, n, f.sc, outp, c->host);
     rec(kEvHost1, c->host);
     // a blocking gather's fills follow on this stream, and its ring write
     // waits for them instead: one packet fewer between the fetch and the fills
     if (!blocking) (void)hipEventRecord(f.host_done, c->host);
+  };
+  auto host_fetch_serial = [&]() {
+    if (f.dma_used) meta_wait_dma(c, f.dma_done, f.dma_seq);
+    rec(kEvHost0, c->meta);
+    lsm::launch_copy(CopyMode::kHostAll, d, n, f.sc, outp, c->meta);
+    rec(kEvHostMid, c->meta);
+    rec(kEvHostLate, c->meta);
+    rec(kEvHost1, c->meta);
   };
 
   rec(kEvAll0, c->meta);
@@ -706,8 +779,7 @@ lsmgnn_status issue_gather(lsmgnn_cache *c, const int64_t *ids, uint64_t n, cons
   const bool dedup = n || clear_n || ann_n;
   if (dedup)
     lsm::launch_dedup(d, ids, n, ann_n ? an.ids : nullptr, ann_n, clear_ids, clear_n, (uint32_t)(t & 31u), f.sc,
-                      unique_ids, c->cn, c->dd_dev, c->meta);
-  (void)hipEventRecord(c->ev_dedup, c->meta);
+                      unique_ids, c->cn, c->dd_dev, ++c->dd_tag & lsm::kDedupTagMask, c->meta);
   // the update of the dynamic information (every U-th gather) reads the window
   // bits the dedup updated; the early-miss list neither reads what it writes
   // nor needs it, so it runs after that list
@@ -719,8 +791,8 @@ lsmgnn_status issue_gather(lsmgnn_cache *c, const int64_t *ids, uint64_t n, cons
     // them meanwhile)
     lsm::launch_probe(d, n, t, f.sc, c->cn, grids, c->meta);
     if (c->pageable) lsm::launch_publish_count(f.sc.gate, &f.sc.gate->n_early, f.hcount_dev, c->meta);
-    (void)hipEventRecord(f.early_done, c->meta);
-    if (!c->pageable) host_fetch_early();
+    if (!serial) (void)hipEventRecord(f.early_done, c->meta);
+    if (!c->pageable && !serial) host_fetch_early();
     if (refresh) lsm::launch_refresh(d, (uint32_t)t, c->cn, c->meta);
     lsm::launch_group_by_set(d, n, (uint32_t)t, f.sc, c->cn, grids, c->meta);
     lsm::launch_set_walk(d, n, (uint32_t)t, f.sc, c->cn, grids, c->meta);
@@ -734,8 +806,10 @@ lsmgnn_status issue_gather(lsmgnn_cache *c, const int64_t *ids, uint64_t n, cons
   }
   // the host fetch needs only the resolve's list; the rest of the metadata
   // runs beside it
-  (void)hipEventRecord(f.meta_done, c->meta);
-  if (!c->pageable) {
+  if (!serial) (void)hipEventRecord(f.meta_done, c->meta);
+  if (serial) {
+    host_fetch_serial();
+  } else if (!c->pageable) {
     if (!n) host_fetch_early();  // no rows: only its events
     host_fetch_late();
   }
@@ -760,7 +834,7 @@ lsmgnn_status issue_gather(lsmgnn_cache *c, const int64_t *ids, uint64_t n, cons
     ann.gate = f.sc.gate;
   }
   lsm::launch_finish(c->cn, f.hc_dev, f.sc.stat_part, grids, d.tail, qf, ann, c->meta);
-  (void)hipEventRecord(f.finish_done, c->meta);
+  if (overlap) (void)hipEventRecord(f.finish_done, c->meta);
 
   // gather t-1's deferred hit copy and fills, now behind this gather's
   // metadata
@@ -771,8 +845,9 @@ lsmgnn_status issue_gather(lsmgnn_cache *c, const int64_t *ids, uint64_t n, cons
   f.data_prof = prof;
   // staging (and unless deferred the hit copy) once gather t-1's fills have
   // landed; the ring write (PCIe egress) is queued later on the dma stream
-  queue_stage(c, t);
-  if (!defer) queue_hit(c, t, overlap);
+  queue_stage(c, t, queues || fill == Flight::kDma);
+  if (!defer) queue_hit(c, t, overlap, !overlap && !serial);
+  if (serial) queue_fills(c, t, fill);
   ps.pending = false;
   if (hipGetLastError() != hipSuccess) return fail_device(c);
 
@@ -781,12 +856,15 @@ lsmgnn_status issue_gather(lsmgnn_cache *c, const int64_t *ids, uint64_t n, cons
   // order, so gather t-1's counters are published by then and its ring write
   // can be queued
   const bool pageable_lists = c->pageable && n;
-  if (hipEventSynchronize(pageable_lists ? f.early_done : c->ev_dedup) != hipSuccess) return fail_device(c);
+  uint32_t err = 0, U = 0;
+  if (pageable_lists && hipEventSynchronize(f.early_done) != hipSuccess) return fail_device(c);
+  if (dedup && !wait_dedup(c, &err, &U)) return fail_device(c);
+  if (!dedup && pf.stats_pending && hipStreamSynchronize(c->meta) != hipSuccess) return fail_device(c);
   harvest_stats(c, pf);
-  issue_dma(c, pf, n ? f.meta_done : nullptr);
+  issue_dma(c, pf, n && !serial ? f.meta_done : nullptr);
   if (queues) (void)hipEventRecord(c->ev_q, c->dma);  // every queue write up to gather t-1's
   if (c->pageable) {
-    const bool rows = n && !(dedup && c->dd->err);
+    const bool rows = n && !err;
     const uint64_t n_early = rows ? f.hcount_host[0] : 0;
     if (rows) copy_host_rows(c, f, 0, n_early, prof);  // store rows only
     host_fetch_early();
@@ -801,10 +879,8 @@ lsmgnn_status issue_gather(lsmgnn_cache *c, const int64_t *ids, uint64_t n, cons
   }
 
   // fills after the host fetch, the staging and the hit copy
-  if (!defer) queue_fills(c, t, blocking);
+  if (!defer && !serial) queue_fills(c, t, fill);
   if (hipGetLastError() != hipSuccess) return fail_device(c);
-  const uint32_t err = dedup ? c->dd->err : 0u;
-  const uint32_t U = dedup ? c->dd->n_unique : 0u;
   if (err) return LSMGNN_E_RANGE;  // every queued kernel of the batch is a no-op
   f.data_deferred = defer;
 
@@ -818,6 +894,7 @@ lsmgnn_status issue_gather(lsmgnn_cache *c, const int64_t *ids, uint64_t n, cons
     ps.requests = n;
     ps.ring = false;
     ps.pf = false;
+    ps.host_launches = serial ? 1 : 2;
   }
   if (queues) {
     // prefetch of the next gather's queue, on the host-link stream after this
@@ -1035,7 +1112,7 @@ lsmgnn_status lsmgnn_cache_create(const lsmgnn_config *cfg, lsmgnn_cache **out) 
     c->host = ss.host;
     c->dma = ss.dma;
   }
-  for (hipEvent_t *e : {&c->ev_in, &c->ev_dedup, &c->ev_adv, &c->ev_q})
+  for (hipEvent_t *e : {&c->ev_in, &c->ev_adv, &c->ev_q})
     ok = ok && hipEventCreateWithFlags(e, hipEventDisableTiming) == hipSuccess;
   for (Flight &f : c->fl)
     for (hipEvent_t *e : {&f.meta_done, &f.finish_done, &f.stage_done, &f.hit_done, &f.host_done, &f.data_done,
@@ -1125,11 +1202,9 @@ lsmgnn_status lsmgnn_gather(lsmgnn_cache *c, const int64_t *ids, uint64_t n, voi
   if (st != LSMGNN_OK) return st;
   Flight &f = c->fl[t & 1];
   // every output is written once the fills are done (they follow the host
-  // fetch, the hit copy and, on the meta stream, all the metadata); later work
-  // on the caller's stream is ordered after them
-  if (hipEventSynchronize(f.data_done) != hipSuccess || hipEventSynchronize(f.finish_done) != hipSuccess ||
-      hipStreamWaitEvent(s, f.data_done, 0) != hipSuccess)
-    return fail_device(c);
+  // fetch, the hit copy and, on the meta stream, all the metadata); work the
+  // caller queues after this call starts after them
+  if (hipEventSynchronize(f.data_done) != hipSuccess) return fail_device(c);
   harvest_stats(c, f);  // its ring write is queued by the next call (after that gather's metadata) or a sync
   return LSMGNN_OK;
 }
