@@ -143,11 +143,8 @@ __device__ __forceinline__ void announce(const AnnounceArgs &a) {
   }
 }
 
-__global__ __launch_bounds__(kBlock) void k_finish(Counters *cn, Counters *host, const uint32_t *part,
-                                                   StatGrids grids, uint64_t *tail, QueueFinish qf,
-                                                   AnnounceArgs ann) {
-  if (ann.ids) announce(ann);
-  if (blockIdx.x != 0) return;
+__device__ __forceinline__ void finish(Counters *cn, Counters *host, const uint32_t *part, const StatGrids &grids,
+                                       uint64_t *tail, const QueueFinish &qf) {
   __shared__ uint32_t red[kNumStat][kBlock / 64];
   __shared__ uint32_t sums[kNumStat];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
@@ -234,6 +231,13 @@ __global__ __launch_bounds__(kBlock) void k_finish(Counters *cn, Counters *host,
                        __HIP_MEMORY_SCOPE_SYSTEM);
     reinterpret_cast<uint32_t *>(cn)[threadIdx.x] = 0u;
   }
+}
+
+__global__ __launch_bounds__(kBlock) void k_finish(Counters *cn, Counters *host, const uint32_t *part,
+                                                   StatGrids grids, uint64_t *tail, QueueFinish qf,
+                                                   AnnounceArgs ann) {
+  if (ann.ids) announce(ann);
+  if (blockIdx.x == 0) finish(cn, host, part, grids, tail, qf);
 }
 
 void launch_finish(Counters *cn, Counters *host, const uint32_t *stat_part, const StatGrids &grids,
@@ -454,8 +458,7 @@ __device__ __forceinline__ void block_count(uint32_t v, uint32_t *part, int slot
 //
 // Bound by latency: a 128-byte set record and an atomic on the set's counter
 // per unique ID, both in flight together.
-__global__ __launch_bounds__(kBlock) void k_probe(const DevState d, Scratch sc, uint64_t t, const Counters *cn) {
-  if (cn->err) return;
+__device__ __forceinline__ void probe(const DevState &d, const Scratch &sc, uint64_t t, const Counters *cn) {
   const uint32_t U = cn->n_unique;
   uint32_t c_early = 0;
   for (uint32_t base = blockIdx.x * kBlock; base < U; base += gridDim.x * kBlock) {
@@ -499,6 +502,11 @@ __global__ __launch_bounds__(kBlock) void k_probe(const DevState d, Scratch sc, 
   block_count(c_early, sc.stat_part, kStEarly);
 }
 
+__global__ __launch_bounds__(kBlock) void k_probe(const DevState d, Scratch sc, uint64_t t, const Counters *cn) {
+  if (cn->err) return;
+  probe(d, sc, t, cn);
+}
+
 void launch_probe(const DevState &d, uint64_t n, uint64_t t, Scratch &sc, Counters *cn, StatGrids &grids,
                   hipStream_t s) {
   const unsigned g = grid_for(n, kBlock, kMaxGrid);
@@ -509,8 +517,7 @@ void launch_probe(const DevState &d, uint64_t n, uint64_t t, Scratch &sc, Counte
 // Per touched set (its first arrival's thread): a segment for the IDs of a set
 // to be walked, and its entry in the work list its size calls for; a settled
 // set gets none.  Resets the set's counter.
-__global__ __launch_bounds__(kBlock) void k_seg_alloc(const DevState d, Scratch sc, uint32_t t, Counters *cn) {
-  if (cn->err) return;
+__device__ __forceinline__ void seg_alloc(const DevState &d, const Scratch &sc, uint32_t t, Counters *cn) {
   const uint32_t U = cn->n_unique;
   __shared__ uint32_t boff, bwork;
   for (uint32_t base = blockIdx.x * kBlock; base < U; base += gridDim.x * kBlock) {
@@ -546,12 +553,16 @@ __global__ __launch_bounds__(kBlock) void k_seg_alloc(const DevState d, Scratch 
   }
 }
 
+__global__ __launch_bounds__(kBlock) void k_seg_alloc(const DevState d, Scratch sc, uint32_t t, Counters *cn) {
+  if (cn->err) return;
+  seg_alloc(d, sc, t, cn);
+}
+
 // Per unique ID: the node's unique index (read by the inverse index), the
 // dedup map cleared behind the compaction, the per-ID state reset; then a hit
 // for an ID of a settled set, else its entry in the set's segment, in arrival
 // order.
-__global__ __launch_bounds__(kBlock) void k_place(const DevState d, Scratch sc, const Counters *cn) {
-  if (cn->err) return;
+__device__ __forceinline__ void place(const DevState &d, const Scratch &sc, const Counters *cn) {
   const uint32_t U = cn->n_unique;
   uint32_t c_hit = 0;
   for (uint32_t u = blockIdx.x * kBlock + threadIdx.x; u < U; u += gridDim.x * kBlock) {
@@ -570,6 +581,11 @@ __global__ __launch_bounds__(kBlock) void k_place(const DevState d, Scratch sc, 
     }
   }
   block_count(c_hit, sc.stat_part, kStSettled);
+}
+
+__global__ __launch_bounds__(kBlock) void k_place(const DevState d, Scratch sc, const Counters *cn) {
+  if (cn->err) return;
+  place(d, sc, cn);
 }
 
 void launch_group_by_set(const DevState &d, uint64_t n, uint32_t t, Scratch &sc, Counters *cn, StatGrids &grids,
@@ -921,8 +937,7 @@ __device__ __forceinline__ void walk_set(const DevState &d, const Scratch &sc, u
 // launches to four: a blocking gather of 250 requests 144 -> 135 us, of 9 K
 // requests 189 -> 171 us.
 template <int P>
-__global__ __launch_bounds__(kBlock) void k_set_walk(const DevState d, Scratch sc, uint32_t t, Counters *cn) {
-  if (cn->err) return;
+__device__ __forceinline__ void walk_sets(const DevState &d, const Scratch &sc, uint32_t t, const Counters *cn) {
   __shared__ uint32_t lds[3 * kMidSet * (kBlock / 64)];
   static_assert(sizeof(lds) >= (1 + kBlock / 64) * 256 * 4, "the large-set sort works in the same LDS");
   static_assert(kMidSet == 8 * 64 && kSmallSet == 8 * kWays, "eight entries per ordering lane");
@@ -975,6 +990,12 @@ __global__ __launch_bounds__(kBlock) void k_set_walk(const DevState d, Scratch s
   block_count(c.enq, sc.stat_part, kStEnqueued);
   block_count(c.drop, sc.stat_part, kStDropped);
   block_count(c.fin, sc.stat_part, kStFinal);
+}
+
+template <int P>
+__global__ __launch_bounds__(kBlock) void k_set_walk(const DevState d, Scratch sc, uint32_t t, Counters *cn) {
+  if (cn->err) return;
+  walk_sets<P>(d, sc, t, cn);
 }
 
 #ifndef LSM_WALK_GRID
@@ -1203,9 +1224,8 @@ __global__ __launch_bounds__(kBlock) void k_qplace(const DevState d, Scratch sc,
 // scattered record of every evicted line requested later in the batch (which
 // the walk now knows by itself), a blocking gather of 9 K requests took 171 us
 // against 160.
-__global__ __launch_bounds__(kBlock) void k_resolve(const DevState d, Scratch sc, uint64_t t, uint8_t *outcome,
-                                                    int scan, Counters *cn) {
-  if (cn->err) return;
+__device__ __forceinline__ void resolve(const DevState &d, const Scratch &sc, uint64_t t, uint8_t *outcome, int scan,
+                                        Counters *cn) {
   static_assert(kScanChunk == kBlock, "one chunk of enqueue flags per block pass");
   const uint32_t U = cn->n_unique;
   const uint64_t tail0 = d.tail[0], tail_prev = d.tail[1];
@@ -1351,6 +1371,12 @@ __global__ __launch_bounds__(kBlock) void k_resolve(const DevState d, Scratch sc
   block_count(c_vsame, sc.stat_part, kStVhSame);
 }
 
+__global__ __launch_bounds__(kBlock) void k_resolve(const DevState d, Scratch sc, uint64_t t, uint8_t *outcome,
+                                                    int scan, Counters *cn) {
+  if (cn->err) return;
+  resolve(d, sc, t, outcome, scan, cn);
+}
+
 // One pass over the raw requests: the inverse index (if asked for), and the
 // outcome counts (each request takes its unique ID's outcome).
 __device__ __forceinline__ void request_counts(const DevState &d, const Scratch &sc, const int64_t *ids, uint32_t n,
@@ -1378,9 +1404,7 @@ __global__ __launch_bounds__(kBlock) void k_request_counts(const DevState d, Scr
 // have the sequence numbers [q_lo, tail_end), q_lo = tail_end - min(E, V) for E
 // enqueues, and their rows are staged in that order (entries removed again in
 // this batch leave a hole that nothing reads).
-__global__ __launch_bounds__(kBlock) void k_enq_finalize(const DevState d, Scratch sc, const int64_t *ids, uint32_t n,
-                                                         int64_t *inv, Counters *cn) {
-  if (cn->err) return;
+__device__ __forceinline__ void enqueue_entries(const DevState &d, const Scratch &sc, const Counters *cn) {
   const uint32_t U = cn->n_unique;
   const uint64_t tail0 = d.tail[0];
   const uint64_t E = cn->enq_total;
@@ -1413,6 +1437,12 @@ __global__ __launch_bounds__(kBlock) void k_enq_finalize(const DevState d, Scrat
     }
   }
   block_count(c_copy, sc.stat_part, kStEnqCopy);
+}
+
+__global__ __launch_bounds__(kBlock) void k_enq_finalize(const DevState d, Scratch sc, const int64_t *ids, uint32_t n,
+                                                         int64_t *inv, Counters *cn) {
+  if (cn->err) return;
+  enqueue_entries(d, sc, cn);
   // the pass over the requests, in the same launch
   request_counts(d, sc, ids, n, inv);
 }
@@ -1453,6 +1483,117 @@ void launch_ring_enqueue(const DevState &d, const int64_t *ids, uint64_t n, uint
   }
   grids.g[kStReqHits] = g;
   grids.g[kStReqVictimHits] = g;
+}
+
+// --------------------------------------------------------- small gathers
+// All the metadata of a gather of at most kTinyRequests requests, in one block:
+// such a gather costs its launches, not its work (each of the eleven kernels
+// runs for 2-8 us on it, and the host takes about 3 us to submit one).  The
+// passes are those of the kernels above, one after the other; only the dedup
+// is another: the requests are sorted in LDS, so that nothing depends on the
+// number of nodes, as the scans of the byte map do.
+__device__ __forceinline__ void tiny_sort(uint64_t *key, uint32_t n) {
+  uint32_t P = 64;  // the next power of two
+  while (P < n) P *= 2;
+  for (uint32_t i = n + threadIdx.x; i < P; i += kBlock) key[i] = ~0ull;
+  __syncthreads();
+  for (uint32_t k = 2; k <= P; k *= 2)
+    for (uint32_t j = k / 2; j > 0; j /= 2) {
+      for (uint32_t p = threadIdx.x; p < P / 2; p += kBlock) {
+        const uint32_t lo = 2 * p - (p & (j - 1)), hi = lo + j;  // j apart, j-bit clear in lo
+        const uint64_t a = key[lo], b = key[hi];
+        if ((a > b) == ((lo & k) == 0)) {
+          key[lo] = b;
+          key[hi] = a;
+        }
+      }
+      __syncthreads();
+    }
+}
+
+template <int P>
+__global__ __launch_bounds__(kBlock) void k_tiny(const DevState d, Scratch sc, TinyArgs a, Counters *cn) {
+  __shared__ uint64_t key[kTinyRequests];
+  const uint32_t n = a.n;
+  // validate; clear the served minibatch's window bit
+  bool bad = false;
+  for (uint32_t i = threadIdx.x; i < n; i += kBlock) {
+    const int64_t x = a.ids[i];
+    bad |= x < 0 || (uint64_t)x >= d.N;
+    key[i] = (uint64_t)x;
+  }
+  for (uint32_t i = threadIdx.x; i < a.ann_n; i += kBlock) {
+    const int64_t x = a.ann_ids[i];
+    bad |= x < 0 || (uint64_t)x >= d.N;
+  }
+  const uint32_t cb = 1u << a.clear_bit;
+  for (uint32_t i = threadIdx.x; i < a.clear_n; i += kBlock) {
+    const int64_t x = a.clear_ids[i];
+    const uint32_t m = d.mask[x];
+    if (m & cb) d.mask[x] = m & ~cb;
+  }
+  if (__syncthreads_or(bad)) {
+    if (threadIdx.x == 0) {
+      *sc.gate = gate_with(1, 0);
+      publish_dedup(a.dd, a.tag, 1, 0);
+    }
+    return;
+  }
+  // the first of each run of equal IDs gets the next unique index
+  tiny_sort(key, n);
+  uint32_t U = 0;
+  for (uint32_t base = 0; base < n; base += kBlock) {
+    const uint32_t i = base + threadIdx.x;
+    const bool first = i < n && (i == 0 || key[i] != key[i - 1]);
+    uint32_t tot;
+    const uint32_t u = U + block_exclusive_scan(first ? 1u : 0u, tot);
+    U += tot;
+    if (first) {
+      sc.uniq[u] = (uint32_t)key[i];
+      a.unique_out[u] = (int64_t)key[i];
+    }
+  }
+  if (threadIdx.x == 0) {
+    cn->n_unique = U;
+    *sc.gate = gate_with(0, U);
+    publish_dedup(a.dd, a.tag, 0, U);
+  }
+  __syncthreads();
+  probe(d, sc, a.t, cn);
+  __syncthreads();
+  seg_alloc(d, sc, (uint32_t)a.t, cn);
+  __syncthreads();
+  place(d, sc, cn);
+  __syncthreads();
+  walk_sets<P>(d, sc, (uint32_t)a.t, cn);
+  __syncthreads();
+  resolve(d, sc, a.t, a.outcome, d.V ? kScanCounts : kScanNone, cn);
+  __syncthreads();
+  if (d.V) enqueue_entries(d, sc, cn);
+  request_counts(d, sc, a.ids, n, a.inverse);
+  if (a.ann.ids) announce(a.ann);
+  __syncthreads();
+  StatGrids grids;
+#pragma unroll
+  for (int st = 0; st < kNumStat; ++st) grids.g[st] = 1;
+  grids.g[kStEnqCopy] = d.V ? 1 : 0;
+  finish(cn, a.hc, sc.stat_part, grids, d.tail, QueueFinish{});
+}
+
+void launch_tiny(const DevState &d, Scratch &sc, const TinyArgs &a, Counters *cn, hipStream_t s) {
+  switch (d.policy) {
+    case kPolicyStatic:
+      hipLaunchKernelGGL(k_tiny<kPolicyStatic>, dim3(1), dim3(kBlock), 0, s, d, sc, a, cn);
+      break;
+    case kPolicyDynamic:
+      hipLaunchKernelGGL(k_tiny<kPolicyDynamic>, dim3(1), dim3(kBlock), 0, s, d, sc, a, cn);
+      break;
+    case kPolicyRoundRobin:
+      hipLaunchKernelGGL(k_tiny<kPolicyRoundRobin>, dim3(1), dim3(kBlock), 0, s, d, sc, a, cn);
+      break;
+    default:
+      hipLaunchKernelGGL(k_tiny<kPolicyHybrid>, dim3(1), dim3(kBlock), 0, s, d, sc, a, cn);
+  }
 }
 
 // -------------------------------------------------------------- row copies
@@ -1519,18 +1660,17 @@ __global__ __launch_bounds__(kBlock) void k_list_copy(const uint8_t *src, const 
 #endif
 //
 // The list has two parts: its first n_early entries (misses known at batch
-// start) and the n_host entries after them (the resolve's); a launch moves one
-// part (M = kHostEarly, kHostLate) or both (kHostAll).
+// start, `late` false) and the n_host entries after them (the resolve's,
+// `late` true); each launch moves one part.
 template <bool kPow2>
 __global__ __launch_bounds__(kBlock) void k_host_fetch(const DevState d, Scratch sc, uint8_t *out, uint32_t nvec,
-                                                       uint32_t vshift, CopyMode part) {
+                                                       uint32_t vshift, int late) {
   constexpr int kU = LSM_HOST_UNROLL;
   const Gate g = *sc.gate;
   if (g.err) return;
   const uint64_t R = d.R;
-  const uint32_t first = part == CopyMode::kHostLate ? g.n_early : 0u;
-  const uint32_t end = part == CopyMode::kHostEarly ? g.n_early : g.n_early + g.n_host;
-  const uint64_t total = (uint64_t)(end - first) * nvec;
+  const uint32_t first = late ? g.n_early : 0u;
+  const uint64_t total = (uint64_t)(late ? g.n_host : g.n_early) * nvec;
   const uint64_t stride = (uint64_t)gridDim.x * kBlock;
   const uint32_t *list = sc.host_list + first;
   const uint64_t *src = sc.host_src + first;
@@ -1618,12 +1758,13 @@ void launch_copy(CopyMode mode, const DevState &d, uint64_t n, const Scratch &sc
   const uint32_t nvec = (uint32_t)(d.R / 16);
   const bool pow2 = (nvec & (nvec - 1)) == 0;
   const uint32_t vshift = pow2 ? (uint32_t)__builtin_ctz(nvec) : 0u;
-  if (mode == CopyMode::kHostLate || mode == CopyMode::kHostEarly || mode == CopyMode::kHostAll) {
+  if (mode == CopyMode::kHostLate || mode == CopyMode::kHostEarly) {
     const unsigned g = grid_for(n * nvec, (uint64_t)kBlock * kUnroll, d.host_grid ? d.host_grid : LSM_HOST_GRID);
+    const int late = mode == CopyMode::kHostLate;
     if (pow2)
-      hipLaunchKernelGGL((k_host_fetch<true>), dim3(g), dim3(kBlock), 0, s, d, sc, out, nvec, vshift, mode);
+      hipLaunchKernelGGL((k_host_fetch<true>), dim3(g), dim3(kBlock), 0, s, d, sc, out, nvec, vshift, late);
     else
-      hipLaunchKernelGGL((k_host_fetch<false>), dim3(g), dim3(kBlock), 0, s, d, sc, out, nvec, vshift, mode);
+      hipLaunchKernelGGL((k_host_fetch<false>), dim3(g), dim3(kBlock), 0, s, d, sc, out, nvec, vshift, late);
     return;
   }
   switch (mode) {
@@ -1637,6 +1778,64 @@ void launch_copy(CopyMode mode, const DevState &d, uint64_t n, const Scratch &sc
       launch_list<CopyMode::kOutToCache>(out, sc.fill, d.rows, sc.gate, &sc.gate->n_fill, n, d.R, s);
       break;
   }
+}
+
+// A gather on one stream: the host fetch, the hit copy and the staging in one
+// launch.  Item w of the concatenated lists, the host rows first (their reads
+// take longest to come back); tiles as in the list copy.
+template <bool kPow2>
+__global__ __launch_bounds__(kBlock) void k_move_rows(const DevState d, Scratch sc, uint8_t *out, uint32_t nvec,
+                                                      uint32_t vshift) {
+  const Gate g = *sc.gate;
+  if (g.err) return;
+  const uint64_t R = d.R;
+  const uint64_t n_host = (uint64_t)g.n_early + g.n_host, n_out = n_host + g.n_unique;
+  const uint64_t total = (n_out + (d.V ? g.n_stage : 0u)) * nvec;
+  constexpr uint64_t tile = (uint64_t)kListUnroll * kBlock;
+  for (uint64_t base = (uint64_t)blockIdx.x * tile; base < total; base += (uint64_t)gridDim.x * tile) {
+    u32x4 v[kListUnroll];
+    uint8_t *dp[kListUnroll];
+#pragma unroll
+    for (int k = 0; k < kListUnroll; ++k) {
+      const uint64_t w = base + (uint64_t)k * kBlock + threadIdx.x;
+      dp[k] = nullptr;
+      if (w < total) {
+        const uint64_t i = kPow2 ? w >> vshift : w / nvec;
+        const uint64_t byte = (w - i * nvec) * 16u;
+        const uint8_t *sp = nullptr;
+        if (i < n_host) {
+          const uint64_t code = sc.host_src[i];
+          sp = ((code & ~kSrcIndex) == kSrcRing ? d.ring_rows : d.store) + (code & kSrcIndex) * R;
+          dp[k] = out + (uint64_t)sc.host_list[i] * R + byte;
+        } else if (i < n_out) {
+          const uint64_t u = i - n_host;
+          const uint32_t row = sc.hbm.src[u];
+          if (row != kNoRow) {
+            sp = d.rows + (uint64_t)row * R;
+            dp[k] = out + u * R + byte;
+          }
+        } else {
+          const uint64_t j = i - n_out;
+          sp = d.rows + (uint64_t)sc.stage.src[j] * R;
+          dp[k] = sc.staging + (uint64_t)sc.stage.dst[j] * R + byte;
+        }
+        if (dp[k]) v[k] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(sp + byte));
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kListUnroll; ++k)
+      if (dp[k]) __builtin_nontemporal_store(v[k], reinterpret_cast<u32x4 *>(dp[k]));
+  }
+}
+
+void launch_move_rows(const DevState &d, uint64_t n, const Scratch &sc, uint8_t *out, hipStream_t s) {
+  const uint32_t nvec = (uint32_t)(d.R / 16);
+  const unsigned g = grid_for(n * nvec, (uint64_t)kBlock * kListUnroll, LSM_HBM_GRID);
+  if ((nvec & (nvec - 1)) == 0)
+    hipLaunchKernelGGL(k_move_rows<true>, dim3(g), dim3(kBlock), 0, s, d, sc, out, nvec,
+                       (uint32_t)__builtin_ctz(nvec));
+  else
+    hipLaunchKernelGGL(k_move_rows<false>, dim3(g), dim3(kBlock), 0, s, d, sc, out, nvec, 0u);
 }
 
 // Queue mode: the queue of the next gather into its prefetch buffer.  Rows of

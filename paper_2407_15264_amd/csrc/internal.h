@@ -220,9 +220,9 @@ struct DevState {
   uint64_t stage_rows;   // rows per staging buffer: min(max_batch, V)
 };
 
-// kHostEarly / kHostLate / kHostAll: the host fetch of the host-fetch list's
-// first n_early entries, of the rest, of all
-enum class CopyMode { kHbmToOut, kHostLate, kCacheToStage, kOutToCache, kHostEarly, kHostAll };
+// kHostEarly / kHostLate: the host fetch of the host-fetch list's first
+// n_early entries, and of the rest
+enum class CopyMode { kHbmToOut, kHostLate, kCacheToStage, kOutToCache, kHostEarly };
 
 // What the last kernel of a gather does for the victim queues: empty the
 // served slot `cur` and record in the gate what the prefetch of slot `next`
@@ -244,7 +244,27 @@ struct AnnounceArgs {
   const Gate *gate = nullptr;
 };
 
+// A gather whose metadata one block does: at most this many requests, and at
+// most kTinyLists announced IDs and IDs whose window bit it clears.
+constexpr uint32_t kTinyRequests = 1024, kTinyLists = 4096, kTinyMisses = 128;
+struct TinyArgs {
+  const int64_t *ids = nullptr, *ann_ids = nullptr, *clear_ids = nullptr;  // ann_ids: validated
+  uint32_t n = 0, ann_n = 0, clear_n = 0, clear_bit = 0;
+  int64_t *unique_out = nullptr, *inverse = nullptr;
+  uint8_t *outcome = nullptr;
+  uint64_t t = 0;
+  DedupResult *dd = nullptr;
+  uint32_t tag = 0;
+  Counters *hc = nullptr;
+  AnnounceArgs ann;  // recorded
+};
+
 // ----- launchers (gather_kernels.hip) -----
+// dedup to finish in one kernel (no queues, no update of the dynamic
+// information before this gather)
+void launch_tiny(const DevState &d, Scratch &sc, const TinyArgs &a, Counters *cn, hipStream_t s);
+// host fetch, hit copy and staging in one launch
+void launch_move_rows(const DevState &d, uint64_t n, const Scratch &sc, uint8_t *out, hipStream_t s);
 void launch_finish(Counters *cn, Counters *host, const uint32_t *stat_part, const StatGrids &grids,
                    uint64_t *tail, const QueueFinish &qf, const AnnounceArgs &ann, hipStream_t s);
 // ann_ids/ann_n: the list announced with this gather (validated here), or NULL/0

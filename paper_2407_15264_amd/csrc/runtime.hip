@@ -144,7 +144,6 @@ struct PerfSet {
   bool pf = false;       // the prefetch this gather issued for the next one was timed
   uint64_t t = 0, requests = 0;
   uint32_t n_hbm = 0, n_host = 0, n_enq = 0, n_fill = 0, n_pf = 0;
-  uint32_t host_launches = 2;
 };
 
 // The per-device stream triple, created with the first cache on a device and
@@ -530,7 +529,7 @@ void harvest_profile(lsmgnn_cache *c, PerfSet &p) {
       c->acc.enqueue_rows += p.n_enq;
     }
     c->acc.host_fetch_ms += el(kEvHost0, kEvHostMid) + el(kEvHostLate, kEvHost1);  // not the wait between them
-    c->acc.host_fetch_launches += p.host_launches;
+    c->acc.host_fetch_launches += 2;
     c->acc.host_fetch_rows += p.n_host;
     c->acc.fill_ms += el(kEvFill0, kEvFill1);
     c->acc.fill_launches += 1;
@@ -599,6 +598,32 @@ void queue_hit(lsmgnn_cache *c, uint64_t g, bool on_dma, bool event) {
   if (G.data_prof) (void)hipEventRecord(ps.e[kEvHbm1], st);
   if (event) (void)hipEventRecord(G.hit_done, st);
   G.hit_dma = on_dma;
+}
+
+// Gather g on the meta stream alone: its host fetch, hit copy and staging in
+// one launch, once gather g-1's fills (the cache rows) and gather g-2's ring
+// write (the staging rows of parity g, and the ring rows the host fetch may
+// read) have landed.
+void queue_moves(lsmgnn_cache *c, uint64_t g) {
+  Flight &G = c->fl[g & 1], &P = c->fl[(g + 1) & 1];
+  PerfSet &ps = c->ps[g % kPerfSets];
+  if (P.used) meta_wait_fills(c, P);
+  if (G.dma_used) meta_wait_dma(c, G.dma_done, G.dma_seq);
+  if (!G.data_prof) {
+    lsm::launch_move_rows(c->d, G.data_n, G.sc, G.data_out, c->meta);
+  } else {  // timed: each kind of row in launches of its own
+    auto copy = [&](CopyMode m, int e0, int e1) {
+      (void)hipEventRecord(ps.e[e0], c->meta);
+      lsm::launch_copy(m, c->d, G.data_n, G.sc, G.data_out, c->meta);
+      (void)hipEventRecord(ps.e[e1], c->meta);
+    };
+    copy(CopyMode::kHostEarly, kEvHost0, kEvHostMid);
+    copy(CopyMode::kHostLate, kEvHostLate, kEvHost1);
+    if (c->d.V) lsm::launch_copy(CopyMode::kCacheToStage, c->d, G.data_n, G.sc, G.data_out, c->meta);
+    copy(CopyMode::kHbmToOut, kEvHbm0, kEvHbm1);
+  }
+  G.hit_dma = false;
+  G.used = true;
 }
 
 // Fills of gather g, once its host fetch, staging and hit copy are done.
@@ -765,27 +790,54 @@ lsmgnn_status issue_gather(lsmgnn_cache *c, const int64_t *ids, uint64_t n, cons
     // waits for them instead: one packet fewer between the fetch and the fills
     if (!blocking) (void)hipEventRecord(f.host_done, c->host);
   };
-  auto host_fetch_serial = [&]() {
-    if (f.dma_used) meta_wait_dma(c, f.dma_done, f.dma_seq);
-    rec(kEvHost0, c->meta);
-    lsm::launch_copy(CopyMode::kHostAll, d, n, f.sc, outp, c->meta);
-    rec(kEvHostMid, c->meta);
-    rec(kEvHostLate, c->meta);
-    rec(kEvHost1, c->meta);
-  };
 
   rec(kEvAll0, c->meta);
   const uint64_t ann_n = an.on ? an.n : 0;
   const bool dedup = n || clear_n || ann_n;
-  if (dedup)
-    lsm::launch_dedup(d, ids, n, ann_n ? an.ids : nullptr, ann_n, clear_ids, clear_n, (uint32_t)(t & 31u), f.sc,
-                      unique_ids, c->cn, c->dd_dev, ++c->dd_tag & lsm::kDedupTagMask, c->meta);
+  // the announced bits are first read by the next gather's set walk
+  lsm::AnnounceArgs ann;
+  if (record) {
+    ann.ids = an.ids;
+    ann.n = (uint32_t)an.n;
+    ann.bit = (uint32_t)(k & 31u);
+    ann.mask = d.mask;
+    ann.slot_ids = c->win_ids + (uint64_t)kslot * c->max_batch;
+    ann.gate = f.sc.gate;
+  }
+  const uint32_t tag = dedup ? ++c->dd_tag & lsm::kDedupTagMask : 0u;
   // the update of the dynamic information (every U-th gather) reads the window
   // bits the dedup updated; the early-miss list neither reads what it writes
   // nor needs it, so it runs after that list
   const bool refresh = d.U > 1 && t % d.U == 0;
+  // one block for all the metadata while that is faster than the launches it
+  // saves (a blocking gather of 250 resident rows 54 us against 63); its 32
+  // lane groups walk a set in a few us, so a batch expected to miss more than
+  // kTinyMisses rows (by the last gather accounted) takes the kernels
+  const bool tiny = serial && !refresh && n <= lsm::kTinyRequests && ann_n <= lsm::kTinyLists &&
+                    clear_n <= lsm::kTinyLists && (n < c->host_rows ? n : c->host_rows) <= lsm::kTinyMisses;
+  if (dedup && !tiny)
+    lsm::launch_dedup(d, ids, n, ann_n ? an.ids : nullptr, ann_n, clear_ids, clear_n, (uint32_t)(t & 31u), f.sc,
+                      unique_ids, c->cn, c->dd_dev, tag, c->meta);
   lsm::StatGrids grids{};
-  if (n) {
+  if (tiny) {
+    lsm::TinyArgs a;
+    a.ids = ids;
+    a.n = (uint32_t)n;
+    a.ann_ids = an.ids;
+    a.ann_n = (uint32_t)ann_n;
+    a.clear_ids = clear_ids;
+    a.clear_n = (uint32_t)clear_n;
+    a.clear_bit = (uint32_t)(t & 31u);
+    a.unique_out = unique_ids;
+    a.inverse = inverse;
+    a.outcome = outcome;
+    a.t = t;
+    a.dd = c->dd_dev;
+    a.tag = tag;
+    a.hc = f.hc_dev;
+    a.ann = ann;
+    lsm::launch_tiny(d, f.sc, a, c->cn, c->meta);
+  } else if (n) {
     // the misses known at batch start first: their rows cross the link while
     // the rest of the metadata runs (pageable store: the host threads copy
     // them meanwhile)
@@ -807,15 +859,11 @@ lsmgnn_status issue_gather(lsmgnn_cache *c, const int64_t *ids, uint64_t n, cons
   // the host fetch needs only the resolve's list; the rest of the metadata
   // runs beside it
   if (!serial) (void)hipEventRecord(f.meta_done, c->meta);
-  if (serial) {
-    host_fetch_serial();
-  } else if (!c->pageable) {
+  if (!c->pageable && !serial) {
     if (!n) host_fetch_early();  // no rows: only its events
     host_fetch_late();
   }
-  if (n) {
-    lsm::launch_ring_enqueue(d, ids, n, t, inverse, f.sc, c->cn, grids, c->meta);
-  }
+  if (n && !tiny) lsm::launch_ring_enqueue(d, ids, n, t, inverse, f.sc, c->cn, grids, c->meta);
   lsm::QueueFinish qf;
   if (queues) {
     qf.qcount = d.qcount;
@@ -823,17 +871,7 @@ lsmgnn_status issue_gather(lsmgnn_cache *c, const int64_t *ids, uint64_t n, cons
     qf.cur = (uint32_t)(t % (d.L + 1));
     qf.next = (uint32_t)((t + 1) % (d.L + 1));
   }
-  // the announced bits are first read by the next gather's set walk
-  lsm::AnnounceArgs ann;
-  if (record) {
-    ann.ids = an.ids;
-    ann.n = (uint32_t)an.n;
-    ann.bit = (uint32_t)(k & 31u);
-    ann.mask = d.mask;
-    ann.slot_ids = c->win_ids + (uint64_t)kslot * c->max_batch;
-    ann.gate = f.sc.gate;
-  }
-  lsm::launch_finish(c->cn, f.hc_dev, f.sc.stat_part, grids, d.tail, qf, ann, c->meta);
+  if (!tiny) lsm::launch_finish(c->cn, f.hc_dev, f.sc.stat_part, grids, d.tail, qf, ann, c->meta);
   if (overlap) (void)hipEventRecord(f.finish_done, c->meta);
 
   // gather t-1's deferred hit copy and fills, now behind this gather's
@@ -845,9 +883,13 @@ lsmgnn_status issue_gather(lsmgnn_cache *c, const int64_t *ids, uint64_t n, cons
   f.data_prof = prof;
   // staging (and unless deferred the hit copy) once gather t-1's fills have
   // landed; the ring write (PCIe egress) is queued later on the dma stream
-  queue_stage(c, t, queues || fill == Flight::kDma);
-  if (!defer) queue_hit(c, t, overlap, !overlap && !serial);
-  if (serial) queue_fills(c, t, fill);
+  if (serial) {
+    queue_moves(c, t);
+    queue_fills(c, t, fill);
+  } else {
+    queue_stage(c, t, queues || fill == Flight::kDma);
+    if (!defer) queue_hit(c, t, overlap, !overlap);
+  }
   ps.pending = false;
   if (hipGetLastError() != hipSuccess) return fail_device(c);
 
@@ -894,7 +936,6 @@ lsmgnn_status issue_gather(lsmgnn_cache *c, const int64_t *ids, uint64_t n, cons
     ps.requests = n;
     ps.ring = false;
     ps.pf = false;
-    ps.host_launches = serial ? 1 : 2;
   }
   if (queues) {
     // prefetch of the next gather's queue, on the host-link stream after this

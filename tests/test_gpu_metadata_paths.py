@@ -80,3 +80,63 @@ def test_enqueue_scan_limit(requests):
     store = Store.random_bytes(n, 16, 3)
     stat = rng.integers(0, 50, n).astype(np.uint32)
     run_parity(store, stat, 20_000, 30_000, 3, batches, rows="all", label="scan limit")
+
+
+@pytest.mark.parametrize("policy", ["hybrid", "static", "dynamic", "round_robin"])
+@pytest.mark.parametrize("victim,lookahead", [(0, 0), (0, 3), (37, 3), (2000, 16)])
+@pytest.mark.parametrize("requests", [1, 63, 64, 65, 255, 257, 1023, 1024, 1025])
+def test_small_gathers(requests, victim, lookahead, policy):
+    """Request counts around those that one block takes, with mostly resident rows (the block's path), then a batch
+    that misses everything and mostly resident ones again."""
+    log(f"case: {requests} requests, V={victim} L={lookahead} {policy}")
+    n, sets = 3 * max(requests, 40), max(requests, 40) // 4
+    rng = np.random.default_rng(requests + victim)
+    pool = rng.choice(n, max(1, sets * 4), replace=False)
+    batches = []
+    for b in range(14):
+        if b == 7:
+            batches.append(rng.integers(0, n, requests))
+            pool = rng.choice(n, pool.size, replace=False)
+            continue
+        ids = rng.choice(pool, requests)
+        stray = rng.random(requests) < 0.03
+        batches.append(np.where(stray, rng.integers(0, n, requests), ids))
+    store = Store.random_bytes(n, 48, 4)
+    stat = rng.integers(0, 7, n).astype(np.uint32)
+    run_parity(store, stat, sets, victim, lookahead, batches, rows="all", label="small", policy=policy)
+    run_async_parity(store, stat, sets, victim, lookahead, batches, rows="all", label="small pipelined", policy=policy)
+
+
+def test_small_gather_errors():
+    """An ID out of range in a small gather's own or announced list leaves everything as it was."""
+    log("case: small gather errors")
+    n = 500
+    store = Store.random_bytes(n, 32, 5)
+    cache = lsmgnn.FeatureCache(n, 32, store.buf, np.arange(n, dtype=np.uint32), 80, 20, 2, 200)
+    dev = torch.device("cuda")
+    good = torch.arange(40, device=dev)
+    for _ in range(3):
+        cache.advance(good)
+    for _ in range(3):
+        r = cache.gather(good, outcome=True)
+        cache.advance(good)
+    before, stats = cache.export_state(), cache.stats()[1]
+    out = torch.empty(200 * 32, dtype=torch.uint8, device=dev)
+    uniq = torch.empty(200, dtype=torch.int64, device=dev)
+    for bad in (n, -1, 1 << 40):
+        wrong = good.clone()
+        wrong[17] = bad
+        with pytest.raises(lsmgnn.LsmgnnError) as e:
+            cache.gather(wrong)
+        assert e.value.code == lsmgnn.E_RANGE
+        with pytest.raises(lsmgnn.LsmgnnError) as e:
+            cache.gather_async(good, out, uniq, announce=wrong)
+        assert e.value.code == lsmgnn.E_RANGE
+        after = cache.export_state()
+        for key in before:
+            assert np.array_equal(before[key], after[key]), key
+        assert cache.stats()[1] == stats
+    r = cache.gather(good, outcome=True)
+    assert r.n_unique == 40 and bool((r.outcome == lsmgnn.HIT).all())
+    assert np.array_equal(r.out.cpu().numpy(), store.np[:40])
+    cache.close()
