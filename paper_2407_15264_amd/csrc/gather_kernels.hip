@@ -99,6 +99,33 @@ __device__ __forceinline__ uint32_t block_sum(uint32_t v) {
   return tot;
 }
 
+// Rank of this thread among the block's threads with `pred` set, from ballots,
+// and how many there are.  For kN predicates at once: one pair of barriers.
+template <int kN>
+__device__ __forceinline__ void block_ranks(const bool (&pred)[kN], uint32_t (&rank)[kN], uint32_t (&total)[kN]) {
+  __shared__ uint32_t wcnt[kN][kBlock / 64];
+  const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
+  const uint64_t lt = (1ull << lane) - 1ull;
+#pragma unroll
+  for (int i = 0; i < kN; ++i) {
+    const uint64_t m = __ballot(pred[i]);
+    rank[i] = (uint32_t)__popcll(m & lt);
+    if (lane == 0) wcnt[i][wid] = (uint32_t)__popcll(m);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kN; ++i) {
+    total[i] = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < kBlock / 64; ++w) {
+      const uint32_t c = wcnt[i][w];
+      rank[i] += w < wid ? c : 0u;
+      total[i] += c;
+    }
+  }
+  __syncthreads();
+}
+
 // A gather's gate as the dedup leaves it: the error flag and the unique count,
 // every list empty.
 __device__ __forceinline__ Gate gate_with(uint32_t err, uint32_t n_unique) {
@@ -288,26 +315,29 @@ __global__ void k_mark(const int64_t *ids, uint32_t n, const int64_t *ann_ids, u
   }
 }
 
-// Each thread owns kBytesPerThread consecutive bytes of the map (four 128-bit
-// loads); marked bytes hold exactly 1, so a popcount of a word counts them.
-__device__ __forceinline__ void load_words(const uint8_t *present, uint32_t (&w)[kWordsPerThread]) {
-  const u32x4 *p = reinterpret_cast<const u32x4 *>(present + ((size_t)blockIdx.x * kBlock + threadIdx.x) *
-                                                                 kBytesPerThread);
+// Each thread owns kW consecutive words of the map (kW / 4 128-bit loads);
+// marked bytes hold exactly 1, so a popcount of a word counts them.  With 64
+// bytes per thread whatever the number of nodes, 16 K nodes were one block's
+// work (compaction 7.4 us, with 16 bytes 3.8) and 1M nodes 64 blocks'.
+template <int kW>
+__device__ __forceinline__ void load_words(const uint8_t *present, uint32_t (&w)[kW]) {
+  const u32x4 *p = reinterpret_cast<const u32x4 *>(present + ((size_t)blockIdx.x * kBlock + threadIdx.x) * 4 * kW);
 #pragma unroll
-  for (int k = 0; k < kWordsPerThread / 4; ++k) {
+  for (int k = 0; k < kW / 4; ++k) {
     const u32x4 a = p[k];
     w[4 * k] = a.x; w[4 * k + 1] = a.y; w[4 * k + 2] = a.z; w[4 * k + 3] = a.w;
   }
 }
 
+template <int kW>
 __global__ __launch_bounds__(kBlock) void k_chunk_popc(const uint8_t *present, uint32_t *chunk_sums,
                                                        const Counters *cn) {
   if (cn->err) return;
-  uint32_t w[kWordsPerThread];
+  uint32_t w[kW];
   load_words(present, w);
   uint32_t c = 0;
 #pragma unroll
-  for (int k = 0; k < kWordsPerThread; ++k) c += __popc(w[k]);
+  for (int k = 0; k < kW; ++k) c += __popc(w[k]);
   const uint32_t tot = block_sum(c);
   if (threadIdx.x == 0) chunk_sums[blockIdx.x] = tot;
 }
@@ -344,17 +374,17 @@ __global__ __launch_bounds__(kBlock) void k_chunk_scan(uint32_t *chunk_sums, uin
 // saves the separate one-block scan), and the last chunk's block publishes
 // the unique count; otherwise chunk_off holds the scanned offsets.  Each
 // node's own unique index is written later (k_place).
-template <bool kFused>
+template <int kW, bool kFused>
 __global__ __launch_bounds__(kBlock) void k_compact(uint8_t *present, const uint32_t *chunk_off, uint32_t *uniq,
                                                     int64_t *uniq_out, Counters *cn, uint32_t nchunks,
                                                     DedupResult *dd, uint32_t tag, Gate *gate) {
-  uint32_t w[kWordsPerThread];
+  uint32_t w[kW];
   load_words(present, w);
-  const size_t b0 = ((size_t)blockIdx.x * kBlock + threadIdx.x) * kBytesPerThread;  // first byte of this thread
+  const size_t b0 = ((size_t)blockIdx.x * kBlock + threadIdx.x) * 4 * kW;  // first byte of this thread
   const uint32_t err = cn->err;
   if (err) {  // rejected batch: undo the marks
 #pragma unroll
-    for (int k = 0; k < kWordsPerThread; ++k)
+    for (int k = 0; k < kW; ++k)
       if (w[k]) reinterpret_cast<uint32_t *>(present + b0)[k] = 0;
     if (kFused && blockIdx.x == 0 && threadIdx.x == 0) {
       *gate = gate_with(err, 0);
@@ -364,7 +394,7 @@ __global__ __launch_bounds__(kBlock) void k_compact(uint8_t *present, const uint
   }
   uint32_t c = 0;
 #pragma unroll
-  for (int k = 0; k < kWordsPerThread; ++k) c += __popc(w[k]);
+  for (int k = 0; k < kW; ++k) c += __popc(w[k]);
   uint32_t tot;
   const uint32_t ex = block_exclusive_scan(c, tot);
   uint32_t first;
@@ -384,7 +414,7 @@ __global__ __launch_bounds__(kBlock) void k_compact(uint8_t *present, const uint
   if (tot == 0) return;
   uint32_t pos = first + ex;
 #pragma unroll
-  for (int k = 0; k < kWordsPerThread; ++k) {
+  for (int k = 0; k < kW; ++k) {
     uint32_t word = w[k];
     while (word) {  // marked bytes ascending: bit 8j is set for byte j of word k
       const uint32_t x = (uint32_t)(b0 + 4 * k + (__builtin_ctz(word) >> 3));
@@ -398,6 +428,23 @@ __global__ __launch_bounds__(kBlock) void k_compact(uint8_t *present, const uint
 
 constexpr uint32_t kFusedChunkMax = 2048;  // at most this many chunk sums are added up by each block
 
+template <int kW>
+static void launch_compaction(const DevState &d, const Scratch &sc, int64_t *unique_out, Counters *cn, DedupResult *dd,
+                              uint32_t tag, hipStream_t s) {
+  const dim3 g((unsigned)d.nchunks);
+  const uint32_t n = (uint32_t)d.nchunks;
+  hipLaunchKernelGGL(k_chunk_popc<kW>, g, dim3(kBlock), 0, s, d.present, d.chunk_sums, cn);
+  static_assert(kSmallChunkNodes / kChunkSmall <= kFusedChunkMax, "the small chunks' sums are always few");
+  if (kW == kWordsSmall || n <= kFusedChunkMax) {
+    hipLaunchKernelGGL((k_compact<kW, true>), g, dim3(kBlock), 0, s, d.present, d.chunk_sums, sc.uniq, unique_out, cn,
+                       n, dd, tag, sc.gate);
+  } else if constexpr (kW != kWordsSmall) {
+    hipLaunchKernelGGL(k_chunk_scan, dim3(1), dim3(kBlock), 0, s, d.chunk_sums, n, cn, dd, tag, sc.gate);
+    hipLaunchKernelGGL((k_compact<kW, false>), g, dim3(kBlock), 0, s, d.present, d.chunk_sums, sc.uniq, unique_out,
+                       cn, n, dd, tag, sc.gate);
+  }
+}
+
 void launch_dedup(const DevState &d, const int64_t *ids, uint64_t n, const int64_t *ann_ids, uint64_t ann_n,
                   const int64_t *clear_ids, uint64_t clear_n, uint32_t clear_bit, Scratch &sc, int64_t *unique_out,
                   Counters *cn, DedupResult *dd, uint32_t tag, hipStream_t s) {
@@ -406,36 +453,61 @@ void launch_dedup(const DevState &d, const int64_t *ids, uint64_t n, const int64
   const unsigned g = grid_for(work, kBlock, kMaxGrid);
   hipLaunchKernelGGL(k_mark, dim3(g), dim3(kBlock), 0, s, ids, (uint32_t)n, ann_ids, (uint32_t)ann_n, d.N,
                      d.present, clear_ids, (uint32_t)clear_n, clear_bit, d.mask, cn);
-  hipLaunchKernelGGL(k_chunk_popc, dim3((unsigned)d.nchunks), dim3(kBlock), 0, s, d.present, d.chunk_sums, cn);
-  if (d.nchunks <= kFusedChunkMax) {
-    hipLaunchKernelGGL(k_compact<true>, dim3((unsigned)d.nchunks), dim3(kBlock), 0, s, d.present, d.chunk_sums,
-                       sc.uniq, unique_out, cn, (uint32_t)d.nchunks, dd, tag, sc.gate);
-  } else {
-    hipLaunchKernelGGL(k_chunk_scan, dim3(1), dim3(kBlock), 0, s, d.chunk_sums, (uint32_t)d.nchunks, cn, dd,
-                       tag, sc.gate);
-    hipLaunchKernelGGL(k_compact<false>, dim3((unsigned)d.nchunks), dim3(kBlock), 0, s, d.present, d.chunk_sums,
-                       sc.uniq, unique_out, cn, (uint32_t)d.nchunks, dd, tag, sc.gate);
-  }
+  if (d.N <= kSmallChunkNodes)
+    launch_compaction<kWordsSmall>(d, sc, unique_out, cn, dd, tag, s);
+  else
+    launch_compaction<kWordsLarge>(d, sc, unique_out, cn, dd, tag, s);
 }
 
 // ------------------------------------------------------------ group by set
-// Every thread of the block must call this; returns the list index for
-// threads with pred set (one atomic per block).
-__device__ __forceinline__ uint32_t block_append(bool pred, uint32_t *counter) {
-  __shared__ uint32_t base;
-  uint32_t tot;
-  const uint32_t ex = block_exclusive_scan(pred ? 1u : 0u, tot);
-  if (threadIdx.x == 0 && tot) base = atomicAdd(counter, tot);
+// Every thread of the block must call this; index[i] is the list index of a
+// thread with pred[i] set (one atomic per block and list).
+template <int kN>
+__device__ __forceinline__ void block_append(const bool (&pred)[kN], uint32_t *const (&counter)[kN],
+                                             uint32_t (&index)[kN]) {
+  __shared__ uint32_t base[kN];
+  uint32_t tot[kN];
+  block_ranks(pred, index, tot);
+#pragma unroll
+  for (int i = 0; i < kN; ++i)
+    if (threadIdx.x == 64u * (i % (kBlock / 64)) && tot[i]) base[i] = atomicAdd(counter[i], tot[i]);
   __syncthreads();
-  const uint32_t r = base + ex;
+#pragma unroll
+  for (int i = 0; i < kN; ++i) index[i] += base[i];
   __syncthreads();
-  return r;
 }
 
-// Sum of a per-thread counter over the block, stored as this block's partial.
-__device__ __forceinline__ void block_count(uint32_t v, uint32_t *part, int slot) {
-  const uint32_t tot = block_sum(v);
-  if (threadIdx.x == 0) part[slot * kMaxGrid + blockIdx.x] = tot;
+__device__ __forceinline__ uint32_t block_append(bool pred, uint32_t *counter) {
+  uint32_t index[1];
+  block_append<1>({pred}, {counter}, index);
+  return index[0];
+}
+
+// Sums of kN per-thread counters over the block, stored as this block's
+// partials of slots [slot, slot + kN): one barrier for all of them.  With a
+// block scan per counter and list, the walk of a 9 K-request batch took 12.6 us
+// against 9.6, its resolve 10.2 against 7.9.  A kernel that calls this twice
+// with one kN has a barrier in between.
+template <int kN>
+__device__ __forceinline__ void block_counts(const uint32_t (&v)[kN], uint32_t *part, int slot) {
+  __shared__ uint32_t wsum[kN][kBlock / 64];
+  uint32_t x[kN];
+#pragma unroll
+  for (int i = 0; i < kN; ++i) x[i] = v[i];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+    for (int i = 0; i < kN; ++i) x[i] += __shfl_xor(x[i], o);
+  if ((threadIdx.x & 63) == 0)
+#pragma unroll
+    for (int i = 0; i < kN; ++i) wsum[i][threadIdx.x >> 6] = x[i];
+  __syncthreads();
+  if (threadIdx.x < kN) {
+    uint32_t t = 0;
+#pragma unroll
+    for (int w = 0; w < kBlock / 64; ++w) t += wsum[threadIdx.x][w];
+    part[(slot + threadIdx.x) * kMaxGrid + blockIdx.x] = t;
+  }
 }
 
 // Per unique ID, right after the dedup: its set, its arrival order among the
@@ -499,7 +571,7 @@ __device__ __forceinline__ void probe(const DevState &d, const Scratch &sc, uint
       sc.host_src[i] = kSrcStore | x;
     }
   }
-  block_count(c_early, sc.stat_part, kStEarly);
+  block_counts<1>({c_early}, sc.stat_part, kStEarly);
 }
 
 __global__ __launch_bounds__(kBlock) void k_probe(const DevState d, Scratch sc, uint64_t t, const Counters *cn) {
@@ -580,7 +652,7 @@ __device__ __forceinline__ void place(const DevState &d, const Scratch &sc, cons
       sc.ent[off + sc.arrival[u]] = u32x4{x, u, d.stat[x], 0};
     }
   }
-  block_count(c_hit, sc.stat_part, kStSettled);
+  block_counts<1>({c_hit}, sc.stat_part, kStSettled);
 }
 
 __global__ __launch_bounds__(kBlock) void k_place(const DevState d, Scratch sc, const Counters *cn) {
@@ -812,16 +884,29 @@ struct WalkCounts {
 // minimum of (level, static score, way); for the evaluation's ablations
 // (Sec. 5) the minimum of (static score, way), of (no announced use first,
 // then the furthest next use; way), or the set's round-robin pointer.
+//
+// A way's line is loaded before the set's IDs are ordered, so that the loads are
+// under way together.  What its class is computed from is not: reading every
+// line's window bits ahead, needed or not, slowed the host fetch beside the
+// walk by 1 % (pipelined 1M-node stream, 4545 us against 4486 for 8 gathers).
+struct Way {
+  uint32_t tag, st, ins;
+};
+__device__ __forceinline__ Way load_way(const DevState &d, uint32_t s, uint32_t w) {
+  const SetRec *rec = d.sets + s;
+  return Way{rec->tag[w], rec->stat[w], rec->ins[w]};
+}
+
 template <int P, typename Get>
 __device__ __forceinline__ void walk_set(const DevState &d, const Scratch &sc, uint32_t t, uint32_t s, uint32_t k,
-                                         uint32_t lane, WalkCounts &c, const Get &get) {
+                                         const Way &way, uint32_t lane, WalkCounts &c, const Get &get) {
   const bool ring_on = d.V > 0;
   const uint32_t recent_lvl = level_of(kClsRecent, ring_on);
   const uint32_t w = lane & (kWays - 1);   // the way this lane owns
   const uint32_t gsh = lane & ~(kWays - 1);  // first lane of the group in the wave
   const bool lead = w == 0;
   SetRec *rec = d.sets + s;
-  uint32_t tag = rec->tag[w], st = rec->stat[w], ins = rec->ins[w];
+  uint32_t tag = way.tag, st = way.st, ins = way.ins;
   uint32_t cls = kClsNone, lvl = 0, dist = 0;
   bool known = false;  // class (and next-use distance) of this way for this gather computed
   uint32_t rr = 0;     // round-robin pointer (the record holds its complement)
@@ -861,7 +946,7 @@ __device__ __forceinline__ void walk_set(const DevState &d, const Scratch &sc, u
     } else {
       if (!known) {  // batch-start resident
         if (d.U > 1) {  // from the information recorded at the last update
-          class_from_record(d.lreuse[s * kWays + w], ins, t, t - t % d.U, d.T, cls, dist);
+          class_from_record(d.lreuse[(uint64_t)s * kWays + w], ins, t, t - t % d.U, d.T, cls, dist);
         } else {        // exact: from its announced-use bits
           const uint32_t m = d.mask[tag];
           cls = (ins == t) ? kClsRecent : class_from_bits(m, t, d.L, d.T);
@@ -948,7 +1033,8 @@ __device__ __forceinline__ void walk_sets(const DevState &d, const Scratch &sc, 
     sort_big_segment(d, sc, e.off, e.k, cn->n_unique, lds);
     if (threadIdx.x < kWays) {
       u32x4 v{};  // entry (j & ~7) + lane, loaded 8 at a time
-      walk_set<P>(d, sc, t, e.set, e.k, lane, c, [&](uint32_t j, uint32_t &x, uint32_t &u, uint32_t &st) {
+      const Way way = load_way(d, e.set, lane);
+      walk_set<P>(d, sc, t, e.set, e.k, way, lane, c, [&](uint32_t j, uint32_t &x, uint32_t &u, uint32_t &st) {
         if ((j & (kWays - 1)) == 0 && j + lane < e.k) v = sc.ent[e.off + j + lane];
         const int src = (int)(j & (kWays - 1));
         x = __shfl(v.x, src, kWays);
@@ -963,9 +1049,10 @@ __device__ __forceinline__ void walk_sets(const DevState &d, const Scratch &sc, 
   const uint32_t waves = gridDim.x * (kBlock / 64);
   for (uint32_t i = blockIdx.x * (kBlock / 64) + wid; i < cn->n_mid; i += waves) {
     const WorkSet e = sc.work_mid[i];
+    const Way way = load_way(d, e.set, lane & (kWays - 1));
     order_entries<64>(sc.ent + e.off, e.k, lane, mid);
     if (lane < kWays)
-      walk_set<P>(d, sc, t, e.set, e.k, lane, c, [&](uint32_t j, uint32_t &x, uint32_t &u, uint32_t &st) {
+      walk_set<P>(d, sc, t, e.set, e.k, way, lane, c, [&](uint32_t j, uint32_t &x, uint32_t &u, uint32_t &st) {
         mid.get(j, x, u, st);
       });
     wave_lds_fence();
@@ -978,18 +1065,15 @@ __device__ __forceinline__ void walk_sets(const DevState &d, const Scratch &sc, 
   const uint32_t nw = cn->n_work;
   for (uint32_t i = blockIdx.x * (kBlock / kWays) + (threadIdx.x / kWays); i < nw; i += groups) {
     const WorkSet e = sc.work[i];
+    const Way way = load_way(d, e.set, lane & (kWays - 1));
     order_entries<kWays>(sc.ent + e.off, e.k, lane & (kWays - 1), small);
-    walk_set<P>(d, sc, t, e.set, e.k, lane, c, [&](uint32_t j, uint32_t &x, uint32_t &u, uint32_t &st) {
+    walk_set<P>(d, sc, t, e.set, e.k, way, lane, c, [&](uint32_t j, uint32_t &x, uint32_t &u, uint32_t &st) {
       small.get(j, x, u, st);
     });
     wave_lds_fence();
   }
-  block_count(c.hit, sc.stat_part, kStHits);
-  block_count(c.fill, sc.stat_part, kStFills);
-  block_count(c.evict, sc.stat_part, kStEvictions);
-  block_count(c.enq, sc.stat_part, kStEnqueued);
-  block_count(c.drop, sc.stat_part, kStDropped);
-  block_count(c.fin, sc.stat_part, kStFinal);
+  static_assert(kStFinal == kStHits + 5, "the walk's counters are consecutive");
+  block_counts<6>({c.hit, c.fill, c.evict, c.enq, c.drop, c.fin}, sc.stat_part, kStHits);
 }
 
 template <int P>
@@ -1209,7 +1293,7 @@ __global__ __launch_bounds__(kBlock) void k_qplace(const DevState d, Scratch sc,
       sc.stage.dst[i] = pos;
     }
   }
-  block_count(c_copy, sc.stat_part, kStEnqCopy);
+  block_counts<1>({c_copy}, sc.stat_part, kStEnqCopy);
 }
 
 // Victim-ring probe of every fill and the row source of every unique ID.  Builds
@@ -1244,7 +1328,7 @@ __device__ __forceinline__ void resolve(const DevState &d, const Scratch &sc, ui
     uint32_t rank = 0, enq_before = 0;  // u's enqueues before it: in its chunk, in the batch
     if (scan != kScanNone) {
       const uint32_t chunk = base / kScanChunk;
-      uint32_t off, tot;
+      uint32_t off;
       if (scan == kScanCounts) {
         const uint32_t nb = (U + kScanChunk - 1) / kScanChunk;
         uint64_t v = 0, sum;  // all chunks' enqueues, those before this chunk in the upper half
@@ -1259,7 +1343,9 @@ __device__ __forceinline__ void resolve(const DevState &d, const Scratch &sc, ui
       } else {
         off = sc.scan_part[chunk];
       }
-      rank = block_exclusive_scan(u < U ? sc.flags[u] & kFlagEnqueue : 0u, tot);
+      uint32_t ranks[1], tot[1];
+      block_ranks<1>({u < U && (sc.flags[u] & kFlagEnqueue)}, ranks, tot);
+      rank = ranks[0];
       enq_before = off + rank;
       if (u < U) sc.enq_before[u] = enq_before;
     }
@@ -1351,24 +1437,19 @@ __device__ __forceinline__ void resolve(const DevState &d, const Scratch &sc, ui
       // so the copy writes the output rows in order
       sc.hbm.src[u] = from_hbm ? (uint32_t)(code & kSrcIndex) : kNoRow;
     }
-    const uint32_t ih = n_early + block_append(from_host, &sc.gate->n_host);
+    uint32_t index[2];
+    block_append<2>({from_host, refill}, {&sc.gate->n_host, &sc.gate->n_fill}, index);
     if (from_host) {
-      sc.host_list[ih] = u;
-      sc.host_src[ih] = code;
+      sc.host_list[n_early + index[0]] = u;
+      sc.host_src[n_early + index[0]] = code;
     }
-    const uint32_t ifl = block_append(refill, &sc.gate->n_fill);
     if (refill) {
-      sc.fill.src[ifl] = u;
-      sc.fill.dst[ifl] = fd - 1;
+      sc.fill.src[index[1]] = u;
+      sc.fill.dst[index[1]] = fd - 1;
     }
   }
-  block_count(c_vhit, sc.stat_part, kStVictimHits);
-  block_count(c_miss, sc.stat_part, kStMisses);
-  block_count(c_hbm, sc.stat_part, kStHbm);
-  block_count(c_host, sc.stat_part, kStHost);
-  block_count(c_vring, sc.stat_part, kStVhRing);
-  block_count(c_vstaged, sc.stat_part, kStVhStaged);
-  block_count(c_vsame, sc.stat_part, kStVhSame);
+  static_assert(kStVhSame == kStVictimHits + 6, "the resolve's counters are consecutive");
+  block_counts<7>({c_vhit, c_miss, c_hbm, c_host, c_vring, c_vstaged, c_vsame}, sc.stat_part, kStVictimHits);
 }
 
 __global__ __launch_bounds__(kBlock) void k_resolve(const DevState d, Scratch sc, uint64_t t, uint8_t *outcome,
@@ -1389,8 +1470,8 @@ __device__ __forceinline__ void request_counts(const DevState &d, const Scratch 
     c_hit += o == 0;   // LSMGNN_HIT
     c_vhit += o == 1;  // LSMGNN_VICTIM_HIT
   }
-  block_count(c_hit, sc.stat_part, kStReqHits);
-  block_count(c_vhit, sc.stat_part, kStReqVictimHits);
+  static_assert(kStReqVictimHits == kStReqHits + 1, "the requests' counters are consecutive");
+  block_counts<2>({c_hit, c_vhit}, sc.stat_part, kStReqHits);
 }
 
 __global__ __launch_bounds__(kBlock) void k_request_counts(const DevState d, Scratch sc, const int64_t *ids,
@@ -1436,7 +1517,7 @@ __device__ __forceinline__ void enqueue_entries(const DevState &d, const Scratch
       sc.stage.dst[i] = pos;
     }
   }
-  block_count(c_copy, sc.stat_part, kStEnqCopy);
+  block_counts<1>({c_copy}, sc.stat_part, kStEnqCopy);
 }
 
 __global__ __launch_bounds__(kBlock) void k_enq_finalize(const DevState d, Scratch sc, const int64_t *ids, uint32_t n,
@@ -1545,9 +1626,10 @@ __global__ __launch_bounds__(kBlock) void k_tiny(const DevState d, Scratch sc, T
   for (uint32_t base = 0; base < n; base += kBlock) {
     const uint32_t i = base + threadIdx.x;
     const bool first = i < n && (i == 0 || key[i] != key[i - 1]);
-    uint32_t tot;
-    const uint32_t u = U + block_exclusive_scan(first ? 1u : 0u, tot);
-    U += tot;
+    uint32_t rank[1], tot[1];
+    block_ranks<1>({first}, rank, tot);
+    const uint32_t u = U + rank[0];
+    U += tot[0];
     if (first) {
       sc.uniq[u] = (uint32_t)key[i];
       a.unique_out[u] = (int64_t)key[i];
@@ -1732,7 +1814,10 @@ __global__ __launch_bounds__(kBlock) void k_host_fetch(const DevState d, Scratch
 #define LSM_HOST_GRID 40
 #endif
 #ifndef LSM_HBM_GRID
-#define LSM_HBM_GRID 65536  // the HBM-side copies: the largest grid of the measured sweep
+// the HBM-side copies: 65536 blocks.  A resident stream's hit copies beside the
+// next gather's metadata: 1142 us for four gathers, 1219 with 8192 blocks, 1280
+// with 1024, 1250 with 262144
+#define LSM_HBM_GRID 65536
 #endif
 // Staging and fills move the evicted and the missed rows, often few or none of
 // the batch's, while their grid is sized for all of it: blocks that find

@@ -10,9 +10,12 @@ namespace lsm {
 constexpr uint32_t kWays = 8;
 constexpr uint32_t kEmpty = 0xffffffffu;
 constexpr int kBlock = 256;          // threads per block for every kernel
-constexpr int kBytesPerThread = 64;  // dedup map bytes per thread
-constexpr int kWordsPerThread = kBytesPerThread / 4;
-constexpr int kChunkBytes = kBlock * kBytesPerThread;  // dedup map bytes (nodes) per block
+// Dedup map words per thread of the scans, and bytes (nodes) per block: the
+// small chunk spreads the map of few nodes over more blocks, the large one
+// keeps the chunk sums of many nodes few.
+constexpr int kWordsSmall = 4, kWordsLarge = 16;
+constexpr int kChunkSmall = kBlock * 4 * kWordsSmall, kChunkLarge = kBlock * 4 * kWordsLarge;
+constexpr uint64_t kSmallChunkNodes = 1ull << 22;  // up to this many nodes take the small chunk
 constexpr uint32_t kScanChunk = kBlock;  // enqueue flags (unique IDs) per partial count
 constexpr int kMaxQueues = 32;       // victim-queue slots: L + 1 <= 32
 // sets by their unique IDs in a batch: up to kSmallSet walked and ordered by 8
@@ -62,9 +65,9 @@ static_assert(sizeof(SetRec) == 128, "set record must be one 128-byte line");
 enum StatSlot : int {
   kStHits, kStFills, kStEvictions, kStEnqueued, kStDropped, kStFinal,  // set walk
   kStVictimHits, kStMisses, kStHbm, kStHost,                           // resolve
+  kStVhRing, kStVhStaged, kStVhSame,                                   // victim hits by row source
   kStEnqCopy,                                                          // enqueue finalize
   kStReqHits, kStReqVictimHits,                                        // per-request outcomes
-  kStVhRing, kStVhStaged, kStVhSame,                                   // victim hits by row source
   kStEarly,                                                            // misses listed before the walk
   kStSettled,                                                          // hits in sets that need no walk
   kNumStat
@@ -192,7 +195,7 @@ struct DevState {
   uint32_t *ring_tag;    // [V] FIFO ring entries, or queue slot k's entries at k * C
   uint8_t *ring_rows;    // [V][R] pinned host, device-visible address (ring or queue rows)
   const uint8_t *store;  // [N][R] pinned host, device-visible address
-  uint8_t *present;      // [nchunks * kChunkBytes] dedup byte map (all zero between calls)
+  uint8_t *present;      // [nchunks chunks] dedup byte map (all zero between calls)
   uint32_t *chunk_sums;  // [nchunks]
   uint32_t *set_count;   // [S] (all zero between calls)
   uint32_t *set_dirty;   // [S] 1 + index of the last gather that missed in the set
@@ -202,7 +205,7 @@ struct DevState {
   uint64_t *tail;        // [2] ring entries ever enqueued (the FIFO tail), and
                          //     the tail before the last gather's enqueues
   uint64_t N, R, S, V;
-  uint64_t nchunks;
+  uint64_t nchunks;      // of kChunkSmall bytes for at most kSmallChunkNodes nodes, else kChunkLarge
   uint32_t L, T;
   uint32_t policy;
   uint32_t qmode;        // kVictimQueues: per-reuse-iteration queues instead of the ring

@@ -1075,8 +1075,9 @@ lsmgnn_status lsmgnn_cache_create(const lsmgnn_config *cfg, lsmgnn_cache **out) 
   d.store = static_cast<const uint8_t *>(store_dev);  // null for a pageable store
   c->pageable = pageable;
   c->store_host = static_cast<const uint8_t *>(cfg->host_store);
-  d.nchunks = (N + lsm::kChunkBytes - 1) / lsm::kChunkBytes;
-  const uint64_t map_bytes = d.nchunks * lsm::kChunkBytes;
+  const uint64_t chunk = N <= lsm::kSmallChunkNodes ? lsm::kChunkSmall : lsm::kChunkLarge;
+  d.nchunks = (N + chunk - 1) / chunk;
+  const uint64_t map_bytes = d.nchunks * chunk;
   const uint64_t B = cfg->max_batch;
   Scratch sc{};
 

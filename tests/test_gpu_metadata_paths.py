@@ -140,3 +140,15 @@ def test_small_gather_errors():
     assert r.n_unique == 40 and bool((r.outcome == lsmgnn.HIT).all())
     assert np.array_equal(r.out.cpu().numpy(), store.np[:40])
     cache.close()
+
+
+@pytest.mark.parametrize("nodes", [4095, 4096, 4097, (1 << 22) - 1, 1 << 22, (1 << 22) + 1])
+def test_dedup_chunks(nodes):
+    """Node counts at the edges of the dedup map's chunks, and where the chunk size changes; the top IDs are requested."""
+    log(f"case: {nodes} nodes")
+    rng = np.random.default_rng(nodes)
+    batches = [np.concatenate([rng.integers(0, nodes, 3000), [0, nodes - 1, nodes - 2], rng.integers(0, nodes, 40)])
+               for _ in range(4)]
+    store = Store.random_bytes(nodes, 16, 6)
+    stat = rng.integers(0, 9, nodes).astype(np.uint32)
+    run_parity(store, stat, 500, 300, 2, batches, rows="all", label=f"N={nodes}")
