@@ -297,10 +297,10 @@ lsmgnn_status lsmgnn_expand(const void *rows, const int64_t *inverse, uint64_t n
    scores (num_nodes uint32, device): floor(rank / max rank * (2^32 - 1)).
    rank (num_nodes double, device) receives the ranks, or may be NULL.
    Ranks agree with a sequential evaluation to rounding (the per-node sums are
-   accumulated with atomics in varying order), so a score may differ by one
-   where its rank lies within rounding of a quantization step.
-   Work memory of 4 bytes per entry plus 24 bytes per node is allocated and
-   freed inside; the call is ordered after the work queued on `stream` and
+   accumulated partly with atomics in varying order), so a score may differ by
+   one where its rank lies within rounding of a quantization step.
+   Work memory of 16 bytes per entry (4, and slower, where that cannot be had)
+   plus 24 bytes per node is allocated and freed inside; the call is ordered after the work queued on `stream` and
    returns once the scores are written.
    Errors: E_INVAL (num_nodes 0 or above 2^32 - 1, damping outside [0, 1), NULL
    offsets/scores, or NULL adj with entries); E_RANGE (offsets not starting at 0

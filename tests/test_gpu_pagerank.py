@@ -122,3 +122,73 @@ def test_cache_parity_with_pagerank_scores():
     for policy in ("hybrid", "static"):
         run_parity(store, static, cfg.cache.num_sets, cfg.cache.victim_rows, cfg.cache.lookahead, batches,
                    rows="all", state_every=5, label=f"pagerank-{policy}", policy=policy)
+
+
+def _skewed_graph(n, entries, seed, hub=0.3):
+    """A graph of exactly `entries` entries, a share `hub` of them naming node n // 2, over rows of very uneven length."""
+    rng = np.random.default_rng(seed)
+    cuts = np.sort(rng.integers(0, entries + 1, n - 1)) if n > 1 else np.zeros(0, np.int64)
+    offsets = np.concatenate([[0], cuts, [entries]]).astype(np.int64)
+    adj = rng.integers(0, n, entries)
+    adj[rng.random(entries) < hub] = n // 2
+    return offsets, adj.astype(np.uint32)
+
+
+def _check_with_dangling(offsets, adj, d, K, label):
+    """As _check, on graphs most of whose nodes have no entries: the dangling mass is then the longest sum, of Z terms,
+    and enters every rank, so each side's rounding is bounded by (max(D, Z) + 4) eps / (1 - d) by the same argument."""
+    n = offsets.size - 1
+    s_g, r_g = _gpu_pagerank(offsets, adj, d, K)
+    r_o = pagerank(offsets, adj, d, K)
+    terms = max(int(np.bincount(adj, minlength=n).max()), int(np.count_nonzero(np.diff(offsets) == 0)))
+    l1 = float(np.abs(r_g - r_o).sum())
+    log(f"  {label}: |dr|_1 {l1:.3g}, bound {2 * (terms + 4) * EPS / (1 - d):.3g}")
+    assert l1 <= 2 * (terms + 4) * EPS / (1 - d)
+    assert np.array_equal(s_g, np.floor(r_g / r_g.max() * 4294967295.0).astype(np.uint32))
+    assert np.abs(s_g.astype(np.int64) - rank_scores(r_o).astype(np.int64)).max() <= 1
+
+
+@pytest.mark.parametrize("nodes", [1, 255, 257, 70_000])
+@pytest.mark.parametrize("entries", [1, 7, 9, 2047, 2048, 2049, 4095, 4097, 3 * 4096 + 1, 300_001])
+def test_tile_edges(nodes, entries):
+    """Entry counts at the edges of the sort's and the pull's tiles, node counts that take one to three sort passes,
+    one target whose run spans many tiles."""
+    log(f"case: pagerank tiles N={nodes} E={entries}")
+    _check_with_dangling(*_skewed_graph(nodes, entries, nodes + entries), 0.85, 6, f"N={nodes} E={entries}")
+
+
+def test_rows_concentrated():
+    """All entries in a few rows far apart, so that tiles search past long stretches of empty rows."""
+    n, entries = 200_000, 50_000
+    offsets = np.zeros(n + 1, np.int64)
+    offsets[7:] += entries // 2
+    offsets[150_000:] += entries - entries // 2
+    adj = np.random.default_rng(1).integers(0, n, entries).astype(np.uint32)
+    log("case: pagerank rows far apart")
+    _check_with_dangling(offsets, adj, 0.85, 4, "rows far apart")
+
+
+def test_without_memory_for_the_sort():
+    """With too little device memory for the sorted entries the shares are pushed instead, with the same result."""
+    log("case: pagerank without memory for the sort")
+    n, entries = 5000, 60_000_000  # sorting takes 0.96 GB, the sources alone 0.24
+    g = torch.Generator(device="cuda").manual_seed(3)
+    adj = torch.randint(0, n, (entries,), generator=g, device="cuda", dtype=torch.int32)
+    offsets = torch.linspace(0, entries, n + 1, dtype=torch.float64, device="cuda").round().long()
+    with_room = lsmgnn.pagerank_scores(offsets, adj, 0.85, 3, rank=True)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    hold, keep = [], 600 << 20
+    free = torch.cuda.mem_get_info()[0]
+    while free > keep + (64 << 20):
+        hold.append(torch.empty(min(free - keep, 32 << 30), dtype=torch.uint8, device="cuda"))
+        free = torch.cuda.mem_get_info()[0]
+    assert free < 900 << 20
+    pushed = lsmgnn.pagerank_scores(offsets, adj, 0.85, 3, rank=True)
+    torch.cuda.synchronize()
+    del hold
+    torch.cuda.empty_cache()
+    # both are the same sums of at most D terms in another order (see the bound above)
+    D = int(torch.bincount(adj, minlength=n).max())
+    l1 = float((with_room[1] - pushed[1]).abs().sum())
+    assert l1 <= 2 * (D + 4) * EPS / 0.15
