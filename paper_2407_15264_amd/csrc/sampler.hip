@@ -22,17 +22,28 @@
 // reduced to [0, m) as ((r >> 32) * m) >> 32.
 //
 // Per hop, on the caller's stream:
-//   tiles    per tile of 256 frontier entries: each entry's k, its offset
-//            within the tile, and the tile's sum
-//   top      one block: exclusive scan of the tile sums, the list length
-//   draw     one wave per frontier node: lane j makes Floyd's j-th draw, the
-//            k steps are resolved in order with one ballot each, and each
-//            lane's rank among the k positions places its sample in the
-//            list; the next frontier's byte-map marks are plain byte stores
-//   popc / chunk scan / compact: the marked nodes in ascending order become
-//            the next frontier, and the map is cleared
-// Every count stays on the device; the host learns the list length once, at
-// the end.  The byte map holds one byte per node and is all zero between calls.
+//   counts   per chunk of the byte map of marked nodes: how many there are and
+//            how many samples they draw
+//   frontier the marked nodes in ascending order become the hop's frontier, each
+//            with its first sample's place within the chunk's; the map is
+//            cleared.  Each block adds up the chunks before its own; the last
+//            one has the hop's totals (with many chunks one block scans them
+//            first)
+//   draw     8 to 64 lanes per frontier node, by the fanout: lane j makes
+//            Floyd's j-th draw, the k steps are resolved in order with one
+//            ballot each, and each lane's rank among the k positions places
+//            its sample in the list; the next frontier's byte-map marks are
+//            plain byte stores
+// Every count stays on the device; the frontier of the last hop gives the list's
+// length and the status, written to the caller's pinned memory at once.  The
+// byte map holds one byte per node and is all zero between calls.
+//
+// A minibatch is bound by its chain of dependent launches (2-8 us each), so
+// there are few: ten for three hops.  With the offsets in two kernels of their
+// own, a separate scan of the chunks, a wave per node whatever the fanout and
+// the result copied afterwards there were twenty-two.  1024 seeds of a 1 M-node
+// graph at (15, 10, 5), waited for: 72 us against 102; 4096 seeds of a 10 M-node
+// graph at (10, 5, 5), queued: 60 against 83.
 //
 // Typed graphs: the list split by node type (per tile of 256 requests a count
 // per type, one block's scan per type, then a ballot rank per type and wave),
@@ -48,9 +59,15 @@
 namespace lsm_smp {
 
 constexpr int kBlock = 256;
-constexpr int kMapBytesPerThread = 64;                        // byte-map bytes per thread
-constexpr uint64_t kChunk = (uint64_t)kBlock * kMapBytesPerThread;  // byte-map bytes per block
-constexpr uint32_t kTile = kBlock;  // frontier entries per tile (one per thread)
+// Byte-map words per thread, and bytes (nodes) per block, a chunk: the small
+// one for at most kSmallChunkNodes nodes, else the large one, so that the
+// chunks are few.  A thread looks up its marked nodes' degrees one by one, and
+// the nodes of a power-law graph's hubs lie together: with 64 bytes per thread
+// the two passes over 10 M nodes took 11 and 13 us, with 16 they take 5 and 8.
+constexpr int kWordsSmall = 4, kWordsLarge = 16;
+constexpr uint64_t kSmallChunkNodes = 1ull << 24;
+// at most this many small chunks, and large ones, are added up by each block
+constexpr uint32_t kFusedSmall = 4096, kFusedLarge = 2048;
 constexpr unsigned kMaxGrid = 4096;
 constexpr uint32_t kMaxFanout = 64;  // one wave's lanes
 constexpr uint32_t kMaxHops = 8;
@@ -136,10 +153,6 @@ __global__ __launch_bounds__(kBlock) void k_validate(const int64_t *off, const u
   if (bad) *err = 1u;
 }
 
-__global__ void k_init(Ctl *ctl, uint64_t n_seeds) {
-  if (threadIdx.x == 0) *ctl = Ctl{0u, 0u, n_seeds, n_seeds};
-}
-
 // The seeds open the list and mark the first frontier.
 __global__ __launch_bounds__(kBlock) void k_seeds(const int64_t *seeds, uint64_t n, uint64_t N, int64_t *out,
                                                   uint64_t cap, uint8_t *present, Ctl *ctl) {
@@ -156,11 +169,16 @@ __global__ __launch_bounds__(kBlock) void k_seeds(const int64_t *seeds, uint64_t
   if (__ballot(bad) && __lane_id() == 0) atomicOr(&ctl->err, 1u);
 }
 
-__device__ __forceinline__ void load_map(const uint8_t *present, uint32_t (&w)[kMapBytesPerThread / 4]) {
-  const u32x4 *p = reinterpret_cast<const u32x4 *>(present + (uint64_t)blockIdx.x * kChunk +
-                                                    (uint64_t)threadIdx.x * kMapBytesPerThread);
+template <int kW>
+__device__ __forceinline__ uint64_t chunk_node(uint32_t chunk) {  // first node of this thread's words
+  return ((uint64_t)chunk * kBlock + threadIdx.x) * 4 * kW;
+}
+
+template <int kW>
+__device__ __forceinline__ void load_map(const uint8_t *present, uint64_t v0, uint32_t (&w)[kW]) {
+  const u32x4 *p = reinterpret_cast<const u32x4 *>(present + v0);
 #pragma unroll
-  for (int k = 0; k < kMapBytesPerThread / 16; ++k) {
+  for (int k = 0; k < kW / 4; ++k) {
     const u32x4 a = p[k];
     w[4 * k] = a.x;
     w[4 * k + 1] = a.y;
@@ -169,137 +187,168 @@ __device__ __forceinline__ void load_map(const uint8_t *present, uint32_t (&w)[k
   }
 }
 
-// marked bytes hold exactly 1, so a word's popcount counts them
-__global__ __launch_bounds__(kBlock) void k_popc(const uint8_t *present, uint32_t *chunk_sums) {
-  uint32_t w[kMapBytesPerThread / 4];
-  load_map(present, w);
-  uint32_t c = 0;
-#pragma unroll
-  for (int k = 0; k < kMapBytesPerThread / 4; ++k) c += __popc(w[k]);
-  uint32_t tot;
-  (void)block_exclusive_scan(c, tot);
-  if (threadIdx.x == 0) chunk_sums[blockIdx.x] = tot;
-}
-
-__global__ __launch_bounds__(kBlock) void k_chunk_scan(uint32_t *chunk_sums, uint32_t nchunks, Ctl *ctl) {
-  uint32_t carry = 0;
-  for (uint32_t base = 0; base < nchunks; base += kBlock) {
-    const uint32_t i = base + threadIdx.x;
-    const uint32_t v = i < nchunks ? chunk_sums[i] : 0u;
-    uint32_t tot;
-    const uint32_t ex = block_exclusive_scan(v, tot);
-    if (i < nchunks) chunk_sums[i] = carry + ex;
-    carry += tot;
-  }
-  if (threadIdx.x == 0) ctl->frontier = carry;
-}
-
-// The marked nodes, ascending, become the frontier; the map is cleared.
-__global__ __launch_bounds__(kBlock) void k_compact(uint8_t *present, const uint32_t *chunk_off, uint32_t *frontier) {
-  uint32_t w[kMapBytesPerThread / 4];
-  load_map(present, w);
-  const uint64_t b0 = (uint64_t)blockIdx.x * kChunk + (uint64_t)threadIdx.x * kMapBytesPerThread;
-  uint32_t c = 0;
-#pragma unroll
-  for (int k = 0; k < kMapBytesPerThread / 4; ++k) c += __popc(w[k]);
-  uint32_t tot;
-  const uint32_t ex = block_exclusive_scan(c, tot);
-  if (tot == 0) return;
-  uint32_t pos = chunk_off[blockIdx.x] + ex;
-#pragma unroll
-  for (int k = 0; k < kMapBytesPerThread / 4; ++k) {
-    uint32_t word = w[k];
-    if (word) reinterpret_cast<uint32_t *>(present + b0)[k] = 0u;
-    while (word) {  // marked bytes ascending: bit 8j is set for byte j
-      frontier[pos++] = (uint32_t)(b0 + 4 * k + (__builtin_ctz(word) >> 3));
-      word &= word - 1u;
-    }
-  }
-}
-
-__device__ __forceinline__ uint32_t draws_of(const int64_t *off, uint32_t v, uint32_t fanout) {
+__device__ __forceinline__ uint32_t draws_of(const int64_t *off, uint64_t v, uint32_t fanout) {
   const uint64_t deg = (uint64_t)(off[v + 1] - off[v]);
   return (uint32_t)(fanout < deg ? fanout : deg);
 }
 
-// Per tile of the frontier, the number of samples it draws.
-__global__ __launch_bounds__(kBlock) void k_tiles(const uint32_t *frontier, const int64_t *off, uint32_t fanout,
-                                                  uint64_t *tile_sum, uint32_t *node_off, const Ctl *ctl) {
-  const uint32_t f = ctl->frontier;
-  const uint32_t ntiles = (f + kTile - 1) / kTile;
-  for (uint32_t b = blockIdx.x; b < ntiles; b += gridDim.x) {
-    const uint32_t i = b * kTile + threadIdx.x;
-    const uint32_t c = i < f ? draws_of(off, frontier[i], fanout) : 0u;
-    uint32_t tot;
-    const uint32_t ex = block_exclusive_scan(c, tot);
-    if (i < f) node_off[i] = ex;
-    if (threadIdx.x == 0) tile_sum[b] = tot;
+// f(node) for each marked node of the thread's words, ascending (marked bytes
+// hold exactly 1: bit 8j of a word is set for its byte j)
+template <int kW, typename F>
+__device__ __forceinline__ void for_marked(const uint32_t (&w)[kW], uint64_t v0, const F &f) {
+#pragma unroll
+  for (int k = 0; k < kW; ++k)
+    for (uint32_t word = w[k]; word; word &= word - 1u) f(v0 + 4 * k + (__builtin_ctz(word) >> 3));
+}
+
+// Marked nodes and samples drawn, as one word: a large chunk has at most 2^14
+// nodes and draws at most 2^20 samples, so the chunks that are added up draw
+// 2^31 at most.
+__device__ __forceinline__ uint64_t pack(uint32_t nodes, uint32_t draws) { return (uint64_t)nodes << 32 | draws; }
+
+template <int kW>
+__global__ __launch_bounds__(kBlock) void k_counts(const uint8_t *present, const int64_t *off, uint32_t fanout,
+                                                   uint64_t *chunk_sum) {
+  const uint64_t v0 = chunk_node<kW>(blockIdx.x);
+  uint32_t w[kW];
+  load_map<kW>(present, v0, w);
+  uint32_t c = 0, d = 0;
+  for_marked<kW>(w, v0, [&](uint64_t v) {
+    ++c;
+    d += draws_of(off, v, fanout);
+  });
+  uint64_t tot;
+  (void)block_exclusive_scan64(pack(c, d), tot);
+  if (threadIdx.x == 0) chunk_sum[blockIdx.x] = tot;
+}
+
+// The hop's totals: its frontier and its samples' places in the list; on the
+// last hop the call's result (list length, status): LSMGNN_OK, E_RANGE for a bad
+// seed, or E_INVAL for a list longer than the output.
+struct Hop {
+  uint64_t n_seeds;  // list length before the hop, if it is the first
+  uint64_t cap;
+  uint64_t *res;     // the last hop's, else NULL
+  int first;
+};
+__device__ __forceinline__ void publish_hop(const Hop &h, uint32_t nodes, uint64_t draws, Ctl *ctl) {
+  const uint64_t len = h.first ? h.n_seeds : ctl->len;
+  ctl->frontier = nodes;
+  ctl->hop_base = len;
+  ctl->len = len + draws;
+  if (h.res) {
+    const uint64_t all = len + draws;
+    const uint64_t st = ctl->err ? (uint64_t)LSMGNN_E_RANGE : all > h.cap ? (uint64_t)LSMGNN_E_INVAL : (uint64_t)LSMGNN_OK;
+    __hip_atomic_store(h.res, all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(h.res + 1, st, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    ctl->err = 0;  // for the next call
   }
 }
 
-// One block: tile sums -> tile offsets within the hop; the hop's samples take
-// list positions [len, len + total).
-__global__ __launch_bounds__(kBlock) void k_top(uint64_t *tile_sum, Ctl *ctl) {
-  const uint32_t f = ctl->frontier;
-  const uint32_t ntiles = (f + kTile - 1) / kTile;
-  uint64_t carry = 0;
-  for (uint32_t base = 0; base < ntiles; base += kBlock) {
+// One block, more than kFusedLarge chunks: each chunk's first frontier entry
+// and first sample.
+__global__ __launch_bounds__(kBlock) void k_chunk_scan(const uint64_t *chunk_sum, uint32_t nchunks,
+                                                       uint32_t *chunk_first, uint64_t *chunk_base, Hop hop,
+                                                       Ctl *ctl) {
+  uint32_t nodes = 0;
+  uint64_t draws = 0;
+  for (uint32_t base = 0; base < nchunks; base += kBlock) {
     const uint32_t i = base + threadIdx.x;
-    const uint64_t v = i < ntiles ? tile_sum[i] : 0ull;
+    const uint64_t v = i < nchunks ? chunk_sum[i] : 0ull;
     uint64_t tot;
-    const uint64_t ex = block_exclusive_scan64(v, tot);
-    if (i < ntiles) tile_sum[i] = carry + ex;
-    carry += tot;
+    const uint64_t ex = block_exclusive_scan64(v, tot);  // 256 chunks draw at most 2^28 samples
+    if (i < nchunks) {
+      chunk_first[i] = nodes + (uint32_t)(ex >> 32);
+      chunk_base[i] = draws + (uint32_t)ex;
+    }
+    nodes += (uint32_t)(tot >> 32);
+    draws += (uint32_t)tot;
   }
-  if (threadIdx.x == 0) {
-    ctl->hop_base = ctl->len;
-    ctl->len += carry;
-  }
+  if (threadIdx.x == 0) publish_hop(hop, nodes, draws, ctl);
 }
 
-// (list length, status) of the call: LSMGNN_OK, E_RANGE for a bad seed, or
-// E_INVAL for a list longer than the output
-__global__ void k_result(const Ctl *ctl, uint64_t cap, uint64_t *res) {
-  if (threadIdx.x == 0) {
-    res[0] = ctl->len;
-    res[1] = ctl->err ? (uint64_t)LSMGNN_E_RANGE : ctl->len > cap ? (uint64_t)LSMGNN_E_INVAL : (uint64_t)LSMGNN_OK;
+// The marked nodes, ascending, become the frontier; node_off: a node's first
+// sample among its chunk's, chunk_base: the chunk's among the hop's.
+template <int kW, bool kFused>
+__global__ __launch_bounds__(kBlock) void k_frontier(uint8_t *present, const int64_t *off, uint32_t fanout,
+                                                     const uint64_t *chunk_sum, const uint32_t *chunk_first,
+                                                     uint64_t *chunk_base, uint32_t *frontier, uint32_t *node_off,
+                                                     Hop hop, Ctl *ctl) {
+  const uint64_t v0 = chunk_node<kW>(blockIdx.x);
+  uint32_t w[kW];
+  load_map<kW>(present, v0, w);
+  uint64_t before = 0;  // the chunks before this one
+  if constexpr (kFused) {
+    uint64_t sum = 0;
+    for (uint32_t j = threadIdx.x; j < blockIdx.x; j += kBlock) sum += chunk_sum[j];
+    (void)block_exclusive_scan64(sum, before);
   }
+  uint32_t c = 0, d = 0;
+  for_marked<kW>(w, v0, [&](uint64_t v) {
+    ++c;
+    d += draws_of(off, v, fanout);
+  });
+  uint64_t tot;
+  const uint64_t ex = block_exclusive_scan64(pack(c, d), tot);
+  uint32_t pos = (uint32_t)(ex >> 32), place = (uint32_t)ex;
+  if constexpr (kFused) {
+    pos += (uint32_t)(before >> 32);
+    if (threadIdx.x == 0) {
+      chunk_base[blockIdx.x] = (uint32_t)before;
+      if (blockIdx.x == gridDim.x - 1) {
+        const uint64_t all = before + tot;
+        publish_hop(hop, (uint32_t)(all >> 32), (uint32_t)all, ctl);
+      }
+    }
+  } else {
+    pos += chunk_first[blockIdx.x];
+  }
+#pragma unroll
+  for (int k = 0; k < kW; ++k)
+    if (w[k]) reinterpret_cast<uint32_t *>(present + v0)[k] = 0u;
+  for_marked<kW>(w, v0, [&](uint64_t v) {
+    frontier[pos] = (uint32_t)v;
+    node_off[pos] = place;
+    ++pos;
+    place += draws_of(off, v, fanout);
+  });
 }
 
-// One wave per frontier node: lane j makes Floyd's j-th draw; the k steps are
-// then resolved in order with one ballot each (a draw already taken yields
-// the step's own bound instead), and each lane's rank among the k positions
-// gives its place in the ascending list.
-__global__ __launch_bounds__(kBlock) void k_draw_wave(const uint32_t *frontier, const int64_t *off,
-                                                      const uint32_t *adj, uint32_t fanout, uint64_t key_hop,
-                                                      const uint64_t *tile_off, const uint32_t *node_off,
-                                                      int64_t *out, uint64_t cap, uint8_t *present, int mark,
-                                                      const Ctl *ctl) {
+// G lanes per frontier node (G >= fanout): lane j makes Floyd's j-th draw; the
+// k steps are then resolved in order with one ballot each (a draw already
+// taken yields the step's own bound instead), and each lane's rank among the k
+// positions gives its place in the ascending list.
+template <int G>
+__global__ __launch_bounds__(kBlock) void k_draw(const uint32_t *frontier, const int64_t *off, const uint32_t *adj,
+                                                 uint32_t fanout, uint64_t key_hop, const uint64_t *chunk_base,
+                                                 uint32_t chunk_shift, const uint32_t *node_off, int64_t *out,
+                                                 uint64_t cap, uint8_t *present, int mark, const Ctl *ctl) {
   const uint32_t f = ctl->frontier;
   const uint64_t hop_base = ctl->hop_base;
-  const int lane = threadIdx.x & 63;
-  const uint32_t waves = gridDim.x * (kBlock / 64);
-  for (uint32_t i = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6); i < f; i += waves) {
+  const uint32_t lane = threadIdx.x & (G - 1);
+  const uint64_t mine = (G == 64 ? ~0ull : (1ull << (G & 63)) - 1ull) << (threadIdx.x & 63u & ~(uint32_t)(G - 1));
+  const uint32_t groups = gridDim.x * (kBlock / G);
+  for (uint32_t i = blockIdx.x * (kBlock / G) + threadIdx.x / G; i < f; i += groups) {
     const uint32_t v = frontier[i];
     const int64_t o = off[v];
-    const uint64_t deg = (uint64_t)(off[v + 1] - o);
+    const uint64_t deg = (uint64_t)(off[v + 1ull] - o);
     const uint32_t k = (uint32_t)(fanout < deg ? fanout : deg);
     if (k == 0) continue;
-    uint32_t pos = (uint32_t)lane, rank = (uint32_t)lane;  // k == deg: every position, in order
+    uint32_t pos = lane, rank = lane;  // k == deg: every position, in order
     if (k < deg) {
       const uint64_t jj = deg - k + (uint64_t)lane;  // this lane's step bound
       uint32_t r = 0;
-      if (lane < (int)k) r = (uint32_t)(((stream_at(derive(key_hop, v), (uint64_t)lane) >> 32) * (jj + 1)) >> 32);
+      if (lane < k) r = (uint32_t)(((stream_at(derive(key_hop, v), (uint64_t)lane) >> 32) * (jj + 1)) >> 32);
       for (uint32_t q = 0; q < k; ++q) {
-        const uint32_t rq = __shfl(r, (int)q);
-        const bool taken = __ballot(lane < (int)q && pos == rq) != 0ull;
-        if (lane == (int)q) pos = taken ? (uint32_t)jj : r;
+        const uint32_t rq = __shfl(r, (int)q, G);
+        const bool taken = (__ballot(lane < q && pos == rq) & mine) != 0ull;
+        if (lane == q) pos = taken ? (uint32_t)jj : r;
       }
       rank = 0;  // the positions are distinct
-      for (uint32_t q = 0; q < k; ++q) rank += __shfl(pos, (int)q) < pos ? 1u : 0u;
+      for (uint32_t q = 0; q < k; ++q) rank += __shfl(pos, (int)q, G) < pos ? 1u : 0u;
     }
-    if (lane < (int)k) {
-      const uint64_t p = hop_base + tile_off[i / kTile] + node_off[i] + rank;
+    if (lane < k) {
+      const uint64_t p = hop_base + chunk_base[v >> chunk_shift] + node_off[i] + rank;
       const uint32_t u = adj[o + pos];
       if (p < cap) out[p] = (int64_t)u;
       if (mark) present[u] = 1;
@@ -426,17 +475,18 @@ struct lsmgnn_sampler {
   int device = 0;
   const int64_t *off = nullptr;
   const uint32_t *adj = nullptr;
-  uint64_t N = 0, nchunks = 0, max_tiles = 0;
+  uint64_t N = 0, nchunks = 0, chunk = 0;  // byte-map bytes per block
+  uint32_t chunk_shift = 0;
   uint32_t hops = 0;
   uint32_t fanout[lsm_smp::kMaxHops] = {};
   uint64_t seed = 0;
-  uint8_t *present = nullptr;  // byte map, nchunks * kChunk bytes, zero between calls
-  uint32_t *chunk_sums = nullptr;
-  uint32_t *frontier[2] = {nullptr, nullptr};
-  uint64_t *tile_sum = nullptr;
-  lsm_smp::Ctl *ctl = nullptr;     // device
+  uint8_t *present = nullptr;  // byte map, nchunks * chunk bytes, zero between calls
+  uint64_t *chunk_sum = nullptr, *chunk_base = nullptr;
+  uint32_t *chunk_first = nullptr;  // only with more than kFusedLarge large chunks
+  uint32_t *frontier = nullptr, *node_off = nullptr;
+  lsm_smp::Ctl *ctl = nullptr;      // device; its error flag is zero between calls
   uint64_t *res = nullptr;          // device: (list length, status) of the last call queued
-  uint64_t *res_host = nullptr;     // pinned: the same, read by the blocking call
+  uint64_t *res_host = nullptr, *res_dev = nullptr;  // pinned: the same, read by the blocking call
 };
 
 namespace {
@@ -454,46 +504,82 @@ struct DeviceScope {
 };
 
 void sampler_free(lsmgnn_sampler *s) {
-  for (void *p : {(void *)s->present, (void *)s->chunk_sums, (void *)s->frontier[0], (void *)s->frontier[1],
-                  (void *)s->tile_sum, (void *)s->ctl, (void *)s->res})
+  for (void *p : {(void *)s->present, (void *)s->chunk_sum, (void *)s->chunk_base, (void *)s->chunk_first,
+                  (void *)s->frontier, (void *)s->node_off, (void *)s->ctl, (void *)s->res})
     if (p) (void)hipFree(p);
   if (s->res_host) (void)hipHostFree(s->res_host);
   (void)hipGetLastError();
   delete s;
 }
 
-// Queue one minibatch's sampling on `st`; the last kernel leaves (list
-// length, status) in s->res.
-bool queue_sample(lsmgnn_sampler *s, const int64_t *seeds, uint64_t n_seeds, uint64_t batch, int64_t *out,
-                  uint64_t out_cap, hipStream_t st) {
+template <int kW>
+void queue_frontier(lsmgnn_sampler *s, uint32_t fanout, const lsm_smp::Hop &hop, hipStream_t st) {
   using namespace lsm_smp;
-  const unsigned gN = grid_for(s->N, kTile, kMaxGrid);  // frontier tiles: at most N entries
-  const unsigned gc = (unsigned)s->nchunks;
+  const dim3 g((unsigned)s->nchunks);
+  hipLaunchKernelGGL(k_counts<kW>, g, dim3(kBlock), 0, st, s->present, s->off, fanout, s->chunk_sum);
+  if (!s->chunk_first) {
+    hipLaunchKernelGGL((k_frontier<kW, true>), g, dim3(kBlock), 0, st, s->present, s->off, fanout, s->chunk_sum,
+                       s->chunk_first, s->chunk_base, s->frontier, s->node_off, hop, s->ctl);
+  } else if constexpr (kW != kWordsSmall) {
+    hipLaunchKernelGGL(k_chunk_scan, dim3(1), dim3(kBlock), 0, st, s->chunk_sum, (uint32_t)s->nchunks,
+                       s->chunk_first, s->chunk_base, hop, s->ctl);
+    hipLaunchKernelGGL((k_frontier<kW, false>), g, dim3(kBlock), 0, st, s->present, s->off, fanout, s->chunk_sum,
+                       s->chunk_first, s->chunk_base, s->frontier, s->node_off, hop, s->ctl);
+  }
+}
+
+template <int G>
+void queue_draw(lsmgnn_sampler *s, uint64_t nodes, uint32_t fanout, uint64_t key_hop, int64_t *out, uint64_t cap,
+                bool mark, hipStream_t st) {
+  using namespace lsm_smp;
+  hipLaunchKernelGGL(k_draw<G>, dim3(grid_for(nodes, kBlock / G, kMaxGrid)), dim3(kBlock), 0, st, s->frontier, s->off,
+                     s->adj, fanout, key_hop, s->chunk_base, s->chunk_shift, s->node_off, out, cap, s->present,
+                     mark ? 1 : 0, s->ctl);
+}
+
+// Queue one minibatch's sampling on `st`; (list length, status) goes to res
+// (device memory, or pinned memory by its device address).
+bool queue_sample(lsmgnn_sampler *s, const int64_t *seeds, uint64_t n_seeds, uint64_t batch, int64_t *out,
+                  uint64_t out_cap, uint64_t *res, hipStream_t st) {
+  using namespace lsm_smp;
   const uint64_t key_b = derive(derive(s->seed, kLabelSample), batch);
-  hipLaunchKernelGGL(k_init, dim3(1), dim3(64), 0, st, s->ctl, n_seeds);
   if (n_seeds)
     hipLaunchKernelGGL(k_seeds, dim3(grid_for(n_seeds, kBlock, kMaxGrid)), dim3(kBlock), 0, st, seeds, n_seeds, s->N,
                        out, out_cap, s->present, s->ctl);
-  hipLaunchKernelGGL(k_popc, dim3(gc), dim3(kBlock), 0, st, s->present, s->chunk_sums);
-  hipLaunchKernelGGL(k_chunk_scan, dim3(1), dim3(kBlock), 0, st, s->chunk_sums, (uint32_t)s->nchunks, s->ctl);
-  hipLaunchKernelGGL(k_compact, dim3(gc), dim3(kBlock), 0, st, s->present, s->chunk_sums, s->frontier[0]);
   // with a bad seed the frontier is still built (and the map cleared) from the
   // valid ones; the hops run, and the call reports E_RANGE
+  uint64_t nodes = n_seeds < s->N ? n_seeds : s->N;  // bounds the hop's frontier
   for (uint32_t h = 0; h < s->hops; ++h) {
-    uint32_t *cur = s->frontier[h & 1], *nxt = s->frontier[(h + 1) & 1];
-    const int last = h + 1 == s->hops;
-    hipLaunchKernelGGL(k_tiles, dim3(gN), dim3(kBlock), 0, st, cur, s->off, s->fanout[h], s->tile_sum, nxt, s->ctl);
-    hipLaunchKernelGGL(k_top, dim3(1), dim3(kBlock), 0, st, s->tile_sum, s->ctl);
-    hipLaunchKernelGGL(k_draw_wave, dim3(gN), dim3(kBlock), 0, st, cur, s->off, s->adj, s->fanout[h],
-                       derive(key_b, h), s->tile_sum, nxt, out, out_cap, s->present, last ? 0 : 1, s->ctl);
-    if (!last) {
-      hipLaunchKernelGGL(k_popc, dim3(gc), dim3(kBlock), 0, st, s->present, s->chunk_sums);
-      hipLaunchKernelGGL(k_chunk_scan, dim3(1), dim3(kBlock), 0, st, s->chunk_sums, (uint32_t)s->nchunks, s->ctl);
-      hipLaunchKernelGGL(k_compact, dim3(gc), dim3(kBlock), 0, st, s->present, s->chunk_sums, nxt);
-    }
+    const bool last = h + 1 == s->hops;
+    const uint32_t fan = s->fanout[h];
+    const Hop hop{n_seeds, out_cap, last ? res : nullptr, h == 0};
+    if (s->N <= kSmallChunkNodes)
+      queue_frontier<kWordsSmall>(s, fan, hop, st);
+    else
+      queue_frontier<kWordsLarge>(s, fan, hop, st);
+    const uint64_t key_hop = derive(key_b, h);
+    // the fewest lanes that hold a node's draws: with a wave per node, five
+    // draws left 59 of 64 lanes idle
+    if (fan <= 8)
+      queue_draw<8>(s, nodes, fan, key_hop, out, out_cap, !last, st);
+    else if (fan <= 16)
+      queue_draw<16>(s, nodes, fan, key_hop, out, out_cap, !last, st);
+    else if (fan <= 32)
+      queue_draw<32>(s, nodes, fan, key_hop, out, out_cap, !last, st);
+    else
+      queue_draw<64>(s, nodes, fan, key_hop, out, out_cap, !last, st);
+    nodes = fan && nodes > s->N / fan ? s->N : nodes * fan;
   }
-  hipLaunchKernelGGL(k_result, dim3(1), dim3(64), 0, st, s->ctl, out_cap, s->res);
   return hipGetLastError() == hipSuccess;
+}
+
+// The device address of pinned host memory, or NULL for memory that the GPU
+// cannot write.
+uint64_t *device_view(uint64_t *host) {
+  void *p = nullptr;
+  if (hipHostGetDevicePointer(&p, host, 0) == hipSuccess && p) return static_cast<uint64_t *>(p);
+  (void)hipGetLastError();
+  return nullptr;
 }
 
 }  // namespace
@@ -531,15 +617,21 @@ lsmgnn_status lsmgnn_sampler_create(const int64_t *offsets, const uint32_t *adj,
   s->hops = hops;
   s->seed = seed;
   for (uint32_t h = 0; h < hops; ++h) s->fanout[h] = fanout[h];
-  s->nchunks = (N + kChunk - 1) / kChunk;
-  s->max_tiles = (N + kTile - 1) / kTile;
+  s->chunk = (uint64_t)kBlock * 4 * (N <= kSmallChunkNodes ? kWordsSmall : kWordsLarge);
+  s->chunk_shift = (uint32_t)__builtin_ctzll(s->chunk);
+  s->nchunks = (N + s->chunk - 1) / s->chunk;
+  static_assert(kSmallChunkNodes / ((uint64_t)kBlock * 4 * kWordsSmall) <= kFusedSmall,
+                "the small chunks' sums are always few");
   uint32_t *err = nullptr;
-  bool ok = hipMalloc(&s->present, s->nchunks * kChunk) == hipSuccess &&
-            hipMalloc(&s->chunk_sums, s->nchunks * 4) == hipSuccess &&
-            hipMalloc(&s->frontier[0], N * 4) == hipSuccess && hipMalloc(&s->frontier[1], N * 4) == hipSuccess &&
-            hipMalloc(&s->tile_sum, s->max_tiles * 8) == hipSuccess &&
+  bool ok = hipMalloc(&s->present, s->nchunks * s->chunk) == hipSuccess &&
+            hipMalloc(&s->chunk_sum, s->nchunks * 8) == hipSuccess &&
+            hipMalloc(&s->chunk_base, s->nchunks * 8) == hipSuccess &&
+            (N <= kSmallChunkNodes || s->nchunks <= kFusedLarge ||
+             hipMalloc(&s->chunk_first, s->nchunks * 4) == hipSuccess) &&
+            hipMalloc(&s->frontier, N * 4) == hipSuccess && hipMalloc(&s->node_off, N * 4) == hipSuccess &&
             hipMalloc(&s->ctl, sizeof(Ctl)) == hipSuccess && hipMalloc(&s->res, 16) == hipSuccess &&
             hipHostMalloc(&s->res_host, 16, hipHostMallocDefault) == hipSuccess &&
+            hipHostGetDevicePointer(reinterpret_cast<void **>(&s->res_dev), s->res_host, 0) == hipSuccess &&
             hipMalloc(&err, 4) == hipSuccess;
   if (!ok) {
     (void)hipGetLastError();
@@ -550,7 +642,8 @@ lsmgnn_status lsmgnn_sampler_create(const int64_t *offsets, const uint32_t *adj,
   // the byte map starts zero; the graph is checked once so that no later
   // kernel reads outside it
   uint32_t herr = 0;
-  ok = hipMemset(s->present, 0, s->nchunks * kChunk) == hipSuccess && hipMemset(err, 0, 4) == hipSuccess;
+  ok = hipMemset(s->present, 0, s->nchunks * s->chunk) == hipSuccess &&
+       hipMemset(s->ctl, 0, sizeof(Ctl)) == hipSuccess && hipMemset(err, 0, 4) == hipSuccess;
   if (ok) {
     hipLaunchKernelGGL(k_validate, dim3(grid_for(N > E ? N : E, kBlock, 8192)), dim3(kBlock), 0, 0, offsets, adj, N,
                        E, err);
@@ -583,8 +676,7 @@ lsmgnn_status lsmgnn_sample(lsmgnn_sampler *s, const int64_t *seeds, uint64_t n_
   DeviceScope ds(s->device);
   if (!ds.ok) return LSMGNN_E_DEVICE;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (!queue_sample(s, seeds, n_seeds, batch, out, out_cap, st) ||
-      hipMemcpyAsync(s->res_host, s->res, 16, hipMemcpyDeviceToHost, st) != hipSuccess ||
+  if (!queue_sample(s, seeds, n_seeds, batch, out, out_cap, s->res_dev, st) ||
       hipStreamSynchronize(st) != hipSuccess) {
     (void)hipGetLastError();
     return LSMGNN_E_DEVICE;
@@ -599,8 +691,10 @@ lsmgnn_status lsmgnn_sample_async(lsmgnn_sampler *s, const int64_t *seeds, uint6
   DeviceScope ds(s->device);
   if (!ds.ok) return LSMGNN_E_DEVICE;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (!queue_sample(s, seeds, n_seeds, batch, out, out_cap, st) ||
-      hipMemcpyAsync(result_host, s->res, 16, hipMemcpyDeviceToHost, st) != hipSuccess) {
+  // the last frontier writes pinned memory itself; other memory gets a copy
+  uint64_t *res = device_view(result_host);
+  if (!queue_sample(s, seeds, n_seeds, batch, out, out_cap, res ? res : s->res, st) ||
+      (!res && hipMemcpyAsync(result_host, s->res, 16, hipMemcpyDeviceToHost, st) != hipSuccess)) {
     (void)hipGetLastError();
     return LSMGNN_E_DEVICE;
   }

@@ -276,3 +276,45 @@ def test_binding_checks_dtypes_and_takes_the_smallest_capacity():
         assert np.array_equal(outs[t][:40].cpu().numpy(), np.arange(40)), t
     assert (outs[0][40:].cpu().numpy() == -1).all() and (guard.cpu().numpy() == -7).all()
     res.close()
+
+
+@pytest.mark.parametrize("nodes", [1, 1023, 1024, 1025, 4097, 1 << 24, (1 << 24) + 1, 2048 * 16384, 2048 * 16384 + 1])
+def test_frontier_chunks(nodes):
+    """Node counts at the edges of the byte map's chunks, where the chunk size changes, and where the chunks are too many
+    to be added up by each block; low, middle and top nodes hold all the entries."""
+    log(f"case: sampler, {nodes} nodes")
+    rng = np.random.default_rng(nodes)
+    live = np.unique(np.concatenate([np.arange(min(nodes, 200)), rng.integers(0, nodes, 3000),
+                                     np.arange(max(0, nodes - 200), nodes)]))
+    deg = rng.integers(0, 40, live.size)
+    off = np.zeros(nodes + 1, np.int64)
+    off[live + 1] = deg
+    np.cumsum(off, out=off)
+    adj = rng.choice(live, max(1, int(off[-1]))).astype(np.uint32)[: int(off[-1])]
+    g = W.Graph(off, adj, np.zeros(1, np.uint32))
+    seeds = rng.choice(live, 6 * 50)
+    _check_stream(g, seeds, 50, (8, 9, 33), 6, seed=3, label=f"N={nodes}")
+
+
+def test_async_result_words():
+    """The length and status of asynchronous calls queued one after another, into pinned memory (written by the GPU) and
+    into ordinary memory (copied)."""
+    g = W.rmat_graph(1 << 11, 1 << 14, seed=4)
+    ref = _host_lists(g, np.arange(4 * 64), 64, (10, 5, 3), 4, 6)
+    off, adj = _dev_graph(g)
+    smp = lsmgnn.GpuSampler(off, adj, (10, 5, 3), seed=6)
+    seeds = torch.arange(4 * 64, dtype=torch.int64, device="cuda")
+    pinned, plain = lsmgnn.PinnedBuffer(16 * 5), np.zeros((5, 2), np.uint64)
+    for words, ptr in ((pinned.numpy(np.uint64, (5, 2)), pinned.ptr), (plain, plain.ctypes.data)):
+        outs = [torch.zeros(max(r.size for r in ref), dtype=torch.int64, device="cuda") for _ in range(4)]
+        for b in range(4):
+            smp.sample_async(seeds[b * 64:(b + 1) * 64], b, outs[b], ptr + 16 * b)
+        smp.sample_async(torch.tensor([5, 1 << 11], device="cuda"), 0, torch.zeros(9, dtype=torch.int64, device="cuda"),
+                         ptr + 64)
+        torch.cuda.synchronize()
+        for b in range(4):
+            assert words[b].tolist() == [ref[b].size, lsmgnn.OK]
+            assert np.array_equal(outs[b].cpu().numpy()[: ref[b].size], ref[b]), b
+        assert int(words[4, 1]) == lsmgnn.E_RANGE
+    smp.close()
+    pinned.close()
