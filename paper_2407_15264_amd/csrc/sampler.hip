@@ -45,9 +45,9 @@
 // graph at (15, 10, 5), waited for: 72 us against 102; 4096 seeds of a 10 M-node
 // graph at (10, 5, 5), queued: 60 against 83.
 //
-// Typed graphs: the list split by node type (per tile of 256 requests a count
-// per type, one block's scan per type, then a ballot rank per type and wave),
-// each ID replaced by its index within its type.
+// Typed graphs: the list split by node type (per tile of requests a count per
+// type, then each tile adds up the tiles before it and ranks its requests by
+// ballots), each ID replaced by its index within its type.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -358,108 +358,179 @@ __global__ __launch_bounds__(kBlock) void k_draw(const uint32_t *frontier, const
 
 // ------------------------------------------------------------ typed graphs
 // A request list of global IDs split by node type, in request order, each ID
-// replaced by its index within its type.  Tiles of 256 requests: per-tile
-// counts per type, one block's scan of them per type, then each request's
-// rank among its tile's requests of the same type (one ballot per type and
-// wave).  result[t] = length of type t's list; result[T] = status.
+// replaced by its index within its type.  Tiles of kSplitTile requests, four
+// per thread: per-tile counts per type, then each tile's lists start where the
+// tiles before it end (added up by the tile's own block, or with many tiles by
+// one block's scan first), and each request's rank among its tile's requests
+// of its type comes from one ballot per type, wave and row of 64 requests.
+// result[t] = length of type t's list; result[T] = status: LSMGNN_E_RANGE for an
+// invalid ID or type, LSMGNN_E_INVAL when a list is longer than the outputs.
+//
+// Bound by the random lines of the two tables: a request's type is looked up by
+// both kernels, its index by the second (389 K requests over 20 M nodes: 9 and
+// 19 us, at 128 bytes a lookup 5.4 TB/s).  With tiles of 256, one block scanning
+// all of them type by type (14 us) and the result words initialised, finished
+// and copied by launches of their own it took 44 us, now 28.
 constexpr uint32_t kMaxTypes = 16;
+constexpr uint32_t kSplitItems = 4, kSplitTile = kBlock * kSplitItems;
+constexpr uint32_t kSplitFusedMax = 1024;  // at most this many tiles are added up by each block
+constexpr uint32_t kSplitCounts = 144;     // byte offset of the counts in the work memory
+static_assert((kMaxTypes + 1) * 8 <= kSplitCounts && kSplitCounts + (kMaxTypes + 1) * 4 <= 256 + kMaxTypes * 4,
+              "the result words and one tile's counts fit the smallest work memory");
 
 struct TypeOuts {
   int64_t *p[kMaxTypes];
 };
 
+// Counts of tile b at cnt[b * (T + 1)]: per type, then the invalid requests.
 __global__ __launch_bounds__(kBlock) void k_type_count(const int64_t *ids, uint64_t n, uint64_t N,
-                                                       const uint8_t *node_type, uint32_t T, uint32_t *tile_cnt,
-                                                       uint64_t *result) {
-  __shared__ uint32_t cnt[kMaxTypes];
-  const uint64_t ntiles = (n + kBlock - 1) / kBlock;
+                                                       const uint8_t *node_type, uint32_t T, uint32_t *cnt) {
+  __shared__ uint32_t h[kMaxTypes + 1];
+  const uint64_t ntiles = (n + kSplitTile - 1) / kSplitTile;
   for (uint64_t b = blockIdx.x; b < ntiles; b += gridDim.x) {
-    if (threadIdx.x < kMaxTypes) cnt[threadIdx.x] = 0;
+    if (threadIdx.x <= T) h[threadIdx.x] = 0;
     __syncthreads();
-    const uint64_t i = b * kBlock + threadIdx.x;
-    bool bad = false;
-    if (i < n) {
-      const int64_t x = ids[i];
-      if (x < 0 || (uint64_t)x >= N) {
-        bad = true;
-      } else {
-        const uint32_t t = node_type[x];
-        if (t >= T)
-          bad = true;
-        else
-          atomicAdd(&cnt[t], 1u);
+    uint32_t t[kSplitItems];
+#pragma unroll
+    for (uint32_t q = 0; q < kSplitItems; ++q) {
+      const uint64_t i = b * kSplitTile + q * kBlock + threadIdx.x;
+      t[q] = kMaxTypes + 1;  // no request
+      if (i < n) {
+        const int64_t x = ids[i];
+        t[q] = x < 0 || (uint64_t)x >= N ? T : node_type[x];
+        t[q] = t[q] < T ? t[q] : T;
       }
     }
-    if (__ballot(bad) && __lane_id() == 0) atomicOr((unsigned long long *)&result[T], 1ull);
+    // one LDS add per type and wave
+    for (uint32_t k = 0; k <= T; ++k) {
+      uint32_t c = 0;
+#pragma unroll
+      for (uint32_t q = 0; q < kSplitItems; ++q) c += (uint32_t)__popcll(__ballot(t[q] == k));
+      if ((threadIdx.x & 63) == 0 && c) atomicAdd(&h[k], c);
+    }
     __syncthreads();
-    if (threadIdx.x < T) tile_cnt[b * T + threadIdx.x] = cnt[threadIdx.x];
+    if (threadIdx.x <= T) cnt[b * (T + 1) + threadIdx.x] = h[threadIdx.x];
     __syncthreads();
   }
 }
 
-// One block: per type, the exclusive scan of the tile counts (in place) and
-// the type's list length.
-__global__ __launch_bounds__(kBlock) void k_type_scan(uint32_t *tile_cnt, uint64_t ntiles, uint32_t T,
-                                                      uint64_t *result) {
-  for (uint32_t t = 0; t < T; ++t) {
-    uint32_t carry = 0;
+// The result words from the lists' lengths (threads 0..T - 1 hold one each,
+// thread T the invalid requests).
+__device__ __forceinline__ void publish_split(uint32_t T, uint64_t len, uint64_t cap, uint64_t *res) {
+  const uint64_t over = __ballot(threadIdx.x < T && len > cap);  // T < 64: one wave
+  if (threadIdx.x < T) __hip_atomic_store(res + threadIdx.x, len, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (threadIdx.x == T) {
+    const uint64_t st = len ? (uint64_t)LSMGNN_E_RANGE : over ? (uint64_t)LSMGNN_E_INVAL : (uint64_t)LSMGNN_OK;
+    __hip_atomic_store(res + T, st, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+}
+
+// One block, more than kSplitFusedMax tiles: the exclusive scan of the tiles'
+// counts (in place) per type, and the result.
+__global__ __launch_bounds__(kBlock) void k_type_scan(uint32_t *cnt, uint64_t ntiles, uint32_t T, uint64_t cap,
+                                                      uint64_t *res) {
+  __shared__ uint64_t len[kMaxTypes + 1];
+  for (uint32_t t = 0; t <= T; ++t) {
+    uint64_t carry = 0;
     for (uint64_t base = 0; base < ntiles; base += kBlock) {
       const uint64_t i = base + threadIdx.x;
-      const uint32_t v = i < ntiles ? tile_cnt[i * T + t] : 0u;
+      const uint32_t v = i < ntiles ? cnt[i * (T + 1) + t] : 0u;
       uint32_t tot;
       const uint32_t ex = block_exclusive_scan(v, tot);
-      if (i < ntiles) tile_cnt[i * T + t] = carry + ex;
+      if (i < ntiles) cnt[i * (T + 1) + t] = (uint32_t)carry + ex;
       carry += tot;
     }
-    if (threadIdx.x == 0) result[t] = carry;
+    if (threadIdx.x == 0) len[t] = carry;
   }
+  __syncthreads();
+  if (threadIdx.x < 64) publish_split(T, threadIdx.x <= T ? len[threadIdx.x] : 0, cap, res);
 }
 
+template <bool kFused>
 __global__ __launch_bounds__(kBlock) void k_type_scatter(const int64_t *ids, uint64_t n, uint64_t N,
                                                          const uint8_t *node_type, const uint32_t *local, uint32_t T,
-                                                         const uint32_t *tile_off, TypeOuts outs, uint64_t cap) {
-  __shared__ uint32_t wcnt[kBlock / 64][kMaxTypes];
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;  // lanes below this one
-  const uint64_t ntiles = (n + kBlock - 1) / kBlock;
+                                                         const uint32_t *cnt, TypeOuts outs, uint64_t cap,
+                                                         uint64_t *res) {
+  constexpr uint32_t kRows = kSplitItems * (kBlock / 64);  // rows of 64 requests
+  __shared__ uint32_t rows[kRows][kMaxTypes];
+  __shared__ uint32_t start[kMaxTypes + 1], all[kMaxTypes + 1];  // the tiles' before this one, and all of them
+  const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
+  const uint64_t lt = (1ull << lane) - 1ull;  // lanes below this one
+  const uint64_t ntiles = (n + kSplitTile - 1) / kSplitTile;
   for (uint64_t b = blockIdx.x; b < ntiles; b += gridDim.x) {
-    const uint64_t i = b * kBlock + threadIdx.x;
-    uint32_t t = kMaxTypes, loc = 0;  // kMaxTypes: no request, or an invalid one
-    if (i < n) {
-      const int64_t x = ids[i];
-      if (x >= 0 && (uint64_t)x < N && node_type[x] < T) {
-        t = node_type[x];
-        loc = local[x];
+    uint32_t t[kSplitItems], loc[kSplitItems], rank[kSplitItems];
+#pragma unroll
+    for (uint32_t q = 0; q < kSplitItems; ++q) {
+      const uint64_t i = b * kSplitTile + q * kBlock + threadIdx.x;
+      t[q] = kMaxTypes;  // no request, or an invalid one
+      loc[q] = 0;
+      if (i < n) {
+        const int64_t x = ids[i];
+        if (x >= 0 && (uint64_t)x < N) {
+          const uint32_t y = node_type[x];
+          loc[q] = local[x];
+          t[q] = y < T ? y : kMaxTypes;
+        }
       }
     }
-    uint32_t rank = 0;
-    for (uint32_t k = 0; k < T; ++k) {
-      const uint64_t m = __ballot(t == k);
-      if (t == k) rank = (uint32_t)__popcll(m & lt);
-      if (lane == 0) wcnt[wid][k] = (uint32_t)__popcll(m);
+    if constexpr (kFused) {
+      // thread first * W + word adds up one word of every (kBlock / W)-th tile,
+      // eight of them in flight beside the lookups above
+      if (threadIdx.x <= T) start[threadIdx.x] = all[threadIdx.x] = 0;
+      const uint32_t W = T + 1, per = kBlock / W, word = threadIdx.x % W, first = threadIdx.x / W;
+      const uint32_t tiles = first < per ? (uint32_t)ntiles : 0u;
+      uint32_t before = 0, sum = 0;
+      for (uint32_t j = first; j < tiles; j += 8 * per) {
+        uint32_t c[8];
+#pragma unroll
+        for (uint32_t q = 0; q < 8; ++q) c[q] = j + q * per < tiles ? cnt[(j + q * per) * W + word] : 0u;
+#pragma unroll
+        for (uint32_t q = 0; q < 8; ++q) {
+          sum += c[q];
+          before += j + q * per < b ? c[q] : 0u;
+        }
+      }
+      __syncthreads();
+      if (sum) atomicAdd(&all[word], sum);
+      if (before) atomicAdd(&start[word], before);
+      __syncthreads();
+      if (b == 0 && threadIdx.x < 64) publish_split(T, threadIdx.x <= T ? all[threadIdx.x] : 0, cap, res);
+    } else {
+      if (threadIdx.x < T) start[threadIdx.x] = cnt[b * (T + 1) + threadIdx.x];
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < kSplitItems; ++q) {
+      rank[q] = 0;
+      for (uint32_t k = 0; k < T; ++k) {
+        const uint64_t m = __ballot(t[q] == k);
+        if (t[q] == k) rank[q] = (uint32_t)__popcll(m & lt);
+        if (lane == 0) rows[q * (kBlock / 64) + wid][k] = (uint32_t)__popcll(m);
+      }
     }
     __syncthreads();
-    if (t < T) {
-      uint64_t off = tile_off[b * T + t] + rank;
-      for (int w = 0; w < wid; ++w) off += wcnt[w][t];
-      if (off < cap) outs.p[t][off] = (int64_t)loc;
+    // rows in request order (row q * 4 + wave): their exclusive sums
+    if (threadIdx.x < T) {
+      uint32_t run = start[threadIdx.x];
+      for (uint32_t r = 0; r < kRows; ++r) {
+        const uint32_t c = rows[r][threadIdx.x];
+        rows[r][threadIdx.x] = run;
+        run += c;
+      }
     }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t q = 0; q < kSplitItems; ++q)
+      if (t[q] < T) {
+        const uint64_t p = (uint64_t)rows[q * (kBlock / 64) + wid][t[q]] + rank[q];
+        if (p < cap) outs.p[t[q]][p] = (int64_t)loc[q];
+      }
     __syncthreads();
   }
 }
 
-__global__ void k_type_init(uint64_t *result, uint32_t T) {
-  if (threadIdx.x <= T) result[threadIdx.x] = 0;
-}
-
-// status word: an invalid ID or type (set by the count kernel as 1) becomes
-// E_RANGE; otherwise E_INVAL when a list is longer than the outputs, else OK
-__global__ void k_type_status(uint64_t *result, uint32_t T, uint64_t cap) {
-  if (threadIdx.x == 0) {
-    bool over = false;
-    for (uint32_t t = 0; t < T; ++t) over |= result[t] > cap;
-    result[T] = result[T] ? (uint64_t)LSMGNN_E_RANGE : over ? (uint64_t)LSMGNN_E_INVAL : (uint64_t)LSMGNN_OK;
-  }
+// No requests: every list is empty.
+__global__ void k_type_none(uint64_t *res, uint32_t T) {
+  if (threadIdx.x < 64) publish_split(T, 0, 0, res);
 }
 
 static unsigned grid_for(uint64_t work, uint64_t per_block, unsigned cap) {
@@ -728,22 +799,31 @@ lsmgnn_status queue_split(const int64_t *ids, uint64_t n, uint64_t num_nodes, co
   using namespace lsm_smp;
   TypeOuts to{};
   for (uint32_t t = 0; t < num_types; ++t) to.p[t] = outs[t];
-  // work: the device result (num_types lengths + status, 8 B each), then the tile counts
-  uint64_t *res = static_cast<uint64_t *>(work);
-  uint32_t *tile_cnt = reinterpret_cast<uint32_t *>(static_cast<uint8_t *>(work) + 256);
-  const uint64_t ntiles = (n + kBlock - 1) / kBlock;
+  // work: the device result (num_types lengths + status, 8 B each, used when
+  // the result memory is not pinned), then the tile counts: m tiles of
+  // num_types + 1 words.  There are 112 bytes and, since n > 1024 (m - 1), at
+  // least 4 m - 3 times num_types words for them.
+  uint64_t *res = device_view(result_host), *dev = static_cast<uint64_t *>(work);
+  const bool copy = !res;
+  if (copy) res = dev;
+  uint32_t *cnt = reinterpret_cast<uint32_t *>(static_cast<uint8_t *>(work) + kSplitCounts);
+  const uint64_t ntiles = (n + kSplitTile - 1) / kSplitTile;
   const unsigned g = grid_for(ntiles, 1, kMaxGrid);
-  hipLaunchKernelGGL(k_type_init, dim3(1), dim3(64), 0, st, res, num_types);
   if (n) {
-    hipLaunchKernelGGL(k_type_count, dim3(g), dim3(kBlock), 0, st, ids, n, num_nodes, node_type, num_types, tile_cnt,
-                       res);
-    hipLaunchKernelGGL(k_type_scan, dim3(1), dim3(kBlock), 0, st, tile_cnt, ntiles, num_types, res);
-    hipLaunchKernelGGL(k_type_scatter, dim3(g), dim3(kBlock), 0, st, ids, n, num_nodes, node_type, local, num_types,
-                       tile_cnt, to, out_cap);
+    hipLaunchKernelGGL(k_type_count, dim3(g), dim3(kBlock), 0, st, ids, n, num_nodes, node_type, num_types, cnt);
+    if (ntiles <= kSplitFusedMax) {
+      hipLaunchKernelGGL(k_type_scatter<true>, dim3(g), dim3(kBlock), 0, st, ids, n, num_nodes, node_type, local,
+                         num_types, cnt, to, out_cap, res);
+    } else {
+      hipLaunchKernelGGL(k_type_scan, dim3(1), dim3(kBlock), 0, st, cnt, ntiles, num_types, out_cap, res);
+      hipLaunchKernelGGL(k_type_scatter<false>, dim3(g), dim3(kBlock), 0, st, ids, n, num_nodes, node_type, local,
+                         num_types, cnt, to, out_cap, res);
+    }
+  } else {
+    hipLaunchKernelGGL(k_type_none, dim3(1), dim3(64), 0, st, res, num_types);
   }
-  hipLaunchKernelGGL(k_type_status, dim3(1), dim3(64), 0, st, res, num_types, out_cap);
   if (hipGetLastError() != hipSuccess ||
-      hipMemcpyAsync(result_host, res, (num_types + 1) * 8, hipMemcpyDeviceToHost, st) != hipSuccess) {
+      (copy && hipMemcpyAsync(result_host, res, (num_types + 1) * 8, hipMemcpyDeviceToHost, st) != hipSuccess)) {
     (void)hipGetLastError();
     return LSMGNN_E_DEVICE;
   }

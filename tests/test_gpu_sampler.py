@@ -318,3 +318,32 @@ def test_async_result_words():
         assert int(words[4, 1]) == lsmgnn.E_RANGE
     smp.close()
     pinned.close()
+
+
+@pytest.mark.parametrize("T", [1, 2, 15, 16])
+@pytest.mark.parametrize("n", [1, 64, 255, 1023, 1024, 1025, 4097, 1024 * 1024, 1024 * 1024 + 1])
+def test_split_tiles(n, T):
+    """Request counts at the edges of the split's tiles and where the tiles are too many to be added up by each block,
+    with work memory of exactly the size asked for inside a guarded array."""
+    log(f"case: split n={n} T={T}")
+    rng = np.random.default_rng(n + T)
+    N = 5000
+    node_type = rng.integers(0, T, N).astype(np.uint8)
+    local = rng.permutation(N).astype(np.int32)
+    ids = rng.integers(0, N, n)
+    size = lsmgnn.split_work_bytes(n, T)
+    guarded = torch.full((size + 512,), 0xA5, dtype=torch.uint8, device="cuda")
+    outs = [torch.full((n,), -1, dtype=torch.int64, device="cuda") for _ in range(T)]
+    plain, pinned = np.zeros(T + 1, np.uint64), lsmgnn.PinnedBuffer(8 * (T + 1))
+    for words, ptr in ((pinned.numpy(np.uint64, (T + 1,)), pinned.ptr), (plain, plain.ctypes.data)):
+        lsmgnn.split_by_type_async(torch.as_tensor(ids).cuda(), torch.as_tensor(node_type).cuda(),
+                                   torch.as_tensor(local).cuda(), outs, guarded[256:256 + size], ptr)
+        torch.cuda.synchronize()
+        assert int(words[T]) == lsmgnn.OK
+        for t in range(T):
+            want = local[ids[node_type[ids] == t]].astype(np.int64)
+            assert int(words[t]) == want.size
+            got = outs[t].cpu().numpy()
+            assert np.array_equal(got[: want.size], want) and (got[want.size:] == -1).all(), t
+    assert bool((guarded[:256] == 0xA5).all()) and bool((guarded[256 + size:] == 0xA5).all())
+    pinned.close()
