@@ -283,8 +283,8 @@ void launch_finish(Counters *cn, Counters *host, const uint32_t *stat_part, cons
 // largest N here, 100 MB per pass) against 428-437 with the bitmap.
 //
 // Validate and mark.  Out-of-range IDs set Counters::err; valid ones are still
-// marked, and the compaction kernel then clears the map instead of compacting
-// it, so a rejected batch leaves no trace.  The list announced with the gather
+// marked, and the compaction kernel then clears the map without compacting it,
+// so a rejected batch leaves no trace.  The list announced with the gather
 // (if any) is validated here too; its bits are set only after the gather has
 // been accepted.  The same kernel clears the window bit of the minibatch being
 // gathered: that list is never consulted again, whether or not this call
@@ -382,10 +382,13 @@ __global__ __launch_bounds__(kBlock) void k_compact(uint8_t *present, const uint
   load_words(present, w);
   const size_t b0 = ((size_t)blockIdx.x * kBlock + threadIdx.x) * 4 * kW;  // first byte of this thread
   const uint32_t err = cn->err;
-  if (err) {  // rejected batch: undo the marks
+  // the marks are this block's to read and clear, whether or not the batch is
+  // rejected (cleared later, by a store per unique ID, they were as many
+  // scattered lines)
 #pragma unroll
-    for (int k = 0; k < kW; ++k)
-      if (w[k]) reinterpret_cast<uint32_t *>(present + b0)[k] = 0;
+  for (int k = 0; k < kW; ++k)
+    if (w[k]) reinterpret_cast<uint32_t *>(present + b0)[k] = 0;
+  if (err) {
     if (kFused && blockIdx.x == 0 && threadIdx.x == 0) {
       *gate = gate_with(err, 0);
       publish_dedup(dd, tag, err, 0);
@@ -523,7 +526,7 @@ __device__ __forceinline__ void block_counts(const uint32_t (&v)[kN], uint32_t *
 //
 // A set none of whose IDs is missing changes nothing in this gather, so its
 // IDs' outcomes are settled by this probe alone; the others are marked for the
-// walk (set_dirty holds 1 + the gather index).  Where nearly every row is
+// walk (SetBatch::dirty holds 1 + the gather index).  Where nearly every row is
 // resident this leaves nothing to group: 365 us per gather against 409 with
 // every touched set walked (900 K requests, 235 K unique 2 KiB rows, pipelined);
 // where nearly every set misses it costs nothing measurable.
@@ -543,7 +546,7 @@ __device__ __forceinline__ void probe(const DevState &d, const Scratch &sc, uint
       const uint32_t s = set_index(x, d.S);
       const u32x4 *tp = reinterpret_cast<const u32x4 *>(d.sets[s].tag);
       const u32x4 a = tp[0], b = tp[1];
-      sc.arrival[u] = atomicAdd(&d.set_count[s], 1u);
+      sc.arrival[u] = atomicAdd(&d.batch[s].count, 1u);
       sc.uset[u] = s;
       uint32_t m = 0;  // the ways that hold x
 #pragma unroll
@@ -551,7 +554,7 @@ __device__ __forceinline__ void probe(const DevState &d, const Scratch &sc, uint
       if (m) {
         sc.slot[u] = s * kWays + (uint32_t)__builtin_ctz(m);
       } else {
-        d.set_dirty[s] = (uint32_t)t + 1u;
+        d.batch[s].dirty = (uint32_t)t + 1u;
         bool entry = false;
         if (d.V) {
           const uint64_t vp = d.vpos[x];
@@ -598,10 +601,11 @@ __device__ __forceinline__ void seg_alloc(const DevState &d, const Scratch &sc, 
     bool walk = false;
     if (u < U && sc.arrival[u] == 0) {
       s = sc.uset[u];
-      k = d.set_count[s];
-      d.set_count[s] = 0;
-      walk = d.set_dirty[s] == t + 1u;
-      if (!walk) d.set_off[s] = kSettled;
+      const u32x4 v = *reinterpret_cast<const u32x4 *>(d.batch + s);  // count, dirty
+      k = v.x;
+      d.batch[s].count = 0;
+      walk = v.y == t + 1u;
+      if (!walk) d.batch[s].off = kSettled;
     }
     const bool small = walk && k <= kSmallSet;
     uint64_t tot;  // segment entries below 2^40, small sets above
@@ -613,7 +617,7 @@ __device__ __forceinline__ void seg_alloc(const DevState &d, const Scratch &sc, 
     __syncthreads();
     if (walk) {
       const WorkSet e{s, boff + (uint32_t)ex, k};
-      d.set_off[s] = e.off;
+      d.batch[s].off = e.off;
       if (small)
         sc.work[bwork + (uint32_t)(ex >> 40)] = e;
       else if (k <= kMidSet)
@@ -631,17 +635,15 @@ __global__ __launch_bounds__(kBlock) void k_seg_alloc(const DevState d, Scratch 
 }
 
 // Per unique ID: the node's unique index (read by the inverse index), the
-// dedup map cleared behind the compaction, the per-ID state reset; then a hit
-// for an ID of a settled set, else its entry in the set's segment, in arrival
+// per-ID state reset; then a hit for an ID of a settled set, else its entry in the set's segment, in arrival
 // order.
 __device__ __forceinline__ void place(const DevState &d, const Scratch &sc, const Counters *cn) {
   const uint32_t U = cn->n_unique;
   uint32_t c_hit = 0;
   for (uint32_t u = blockIdx.x * kBlock + threadIdx.x; u < U; u += gridDim.x * kBlock) {
     const uint32_t x = sc.uniq[u];
-    const uint32_t off = d.set_off[sc.uset[u]];
+    const uint32_t off = d.batch[sc.uset[u]].off;
     d.uidx[x] = u;
-    d.present[x] = 0;
     sc.flags[u] = 0;
     sc.dead[u] = 0;
     sc.fill_dst[u] = 0;

@@ -21,7 +21,7 @@ constexpr int kMaxQueues = 32;       // victim-queue slots: L + 1 <= 32
 // sets by their unique IDs in a batch: up to kSmallSet walked and ordered by 8
 // lanes, up to kMidSet ordered by a wave, larger ones sorted by a block
 constexpr uint32_t kSmallSet = 64, kMidSet = 512;
-constexpr uint32_t kSettled = 0xffffffffu;  // set_off of a set that needs no walk
+constexpr uint32_t kSettled = 0xffffffffu;  // SetBatch::off of a set that needs no walk
 
 // dynamic classes of a resident line while a gather runs
 enum : uint32_t { kClsNone = 0, kClsFar = 1, kClsRecent = 2, kClsNear = 3 };
@@ -50,6 +50,15 @@ struct alignas(128) SetRec {
   uint32_t ins[kWays];
   uint32_t rr_inv;
   uint32_t pad[kWays - 1];
+};
+
+// A set's part in the current batch: one line's access where three arrays would
+// take three.
+struct alignas(16) SetBatch {
+  uint32_t count;  // unique IDs of the batch
+  uint32_t dirty;  // 1 + index of the last gather that missed in the set
+  uint32_t off;    // segment of the set's IDs, or kSettled
+  uint32_t pad;
 };
 
 // victim-buffer forms (values of lsmgnn_config.victim_mode)
@@ -197,9 +206,7 @@ struct DevState {
   const uint8_t *store;  // [N][R] pinned host, device-visible address
   uint8_t *present;      // [nchunks chunks] dedup byte map (all zero between calls)
   uint32_t *chunk_sums;  // [nchunks]
-  uint32_t *set_count;   // [S] (all zero between calls)
-  uint32_t *set_dirty;   // [S] 1 + index of the last gather that missed in the set
-  uint32_t *set_off;     // [S] segment of the set's IDs in the current batch, or kSettled
+  SetBatch *batch;       // [S] (counts all zero between calls)
   uint32_t *uidx;        // [N] unique index of the node in the current batch
                          //     (meaningful only where uniq[uidx[x]] == x)
   uint64_t *tail;        // [2] ring entries ever enqueued (the FIFO tail), and

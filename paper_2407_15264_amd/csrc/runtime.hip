@@ -1095,7 +1095,7 @@ lsmgnn_status lsmgnn_cache_create(const lsmgnn_config *cfg, lsmgnn_cache **out) 
             dev_alloc(c, &d.mask, N) &&
             dev_alloc(c, &d.stat, N) && dev_alloc(c, &d.present, map_bytes) &&
             dev_alloc(c, &d.chunk_sums, d.nchunks) &&
-            dev_alloc(c, &d.set_count, S) && dev_alloc(c, &d.set_dirty, S) && dev_alloc(c, &d.set_off, S) && dev_alloc(c, &d.uidx, N) &&
+            dev_alloc(c, &d.batch, S) && dev_alloc(c, &d.uidx, N) &&
             dev_alloc(c, &d.tail, 2) &&
             (V == 0 || (dev_alloc(c, &d.vpos, N) && dev_alloc(c, &d.ring_tag, V))) &&
             (d.U == 1 || dev_alloc(c, &d.lreuse, S * lsm::kWays)) &&
@@ -1166,7 +1166,7 @@ lsmgnn_status lsmgnn_cache_create(const lsmgnn_config *cfg, lsmgnn_cache **out) 
   // initial state: all ways empty, nothing announced, ring empty, counters zero
   ok = ok && hipMemset(d.sets, 0xff, S * sizeof(lsm::SetRec)) == hipSuccess &&
        hipMemset(d.mask, 0, N * 4) == hipSuccess && hipMemset(d.present, 0, map_bytes) == hipSuccess &&
-       hipMemset(d.set_count, 0, S * 4) == hipSuccess && hipMemset(d.set_dirty, 0, S * 4) == hipSuccess && hipMemset(d.tail, 0, 16) == hipSuccess &&
+       hipMemset(d.batch, 0, S * sizeof(lsm::SetBatch)) == hipSuccess && hipMemset(d.tail, 0, 16) == hipSuccess &&
        hipMemset(c->cn, 0, sizeof(Counters)) == hipSuccess &&
        hipMemcpy(d.stat, cfg->static_score, N * 4, hipMemcpyHostToDevice) == hipSuccess &&
        (V == 0 || (hipMemset(d.vpos, 0, N * 8) == hipSuccess && hipMemset(d.ring_tag, 0xff, V * 4) == hipSuccess)) &&
