@@ -185,7 +185,7 @@ typedef struct {
 } lsmgnn_profile;
 
 /* Create a cache on cfg->device.  Allocates the HBM cache (S*8 rows), its
-   metadata, per-node arrays (about 21 bytes per node), scratch and staging
+   metadata, per-node arrays (about 25 bytes per node), scratch and staging
    rows sized for max_batch, and the pinned victim ring (V rows).  On
    failure *out is NULL and nothing stays allocated. */
 lsmgnn_status lsmgnn_cache_create(const lsmgnn_config *cfg, lsmgnn_cache **out);

@@ -154,20 +154,32 @@ static inline unsigned grid_for(uint64_t work, uint64_t per_block, unsigned cap)
 // (they start zeroed at create).
 //
 // With an announcement (ann.ids != NULL) the launch has more blocks, which all
-// also set the announced minibatch's bit for each of its IDs and record its
-// list, unless the gather's gate holds an error: the announced bits are first
-// read by the next gather's set walk.  Only that bit of a node's window word
-// changes in this kernel (duplicates write the same value), so a plain
-// read-modify-write is exact.
+// also set the announced minibatch's bit for each of its IDs, unless the
+// gather's gate holds an error: the announced bits are first read by the next
+// gather's set walk.  Only that bit of a node's window changes in this kernel
+// (duplicates write the same value), so a plain read-modify-write is exact.
+//
+// A node's window word holds the gather index it was last written for (upper
+// half) and one bit per announced minibatch after that one: bits that are
+// behind by now fall out when the word is read, so no pass clears a served
+// minibatch's bits, and no copy of the announced lists is kept for it: with such
+// a pass (a random read-modify-write per request) and the copy, four gathers
+// of 900 K requests took 1133 us beside their row copies, now 1063.
+__device__ __forceinline__ uint32_t window_bits(uint64_t w, uint32_t now) {
+  const uint32_t behind = now - (uint32_t)(w >> 32);
+  return behind < 32u ? (uint32_t)w >> behind : 0u;  // bit i: minibatch now + 1 + i
+}
+
+__device__ __forceinline__ void window_set(uint64_t *win, uint64_t x, uint32_t now, uint32_t bit) {
+  const uint64_t w = win[x];
+  const uint64_t v = (uint64_t)now << 32 | window_bits(w, now) | 1u << bit;
+  if (v != w) win[x] = v;
+}
+
 __device__ __forceinline__ void announce(const AnnounceArgs &a) {
   if (a.gate->err) return;
-  const uint32_t b = 1u << a.bit;
-  for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < a.n; i += gridDim.x * kBlock) {
-    const int64_t x = a.ids[i];
-    a.slot_ids[i] = x;
-    const uint32_t m = a.mask[x];
-    if (!(m & b)) a.mask[x] = m | b;
-  }
+  for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < a.n; i += gridDim.x * kBlock)
+    window_set(a.win, (uint64_t)a.ids[i], a.now, a.bit);
 }
 
 __device__ __forceinline__ void finish(Counters *cn, Counters *host, const uint32_t *part, const StatGrids &grids,
@@ -286,13 +298,9 @@ void launch_finish(Counters *cn, Counters *host, const uint32_t *stat_part, cons
 // marked, and the compaction kernel then clears the map without compacting it,
 // so a rejected batch leaves no trace.  The list announced with the gather
 // (if any) is validated here too; its bits are set only after the gather has
-// been accepted.  The same kernel clears the window bit of the minibatch being
-// gathered: that list is never consulted again, whether or not this call
-// succeeds.  Only that bit of a node's window word changes in this kernel, so a
-// plain read-modify-write is exact.
+// been accepted.
 __global__ void k_mark(const int64_t *ids, uint32_t n, const int64_t *ann_ids, uint32_t ann_n, uint64_t N,
-                       uint8_t *present, const int64_t *clear_ids, uint32_t clear_n, uint32_t clear_bit,
-                       uint32_t *mask, Counters *cn) {
+                       uint8_t *present, Counters *cn) {
   bool bad = false;
   for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
     const int64_t x = ids[i];
@@ -307,12 +315,6 @@ __global__ void k_mark(const int64_t *ids, uint32_t n, const int64_t *ann_ids, u
     bad |= x < 0 || (uint64_t)x >= N;
   }
   if (__ballot(bad) && __lane_id() == 0) atomicOr(&cn->err, 1u);
-  const uint32_t cb = 1u << clear_bit;
-  for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < clear_n; i += gridDim.x * kBlock) {
-    const int64_t x = clear_ids[i];
-    const uint32_t m = mask[x];
-    if (m & cb) mask[x] = m & ~cb;
-  }
 }
 
 // Each thread owns kW consecutive words of the map (kW / 4 128-bit loads);
@@ -449,13 +451,12 @@ static void launch_compaction(const DevState &d, const Scratch &sc, int64_t *uni
 }
 
 void launch_dedup(const DevState &d, const int64_t *ids, uint64_t n, const int64_t *ann_ids, uint64_t ann_n,
-                  const int64_t *clear_ids, uint64_t clear_n, uint32_t clear_bit, Scratch &sc, int64_t *unique_out,
+                  Scratch &sc, int64_t *unique_out,
                   Counters *cn, DedupResult *dd, uint32_t tag, hipStream_t s) {
-  uint64_t work = n > clear_n ? n : clear_n;
-  work = work > ann_n ? work : ann_n;
+  const uint64_t work = n > ann_n ? n : ann_n;
   const unsigned g = grid_for(work, kBlock, kMaxGrid);
   hipLaunchKernelGGL(k_mark, dim3(g), dim3(kBlock), 0, s, ids, (uint32_t)n, ann_ids, (uint32_t)ann_n, d.N,
-                     d.present, clear_ids, (uint32_t)clear_n, clear_bit, d.mask, cn);
+                     d.present, cn);
   if (d.N <= kSmallChunkNodes)
     launch_compaction<kWordsSmall>(d, sc, unique_out, cn, dd, tag, s);
   else
@@ -671,19 +672,18 @@ void launch_group_by_set(const DevState &d, uint64_t n, uint32_t t, Scratch &sc,
 }
 
 // ---------------------------------------------------------------- set walk
-// Class of a resident line from its announced-batch bits: bit (j mod 32) is
-// set while minibatch j is announced and not yet served.  The next use after
-// gather t is the lowest set bit after rotating bit (t+1) to position 0.
-__device__ __forceinline__ uint32_t class_from_bits(uint32_t m, uint32_t t, uint32_t L, uint32_t T) {
-  const uint32_t rel = __builtin_amdgcn_alignbit(m, m, (t + 1u) & 31u) & ((1u << L) - 1u);
+// Class of a resident line from its window bits: bit i is set while minibatch
+// t + 1 + i is announced and not yet served.
+__device__ __forceinline__ uint32_t class_from_bits(uint32_t m, uint32_t L, uint32_t T) {
+  const uint32_t rel = m & ((1u << L) - 1u);
   if (rel == 0) return kClsNone;
   return (uint32_t)__builtin_ctz(rel) + 1u <= T ? kClsNear : kClsFar;
 }
 
 // Distance from gather t to the line's next announced use (1..L), or 0 when
 // none of the next L minibatches names it.
-__device__ __forceinline__ uint32_t dist_from_bits(uint32_t m, uint32_t t, uint32_t L) {
-  const uint32_t rel = __builtin_amdgcn_alignbit(m, m, (t + 1u) & 31u) & ((1u << L) - 1u);
+__device__ __forceinline__ uint32_t dist_from_bits(uint32_t m, uint32_t L) {
+  const uint32_t rel = m & ((1u << L) - 1u);
   return rel ? (uint32_t)__builtin_ctz(rel) + 1u : 0u;
 }
 
@@ -698,7 +698,7 @@ __global__ __launch_bounds__(kBlock) void k_refresh(const DevState d, uint32_t t
     const uint32_t tag = d.sets[i / kWays].tag[i % kWays];
     uint32_t r = 0;
     if (tag != kEmpty) {
-      const uint32_t dist = dist_from_bits(d.mask[tag], t, d.L);
+      const uint32_t dist = dist_from_bits(window_bits(d.win[tag], t), d.L);
       r = dist ? t + dist + 1u : 0u;
     }
     d.lreuse[i] = r;
@@ -950,9 +950,9 @@ __device__ __forceinline__ void walk_set(const DevState &d, const Scratch &sc, u
         if (d.U > 1) {  // from the information recorded at the last update
           class_from_record(d.lreuse[(uint64_t)s * kWays + w], ins, t, t - t % d.U, d.T, cls, dist);
         } else {        // exact: from its announced-use bits
-          const uint32_t m = d.mask[tag];
-          cls = (ins == t) ? kClsRecent : class_from_bits(m, t, d.L, d.T);
-          if (P == kPolicyDynamic || d.qmode) dist = dist_from_bits(m, t, d.L);
+          const uint32_t m = window_bits(d.win[tag], t);
+          cls = (ins == t) ? kClsRecent : class_from_bits(m, d.L, d.T);
+          if (P == kPolicyDynamic || d.qmode) dist = dist_from_bits(m, d.L);
         }
         lvl = level_of(cls, ring_on);
         known = true;
@@ -1598,7 +1598,7 @@ template <int P>
 __global__ __launch_bounds__(kBlock) void k_tiny(const DevState d, Scratch sc, TinyArgs a, Counters *cn) {
   __shared__ uint64_t key[kTinyRequests];
   const uint32_t n = a.n;
-  // validate; clear the served minibatch's window bit
+  // validate
   bool bad = false;
   for (uint32_t i = threadIdx.x; i < n; i += kBlock) {
     const int64_t x = a.ids[i];
@@ -1608,12 +1608,6 @@ __global__ __launch_bounds__(kBlock) void k_tiny(const DevState d, Scratch sc, T
   for (uint32_t i = threadIdx.x; i < a.ann_n; i += kBlock) {
     const int64_t x = a.ann_ids[i];
     bad |= x < 0 || (uint64_t)x >= d.N;
-  }
-  const uint32_t cb = 1u << a.clear_bit;
-  for (uint32_t i = threadIdx.x; i < a.clear_n; i += kBlock) {
-    const int64_t x = a.clear_ids[i];
-    const uint32_t m = d.mask[x];
-    if (m & cb) d.mask[x] = m & ~cb;
   }
   if (__syncthreads_or(bad)) {
     if (threadIdx.x == 0) {
@@ -2023,58 +2017,47 @@ void launch_copy_plain(const void *src, void *dst, uint64_t bytes, bool device_t
 }
 
 // ------------------------------------------------------------------ window
-// Announce: validate the IDs and, when the list is recorded, copy it into its
-// window slot and set the minibatch's bit for every ID.  Only that bit of a
-// node's window word changes in this kernel (duplicates write the same value),
-// so a plain read-modify-write is exact.
-__global__ void k_window_set(const int64_t *ids, uint32_t n, uint64_t N, uint32_t bit, uint32_t *mask,
-                             int64_t *slot_ids, int record, uint32_t *err) {
+// Announce: validate the IDs and, when the list is recorded, set the
+// minibatch's bit for every ID (see window_bits).  Only that bit of a node's
+// window changes in this kernel (duplicates write the same value), so a plain
+// read-modify-write is exact.
+__global__ void k_window_set(const int64_t *ids, uint32_t n, uint64_t N, uint32_t now, uint32_t bit, uint64_t *win,
+                             int record, uint32_t *err) {
   bool bad = false;
-  const uint32_t b = 1u << bit;
   for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
     const int64_t x = ids[i];
-    if (x < 0 || (uint64_t)x >= N) {
+    if (x < 0 || (uint64_t)x >= N)
       bad = true;
-    } else if (record) {
-      slot_ids[i] = x;
-      const uint32_t m = mask[x];
-      if (!(m & b)) mask[x] = m | b;
-    }
+    else if (record)
+      window_set(win, (uint64_t)x, now, bit);
   }
   if (__ballot(bad) && __lane_id() == 0)  // every writer stores the same value
     __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // After a rejected announcement (the host launches it only then): clear the
-// bit again (it was clear before, since the minibatch that last used this bit
-// position has been gathered).
-__global__ void k_window_rollback(const int64_t *ids, uint32_t n, uint64_t N, uint32_t bit, uint32_t *mask) {
+// bit again (it was clear before: a minibatch is announced once).
+__global__ void k_window_rollback(const int64_t *ids, uint32_t n, uint64_t N, uint32_t now, uint32_t bit,
+                                  uint64_t *win) {
   for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
     const int64_t x = ids[i];
-    if (x >= 0 && (uint64_t)x < N) {
-      const uint32_t m = mask[x];
-      if (m & (1u << bit)) mask[x] = m & ~(1u << bit);
-    }
+    if (x >= 0 && (uint64_t)x < N) win[x] = (uint64_t)now << 32 | (window_bits(win[x], now) & ~(1u << bit));
   }
 }
 
-void launch_window_set(const int64_t *ids, uint64_t n, uint64_t N, uint32_t bit, uint32_t *mask, int64_t *slot_ids,
+void launch_window_set(const int64_t *ids, uint64_t n, uint64_t N, uint32_t now, uint32_t bit, uint64_t *win,
                        bool record, uint32_t *err, hipStream_t s) {
   const unsigned g = grid_for(n, kBlock, kMaxGrid);
-  hipLaunchKernelGGL(k_window_set, dim3(g), dim3(kBlock), 0, s, ids, (uint32_t)n, N, bit, mask, slot_ids,
-                     record ? 1 : 0, err);
+  hipLaunchKernelGGL(k_window_set, dim3(g), dim3(kBlock), 0, s, ids, (uint32_t)n, N, now, bit, win, record ? 1 : 0,
+                     err);
 }
 
-void launch_window_rollback(const int64_t *ids, uint64_t n, uint64_t N, uint32_t bit, uint32_t *mask,
+void launch_window_rollback(const int64_t *ids, uint64_t n, uint64_t N, uint32_t now, uint32_t bit, uint64_t *win,
                             hipStream_t s) {
   const unsigned g = grid_for(n, kBlock, kMaxGrid);
-  hipLaunchKernelGGL(k_window_rollback, dim3(g), dim3(kBlock), 0, s, ids, (uint32_t)n, N, bit, mask);
+  hipLaunchKernelGGL(k_window_rollback, dim3(g), dim3(kBlock), 0, s, ids, (uint32_t)n, N, now, bit, win);
 }
 
-// Announcement made together with a gather: the gather's mark kernel has
-// validated the IDs, and its gate says whether the call was accepted.  Records
-// the list in its window slot and sets the minibatch's bit for every ID (only
-// that bit changes in this kernel, so a plain read-modify-write is exact).
 // ------------------------------------------------------ request order
 // Per-position output: row i of `out` <- row inv[i] of `rows` (the unique-row
 // output of a gather), for the n requests in their original order.  Item w =

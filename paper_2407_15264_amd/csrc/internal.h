@@ -197,7 +197,7 @@ struct Scratch {
 struct DevState {
   SetRec *sets;          // [S]
   uint8_t *rows;         // [S*8][R] cache data
-  uint32_t *mask;        // [N] announced-batch bits (bit j mod 32)
+  uint64_t *win;         // [N] window word: gather index it was written for << 32 | bits of the minibatches after it
   uint32_t *stat;        // [N] static score
   uint64_t *vpos;        // [N] FIFO: 1 + sequence of the node's latest ring entry, or 0;
                          //     queues: (1 + reuse iteration) << 32 | position of its latest entry
@@ -244,22 +244,21 @@ struct QueueFinish {
 };
 
 // The announcement made with a gather, set by the gather's last kernel
-// (ids == nullptr: none): the IDs, the minibatch's window bit, the window
-// words and the list's window slot.
+// (ids == nullptr: none): the IDs, the minibatch's window bit and the window
+// words.
 struct AnnounceArgs {
   const int64_t *ids = nullptr;
-  uint32_t n = 0, bit = 0;
-  uint32_t *mask = nullptr;
-  int64_t *slot_ids = nullptr;
+  uint32_t n = 0, bit = 0, now = 0;  // now: gathers done; the minibatch is the (1 + bit)-th after that one
+  uint64_t *win = nullptr;
   const Gate *gate = nullptr;
 };
 
-// A gather whose metadata one block does: at most this many requests, and at
-// most kTinyLists announced IDs and IDs whose window bit it clears.
+// A gather whose metadata one block does: at most this many requests, at most
+// kTinyLists announced IDs and kTinyMisses expected misses.
 constexpr uint32_t kTinyRequests = 1024, kTinyLists = 4096, kTinyMisses = 128;
 struct TinyArgs {
-  const int64_t *ids = nullptr, *ann_ids = nullptr, *clear_ids = nullptr;  // ann_ids: validated
-  uint32_t n = 0, ann_n = 0, clear_n = 0, clear_bit = 0;
+  const int64_t *ids = nullptr, *ann_ids = nullptr;  // ann_ids: validated
+  uint32_t n = 0, ann_n = 0;
   int64_t *unique_out = nullptr, *inverse = nullptr;
   uint8_t *outcome = nullptr;
   uint64_t t = 0;
@@ -279,7 +278,7 @@ void launch_finish(Counters *cn, Counters *host, const uint32_t *stat_part, cons
                    uint64_t *tail, const QueueFinish &qf, const AnnounceArgs &ann, hipStream_t s);
 // ann_ids/ann_n: the list announced with this gather (validated here), or NULL/0
 void launch_dedup(const DevState &d, const int64_t *ids, uint64_t n, const int64_t *ann_ids, uint64_t ann_n,
-                  const int64_t *clear_ids, uint64_t clear_n, uint32_t clear_bit, Scratch &sc, int64_t *unique_out,
+                  Scratch &sc, int64_t *unique_out,
                   Counters *cn, DedupResult *dd, uint32_t tag, hipStream_t s);
 void launch_group_by_set(const DevState &d, uint64_t n, uint32_t t, Scratch &sc, Counters *cn, StatGrids &grids,
                          hipStream_t s);
@@ -306,9 +305,10 @@ void launch_prefetch(const DevState &d, const Gate *gate, const uint8_t *staging
 void launch_expand(const uint8_t *rows, const int64_t *inv, uint64_t n, uint64_t R, uint8_t *out, hipStream_t s);
 // n bounds the gather's unique count (the copies read the exact one from the gate)
 void launch_copy(CopyMode mode, const DevState &d, uint64_t n, const Scratch &sc, uint8_t *out, hipStream_t s);
-void launch_window_set(const int64_t *ids, uint64_t n, uint64_t N, uint32_t bit, uint32_t *mask, int64_t *slot_ids,
+// the announcement of the (1 + bit)-th minibatch after gather `now`, the next one
+void launch_window_set(const int64_t *ids, uint64_t n, uint64_t N, uint32_t now, uint32_t bit, uint64_t *win,
                        bool record, uint32_t *err, hipStream_t s);
-void launch_window_rollback(const int64_t *ids, uint64_t n, uint64_t N, uint32_t bit, uint32_t *mask,
+void launch_window_rollback(const int64_t *ids, uint64_t n, uint64_t N, uint32_t now, uint32_t bit, uint64_t *win,
                             hipStream_t s);
 void launch_copy_plain(const void *src, void *dst, uint64_t bytes, bool device_to_device, hipStream_t s);
 // pageable store: a host-fetch list length in the gate (0 for a rejected gather) to pinned host memory

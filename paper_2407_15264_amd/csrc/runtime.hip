@@ -77,8 +77,6 @@ using lsm::Scratch;
 
 namespace {
 
-constexpr int kMaxSlots = 32;  // window slots: L + 1 <= 32
-
 struct DeviceGuard {
   int prev = -1;
   bool ok = false;
@@ -202,9 +200,6 @@ struct lsmgnn_cache {
   int device = 0;
   DevState d{};
   uint64_t max_batch = 0;
-  int64_t *win_ids = nullptr;  // (L+1) slots of max_batch IDs
-  int64_t win_batch[kMaxSlots];
-  uint64_t win_len[kMaxSlots];
   Counters *cn = nullptr;      // counters of the metadata kernels (meta stream only)
   // a separate announcement's error flag (pinned), set by the window kernel
   uint32_t *adv_err = nullptr, *adv_err_dev = nullptr;
@@ -727,7 +722,6 @@ lsmgnn_status issue_gather(lsmgnn_cache *c, const int64_t *ids, uint64_t n, cons
   const uint64_t k = c->n_adv;
   if (an.on && k > t + 1 + d.L) return LSMGNN_E_WINDOW;
   const bool record = an.on && k > t + 1 && d.L > 0 && an.n > 0;  // lists for k <= t+1 are never consulted
-  const int kslot = (int)(k % (d.L + 1));
   Flight &f = c->fl[t & 1];
   Flight &pf = c->fl[(t + 1) & 1];  // gather t-1
   PerfSet &ps = c->ps[t % kPerfSets];
@@ -760,13 +754,6 @@ lsmgnn_status issue_gather(lsmgnn_cache *c, const int64_t *ids, uint64_t n, cons
   if (!after_caller(c, s)) return fail_device(c);
   if (f.used) meta_wait_fills(c, f);
 
-  // the window list of the minibatch being gathered is never consulted again:
-  // the first kernel clears its bits
-  const int slot = (int)(t % (d.L + 1));
-  const bool clear = d.L > 0 && c->win_batch[slot] == (int64_t)t;
-  const int64_t *clear_ids = clear ? c->win_ids + (uint64_t)slot * c->max_batch : nullptr;
-  const uint64_t clear_n = clear ? c->win_len[slot] : 0;
-
   // host fetch (PCIe ingress), right after gather t-1's on the same stream,
   // in two parts: the misses known at batch start once they are listed, the
   // rest once the resolve has listed it (and the ring write of gather t-2,
@@ -793,31 +780,29 @@ lsmgnn_status issue_gather(lsmgnn_cache *c, const int64_t *ids, uint64_t n, cons
 
   rec(kEvAll0, c->meta);
   const uint64_t ann_n = an.on ? an.n : 0;
-  const bool dedup = n || clear_n || ann_n;
+  const bool dedup = n || ann_n;
   // the announced bits are first read by the next gather's set walk
   lsm::AnnounceArgs ann;
   if (record) {
     ann.ids = an.ids;
     ann.n = (uint32_t)an.n;
-    ann.bit = (uint32_t)(k & 31u);
-    ann.mask = d.mask;
-    ann.slot_ids = c->win_ids + (uint64_t)kslot * c->max_batch;
+    ann.now = (uint32_t)(t + 1);
+    ann.bit = (uint32_t)(k - t - 2);
+    ann.win = d.win;
     ann.gate = f.sc.gate;
   }
   const uint32_t tag = dedup ? ++c->dd_tag & lsm::kDedupTagMask : 0u;
-  // the update of the dynamic information (every U-th gather) reads the window
-  // bits the dedup updated; the early-miss list neither reads what it writes
-  // nor needs it, so it runs after that list
+  // the update of the dynamic information (every U-th gather) runs after the
+  // early-miss list, which neither reads what it writes nor needs it
   const bool refresh = d.U > 1 && t % d.U == 0;
   // one block for all the metadata while that is faster than the launches it
   // saves (a blocking gather of 250 resident rows 54 us against 63); its 32
   // lane groups walk a set in a few us, so a batch expected to miss more than
   // kTinyMisses rows (by the last gather accounted) takes the kernels
   const bool tiny = serial && !refresh && n <= lsm::kTinyRequests && ann_n <= lsm::kTinyLists &&
-                    clear_n <= lsm::kTinyLists && (n < c->host_rows ? n : c->host_rows) <= lsm::kTinyMisses;
+                    (n < c->host_rows ? n : c->host_rows) <= lsm::kTinyMisses;
   if (dedup && !tiny)
-    lsm::launch_dedup(d, ids, n, ann_n ? an.ids : nullptr, ann_n, clear_ids, clear_n, (uint32_t)(t & 31u), f.sc,
-                      unique_ids, c->cn, c->dd_dev, tag, c->meta);
+    lsm::launch_dedup(d, ids, n, ann_n ? an.ids : nullptr, ann_n, f.sc, unique_ids, c->cn, c->dd_dev, tag, c->meta);
   lsm::StatGrids grids{};
   if (tiny) {
     lsm::TinyArgs a;
@@ -825,9 +810,6 @@ lsmgnn_status issue_gather(lsmgnn_cache *c, const int64_t *ids, uint64_t n, cons
     a.n = (uint32_t)n;
     a.ann_ids = an.ids;
     a.ann_n = (uint32_t)ann_n;
-    a.clear_ids = clear_ids;
-    a.clear_n = (uint32_t)clear_n;
-    a.clear_bit = (uint32_t)(t & 31u);
     a.unique_out = unique_ids;
     a.inverse = inverse;
     a.outcome = outcome;
@@ -957,11 +939,6 @@ lsmgnn_status issue_gather(lsmgnn_cache *c, const int64_t *ids, uint64_t n, cons
     nf.pf_ready = true;
     if (hipGetLastError() != hipSuccess) return fail_device(c);
   }
-  if (clear) c->win_batch[slot] = -1;
-  if (record) {
-    c->win_batch[kslot] = (int64_t)k;
-    c->win_len[kslot] = an.n;
-  }
   if (an.on) c->n_adv = k + 1;
   c->t = t + 1;
   *n_unique = U;
@@ -1056,10 +1033,6 @@ lsmgnn_status lsmgnn_cache_create(const lsmgnn_config *cfg, lsmgnn_cache **out) 
   if (!c) return LSMGNN_E_NOMEM;
   c->device = cfg->device;
   c->max_batch = cfg->max_batch;
-  for (int i = 0; i < kMaxSlots; ++i) {
-    c->win_batch[i] = -1;
-    c->win_len[i] = 0;
-  }
   DevState &d = c->d;
   d.N = N;
   d.R = R;
@@ -1092,7 +1065,7 @@ lsmgnn_status lsmgnn_cache_create(const lsmgnn_config *cfg, lsmgnn_cache **out) 
     return LSMGNN_E_INVAL;
   }
   bool ok = dev_alloc(c, &d.sets, S) && dev_alloc(c, &d.rows, total_rows * R) &&
-            dev_alloc(c, &d.mask, N) &&
+            dev_alloc(c, &d.win, N) &&
             dev_alloc(c, &d.stat, N) && dev_alloc(c, &d.present, map_bytes) &&
             dev_alloc(c, &d.chunk_sums, d.nchunks) &&
             dev_alloc(c, &d.batch, S) && dev_alloc(c, &d.uidx, N) &&
@@ -1101,7 +1074,7 @@ lsmgnn_status lsmgnn_cache_create(const lsmgnn_config *cfg, lsmgnn_cache **out) 
             (d.U == 1 || dev_alloc(c, &d.lreuse, S * lsm::kWays)) &&
             (!queues || (dev_alloc(c, &d.qcount, (uint64_t)d.L + 1) &&
                          dev_alloc(c, &sc.qpart, (uint64_t)lsm::kMaxQueues * (B / lsm::kBlock + 1)))) &&
-            dev_alloc(c, &c->win_ids, (uint64_t)(d.L + 1) * B) && dev_alloc(c, &c->cn, 1) &&
+            dev_alloc(c, &c->cn, 1) &&
             dev_alloc(c, &sc.uniq, B) && dev_alloc(c, &sc.uset, B) &&
             dev_alloc(c, &sc.arrival, B) && dev_alloc(c, &sc.work, B) &&
             dev_alloc(c, &sc.work_mid, B / (lsm::kSmallSet + 1) + 1) &&
@@ -1165,7 +1138,7 @@ lsmgnn_status lsmgnn_cache_create(const lsmgnn_config *cfg, lsmgnn_cache **out) 
     for (hipEvent_t &e : p.e) ok = ok && hipEventCreate(&e) == hipSuccess;
   // initial state: all ways empty, nothing announced, ring empty, counters zero
   ok = ok && hipMemset(d.sets, 0xff, S * sizeof(lsm::SetRec)) == hipSuccess &&
-       hipMemset(d.mask, 0, N * 4) == hipSuccess && hipMemset(d.present, 0, map_bytes) == hipSuccess &&
+       hipMemset(d.win, 0, N * 8) == hipSuccess && hipMemset(d.present, 0, map_bytes) == hipSuccess &&
        hipMemset(d.batch, 0, S * sizeof(lsm::SetBatch)) == hipSuccess && hipMemset(d.tail, 0, 16) == hipSuccess &&
        hipMemset(c->cn, 0, sizeof(Counters)) == hipSuccess &&
        hipMemcpy(d.stat, cfg->static_score, N * 4, hipMemcpyHostToDevice) == hipSuccess &&
@@ -1205,28 +1178,22 @@ lsmgnn_status lsmgnn_advance(lsmgnn_cache *c, const int64_t *ids, uint64_t n, vo
   if (!guard.ok) return LSMGNN_E_DEVICE;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const bool record = j > c->t && c->d.L > 0 && n > 0;  // lists for j <= t are never consulted
-  const int slot = (int)(j % (c->d.L + 1));
   if (!after_caller(c, s)) return fail_device(c);
-  const uint32_t bit = (uint32_t)(j & 31u);
+  const uint32_t now = (uint32_t)c->t, bit = record ? (uint32_t)(j - c->t - 1) : 0u;
   volatile uint32_t *err = c->adv_err;  // the window kernel sets it on an out-of-range ID
   *err = 0u;
   if (n)
-    lsm::launch_window_set(ids, n, c->d.N, bit, c->d.mask, c->win_ids + (uint64_t)slot * c->max_batch, record,
-                           c->adv_err_dev, c->meta);
+    lsm::launch_window_set(ids, n, c->d.N, now, bit, c->d.win, record, c->adv_err_dev, c->meta);
   if (hipEventRecord(c->ev_adv, c->meta) != hipSuccess || hipGetLastError() != hipSuccess ||
       hipEventSynchronize(c->ev_adv) != hipSuccess)
     return fail_device(c);
   if (*err) {
     // the valid IDs of a recorded list had their bit set: clear it again
     if (record) {
-      lsm::launch_window_rollback(ids, n, c->d.N, bit, c->d.mask, c->meta);
+      lsm::launch_window_rollback(ids, n, c->d.N, now, bit, c->d.win, c->meta);
       if (hipGetLastError() != hipSuccess || hipStreamSynchronize(c->meta) != hipSuccess) return fail_device(c);
     }
     return LSMGNN_E_RANGE;
-  }
-  if (record) {
-    c->win_batch[slot] = (int64_t)j;
-    c->win_len[slot] = n;
   }
   c->n_adv = j + 1;
   return LSMGNN_OK;
