@@ -534,9 +534,12 @@ __device__ __forceinline__ void block_counts(const uint32_t (&v)[kN], uint32_t *
 //
 // Bound by latency: a 128-byte set record and an atomic on the set's counter
 // per unique ID, both in flight together.
-__device__ __forceinline__ void probe(const DevState &d, const Scratch &sc, uint64_t t, const Counters *cn) {
+//
+// Returns whether this thread saw an ID that is not resident.
+__device__ __forceinline__ bool probe(const DevState &d, const Scratch &sc, uint64_t t, const Counters *cn) {
   const uint32_t U = cn->n_unique;
   uint32_t c_early = 0;
+  bool missed = false;
   for (uint32_t base = blockIdx.x * kBlock; base < U; base += gridDim.x * kBlock) {
     const uint32_t u = base + threadIdx.x;
     bool early = false;
@@ -555,6 +558,7 @@ __device__ __forceinline__ void probe(const DevState &d, const Scratch &sc, uint
       if (m) {
         sc.slot[u] = s * kWays + (uint32_t)__builtin_ctz(m);
       } else {
+        missed = true;
         d.batch[s].dirty = (uint32_t)t + 1u;
         bool entry = false;
         if (d.V) {
@@ -576,11 +580,12 @@ __device__ __forceinline__ void probe(const DevState &d, const Scratch &sc, uint
     }
   }
   block_counts<1>({c_early}, sc.stat_part, kStEarly);
+  return missed;
 }
 
 __global__ __launch_bounds__(kBlock) void k_probe(const DevState d, Scratch sc, uint64_t t, const Counters *cn) {
   if (cn->err) return;
-  probe(d, sc, t, cn);
+  (void)probe(d, sc, t, cn);
 }
 
 void launch_probe(const DevState &d, uint64_t n, uint64_t t, Scratch &sc, Counters *cn, StatGrids &grids,
@@ -1594,6 +1599,26 @@ __device__ __forceinline__ void tiny_sort(uint64_t *key, uint32_t n) {
     }
 }
 
+// The rest of a gather all of whose IDs are resident: hits change nothing, so
+// there is nothing to group, walk, scan or resolve (a blocking lookup of 250
+// resident rows 48 -> 42 us).
+__device__ __forceinline__ void tiny_all_hits(const DevState &d, const Scratch &sc, const TinyArgs &a, uint32_t U) {
+  for (uint32_t u = threadIdx.x; u < U; u += kBlock) {
+    d.uidx[sc.uniq[u]] = u;
+    d.batch[sc.uset[u]].count = 0;
+    sc.hbm.src[u] = sc.slot[u];
+    if (a.outcome) a.outcome[u] = 0;  // LSMGNN_HIT
+  }
+  __syncthreads();
+  if (a.inverse)
+    for (uint32_t i = threadIdx.x; i < a.n; i += kBlock) a.inverse[i] = (int64_t)d.uidx[a.ids[i]];
+  if (threadIdx.x == 0) {
+    sc.stat_part[kStSettled * kMaxGrid] = U;
+    sc.stat_part[kStHbm * kMaxGrid] = U;
+    sc.stat_part[kStReqHits * kMaxGrid] = a.n;
+  }
+}
+
 template <int P>
 __global__ __launch_bounds__(kBlock) void k_tiny(const DevState d, Scratch sc, TinyArgs a, Counters *cn) {
   __shared__ uint64_t key[kTinyRequests];
@@ -1637,24 +1662,27 @@ __global__ __launch_bounds__(kBlock) void k_tiny(const DevState d, Scratch sc, T
     publish_dedup(a.dd, a.tag, 0, U);
   }
   __syncthreads();
-  probe(d, sc, a.t, cn);
-  __syncthreads();
-  seg_alloc(d, sc, (uint32_t)a.t, cn);
-  __syncthreads();
-  place(d, sc, cn);
-  __syncthreads();
-  walk_sets<P>(d, sc, (uint32_t)a.t, cn);
-  __syncthreads();
-  resolve(d, sc, a.t, a.outcome, d.V ? kScanCounts : kScanNone, cn);
-  __syncthreads();
-  if (d.V) enqueue_entries(d, sc, cn);
-  request_counts(d, sc, a.ids, n, a.inverse);
+  StatGrids grids{};
+  if (!__syncthreads_or(probe(d, sc, a.t, cn))) {
+    tiny_all_hits(d, sc, a, U);
+    grids.g[kStSettled] = grids.g[kStHbm] = grids.g[kStReqHits] = 1;
+  } else {
+    seg_alloc(d, sc, (uint32_t)a.t, cn);
+    __syncthreads();
+    place(d, sc, cn);
+    __syncthreads();
+    walk_sets<P>(d, sc, (uint32_t)a.t, cn);
+    __syncthreads();
+    resolve(d, sc, a.t, a.outcome, d.V ? kScanCounts : kScanNone, cn);
+    __syncthreads();
+    if (d.V) enqueue_entries(d, sc, cn);
+    request_counts(d, sc, a.ids, n, a.inverse);
+#pragma unroll
+    for (int st = 0; st < kNumStat; ++st) grids.g[st] = 1;
+    grids.g[kStEnqCopy] = d.V ? 1 : 0;
+  }
   if (a.ann.ids) announce(a.ann);
   __syncthreads();
-  StatGrids grids;
-#pragma unroll
-  for (int st = 0; st < kNumStat; ++st) grids.g[st] = 1;
-  grids.g[kStEnqCopy] = d.V ? 1 : 0;
   finish(cn, a.hc, sc.stat_part, grids, d.tail, QueueFinish{});
 }
 
