@@ -905,7 +905,13 @@ lsmgnn_status issue_gather(lsmgnn_cache *c, const int64_t *ids, uint64_t n, cons
   // fills after the host fetch, the staging and the hit copy
   if (!defer && !serial) queue_fills(c, t, fill);
   if (hipGetLastError() != hipSuccess) return fail_device(c);
-  if (err) return LSMGNN_E_RANGE;  // every queued kernel of the batch is a no-op
+  if (err) {
+    // every queued kernel of the batch is a no-op, but its host fetch still has
+    // to read the gate that says so: the call that resets this parity's gate
+    // and lists next waits for the gather's fills, and a deferred one has none
+    if (defer && hipStreamWaitEvent(c->meta, f.host_done, 0) != hipSuccess) return fail_device(c);
+    return LSMGNN_E_RANGE;
+  }
   f.data_deferred = defer;
 
   f.stats_pending = true;
