@@ -253,6 +253,10 @@ struct AnnounceArgs {
   const Gate *gate = nullptr;
 };
 
+// A gather runs on one stream when it is expected to fetch at most this many
+// bytes over the link.
+constexpr uint64_t kSerialBytes = 1ull << 20;
+
 // A gather whose metadata one block does: at most this many requests, at most
 // kTinyLists announced IDs and kTinyMisses expected misses.
 constexpr uint32_t kTinyRequests = 1024, kTinyLists = 4096, kTinyMisses = 128;

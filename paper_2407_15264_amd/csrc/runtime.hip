@@ -144,6 +144,11 @@ struct PerfSet {
   uint32_t n_hbm = 0, n_host = 0, n_enq = 0, n_fill = 0, n_pf = 0;
 };
 
+// What a gather found: its requests, and its rows over the link and in all.
+struct Recent {
+  uint64_t requests = 0, host_rows = 0, rows = 0;
+};
+
 // The per-device stream triple, created with the first cache on a device and
 // destroyed with the last.
 constexpr int kMaxDevices = 64;
@@ -205,7 +210,7 @@ struct lsmgnn_cache {
   uint32_t *adv_err = nullptr, *adv_err_dev = nullptr;
   DedupResult *dd = nullptr, *dd_dev = nullptr;
   uint32_t dd_tag = 0;           // of the last dedup queued
-  uint64_t host_rows = ~0ull, rows = ~0ull;  // rows the last accounted gather fetched over the link, and in all
+  Recent recent[2];              // the last two gathers accounted that had requests
   Flight fl[2];
   PerfSet ps[kPerfSets];
   hipStream_t meta = nullptr, host = nullptr, dma = nullptr;  // the device's shared streams
@@ -327,8 +332,10 @@ void harvest_stats(lsmgnn_cache *c, Flight &f) {
   c->total.victim_rows_staged += st.victim_rows_staged;
   c->total.victim_rows_cache += st.victim_rows_cache;
   c->total.victim_rows_prefetched += st.victim_rows_prefetched;
-  c->host_rows = h.n_host;
-  c->rows = h.n_unique;
+  if (f.requests) {  // an empty one says nothing about the next
+    c->recent[1] = c->recent[0];
+    c->recent[0] = Recent{f.requests, h.n_host, h.n_unique};
+  }
   c->tail += h.enq_total;
   f.enq_total = h.enq_total;
   f.tail_end = c->tail;
@@ -684,22 +691,41 @@ struct Announce {
   uint64_t n = 0;
 };
 
+// The rows a gather of n requests is expected to take, over the link
+// (Recent::host_rows) or in all (Recent::rows): the larger share of requests
+// that the last two gathers accounted had, so that a stream which alternates
+// between resident and missing minibatches is taken for a missing one.  A list
+// of less than a quarter of n requests says nothing about this one; without any
+// other, every request is expected to be a row.
+uint64_t expected_rows(const lsmgnn_cache *c, uint64_t n, uint64_t Recent::*rows) {
+  uint64_t most = 0;
+  bool known = false;
+  for (const Recent &r : c->recent)
+    if (r.requests && n / 4 <= r.requests) {
+      const uint64_t e = (r.*rows * n + r.requests - 1) / r.requests;  // both below 2^32
+      most = e > most ? e : most;
+      known = true;
+    }
+  return known && most < n ? most : n;
+}
+
 // Whether a gather runs on the meta stream alone: when it is expected to fetch
-// at most kSerialBytes over the link, judged by the last gather accounted (the
-// first one by its request list).  The fetch, up to 18 us for 1 MiB, then no
+// at most kSerialBytes over the link.  The fetch (18 us for 1 MiB of wide rows;
+// scattered narrow ones cost 2-3 ns each, 135 us for 65536 of 16 bytes) then no
 // longer runs beside the rest of the metadata (30-50 us), but the gather has
 // no hand-over to the host-link stream and back (10-15 us each): a blocking
 // gather of 250 requests took 63 us against 123, of 9 K requests 117 against
-// 160.  A pipelined gather moves at most kSerialRowBytes of rows this way (6 us
-// of hit copy): more of them are better copied beside the next gather's
-// metadata (four gathers of 480 MB each 1191 us, on one stream 1303).  Not
-// with a pageable store or queues, whose rows the host or the prefetch stream
-// brings.
-constexpr uint64_t kSerialBytes = 1ull << 20, kSerialRowBytes = 16ull << 20;
+// 160, and with narrow rows that all miss 121 against 152 (16 K requests) and
+// 231 against 252 (60 K).  A pipelined gather moves at most kSerialRowBytes of
+// rows this way (6 us of hit copy): more of them are better copied beside the
+// next gather's metadata (four gathers of 480 MB each 1191 us, on one stream
+// 1303).  Not with a pageable store or queues, whose rows the host or the
+// prefetch stream brings.
+constexpr uint64_t kSerialRowBytes = 16ull << 20;
 bool queue_serial(const lsmgnn_cache *c, uint64_t n, bool queues, bool pipelined) {
-  const uint64_t host_rows = n < c->host_rows ? n : c->host_rows, rows = n < c->rows ? n : c->rows;
-  return n && !c->pageable && !queues && host_rows <= kSerialBytes / c->d.R &&
-         (!pipelined || rows <= kSerialRowBytes / c->d.R);
+  return n && !c->pageable && !queues &&
+         expected_rows(c, n, &Recent::host_rows) <= lsm::kSerialBytes / c->d.R &&
+         (!pipelined || expected_rows(c, n, &Recent::rows) <= kSerialRowBytes / c->d.R);
 }
 
 // Queue one gather (and the announcement after it).  Returns once its unique
@@ -798,9 +824,9 @@ lsmgnn_status issue_gather(lsmgnn_cache *c, const int64_t *ids, uint64_t n, cons
   // one block for all the metadata while that is faster than the launches it
   // saves (a blocking gather of 250 resident rows 54 us against 63); its 32
   // lane groups walk a set in a few us, so a batch expected to miss more than
-  // kTinyMisses rows (by the last gather accounted) takes the kernels
+  // kTinyMisses rows takes the kernels
   const bool tiny = serial && !refresh && n <= lsm::kTinyRequests && ann_n <= lsm::kTinyLists &&
-                    (n < c->host_rows ? n : c->host_rows) <= lsm::kTinyMisses;
+                    expected_rows(c, n, &Recent::host_rows) <= lsm::kTinyMisses;
   if (dedup && !tiny)
     lsm::launch_dedup(d, ids, n, ann_n ? an.ids : nullptr, ann_n, f.sc, unique_ids, c->cn, c->dd_dev, tag, c->meta);
   lsm::StatGrids grids{};

@@ -152,3 +152,25 @@ def test_dedup_chunks(nodes):
     store = Store.random_bytes(nodes, 16, 6)
     stat = rng.integers(0, 9, nodes).astype(np.uint32)
     run_parity(store, stat, 500, 300, 2, batches, rows="all", label=f"N={nodes}")
+
+
+@pytest.mark.parametrize("victim", [0, 700])
+@pytest.mark.parametrize("row_bytes", [16, 1008, 4096])
+def test_more_host_rows_than_expected(row_bytes, victim):
+    """Minibatches that miss everything after resident ones: they were expected to fetch little, and their host rows
+    take more tiles than one launch has blocks for."""
+    log(f"case: more host rows than expected, {row_bytes} B rows, V={victim}")
+    n, sets, requests = 40_000, 1500, max(3000, (2 << 20) // row_bytes if row_bytes > 16 else 9000)
+    rng = np.random.default_rng(row_bytes + victim)
+    pool = rng.choice(n, requests // 2, replace=False)
+    batches = []
+    for b in range(12):
+        if b % 4 == 3:
+            batches.append(rng.permutation(n)[:requests])
+            pool = rng.choice(n, requests // 2, replace=False)
+        else:
+            batches.append(rng.choice(pool, requests))
+    store = Store.random_bytes(n, row_bytes, 7)
+    stat = rng.integers(0, 7, n).astype(np.uint32)
+    run_parity(store, stat, sets, victim, 2, batches, rows="all", label="unexpected misses")
+    run_async_parity(store, stat, sets, victim, 2, batches, rows="all", label="unexpected misses pipelined")

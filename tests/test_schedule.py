@@ -162,3 +162,67 @@ def test_retry_of_a_rejected_pipelined_gather(fresh):
     c.gather(60_000, 50_000, 20_000, 5000, 3000, pipelined=True)
     c.close()
     check(fresh)
+
+
+def moved(log):
+    """How a gather's rows moved: by one launch on the meta stream, or over the three streams."""
+    names = {line.split(" ")[-1] for line in log}
+    assert ("move_rows@meta" in names) != ("host_late@host" in names), log
+    return "one" if "move_rows@meta" in names else "three"
+
+
+def tiny(log):
+    return any(line.endswith("tiny@meta") for line in log)
+
+
+def test_streams_of_a_steady_gather(fresh):
+    """Up to 1 MiB expected over the link: one stream; above it, three.  Lists of about the same length scale."""
+    rows = (1 << 20) // 4096
+    c = Cache(fresh)
+    assert moved(c.gather(1000, 900, 900)[3]) == "three"  # nothing known: every request may miss
+    for n, host, want in [(1000, rows, "three"), (1000, rows, "three"), (1000, rows + 1, "one"), (1000, 0, "three"),
+                          (1000, 0, "three"), (1000, 0, "one"), (4000, 0, "one"), (16003, 0, "one"),
+                          (70_000, 0, "three")]:
+        assert moved(c.gather(n, min(n, 900), host)[3]) == want, (n, host)
+    c.close()
+    check(fresh)
+
+
+def test_an_empty_gather_predicts_nothing(fresh):
+    c = Cache(fresh, victim=5000)
+    for _ in range(3):
+        c.gather(60_000, 50_000, 30_000, enq=100)
+        c.gather(0)
+        assert moved(c.gather(60_000, 50_000, 30_000, enq=100, pipelined=True)[3]) == "three"
+        c.gather(0, pipelined=True)
+    c.close()
+    c = Cache(fresh, row_bytes=16)
+    for _ in range(3):
+        c.gather(1000, 900, 900)
+        c.gather(0)
+        log = c.gather(1000, 900, 900)[3]
+        assert moved(log) == "one" and not tiny(log)
+    c.close()
+    check(fresh)
+
+
+@pytest.mark.parametrize("pipelined", [False, True])
+def test_a_lookup_predicts_no_large_gather(fresh, pipelined):
+    c = Cache(fresh, row_bytes=1024)
+    for _ in range(3):
+        for _ in range(3):
+            log = c.gather(250, 200, 0)[3]
+        assert tiny(log)
+        assert moved(c.gather(60_000, 50_000, 30_000, pipelined=pipelined)[3]) == "three"
+    c.close()
+    check(fresh)
+
+
+def test_alternating_minibatches_take_three_streams(fresh):
+    """Resident and missing minibatches in turn: the missing ones are never taken for resident ones."""
+    c = Cache(fresh)
+    for k in range(12):
+        log = c.gather(5000, 4000, 3000 if k % 2 else 0, pipelined=k % 3 == 0)[3]
+        assert moved(log) == "three", k
+    c.close()
+    check(fresh)
