@@ -569,13 +569,17 @@ void queue_stage(lsmgnn_cache *c, uint64_t g, bool event) {
 // on its entries), which gather g+1's staging overwrites later on the same
 // stream.
 //
-// `on_dma` (pipelined gathers without a victim buffer): on the dma stream,
-// which then carries nothing but hit copies and fills, once the resolve has
-// listed the rows.  The next gather's metadata, bound by latency, then runs
+// `on_dma` (pipelined gathers without a victim buffer): on the dma stream, once
+// the resolve has listed the rows; this cache queues nothing there but hit
+// copies and fills.  The next gather's metadata, bound by latency, then runs
 // beside this copy, bound by HBM bandwidth, instead of behind it: four
 // gathers of 900 K requests (235 K resident 2 KiB rows each) took 1191 us
 // against 1465.  With a victim buffer the copy would wait there for the
 // previous gather's ring write, which can take as long as the host fetch.
+// Another cache's ring writes on the shared stream cost nothing measurable:
+// minibatches of a cache that keeps its evicted rows in a ring (30 K requests of
+// 4 KiB rows, most of them fetched) and of two resident ones beside it took
+// 1817 us, with the copy on the meta stream 1821.
 //
 // `event`: record hit_done (for fills on another stream).
 void queue_hit(lsmgnn_cache *c, uint64_t g, bool on_dma, bool event) {
@@ -721,6 +725,12 @@ uint64_t expected_rows(const lsmgnn_cache *c, uint64_t n, uint64_t Recent::*rows
 // next gather's metadata (four gathers of 480 MB each 1191 us, on one stream
 // 1303).  Not with a pageable store or queues, whose rows the host or the
 // prefetch stream brings.
+//
+// Other caches on the device, whose metadata queues behind these rows on the
+// shared stream, make no difference to the rule: the minibatches of the three
+// caches named at queue_hit took 1817 us, with three streams for each gather
+// 1837 (blocking 2080 and 2147), and of three caches of 16 K nodes 219 us
+// against 388.
 constexpr uint64_t kSerialRowBytes = 16ull << 20;
 bool queue_serial(const lsmgnn_cache *c, uint64_t n, bool queues, bool pipelined) {
   return n && !c->pageable && !queues &&

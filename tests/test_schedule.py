@@ -109,10 +109,12 @@ KINDS = {"no ring": dict(), "ring": dict(victim=5000), "queues": dict(victim=300
          "pageable": dict(victim=5000, pageable=True, max_batch=3000, row_bytes=64)}
 
 
-def random_calls(c, rng, steps):
+def random_calls(caches, rng, steps):
     """Blocking, pipelined, small, large, empty and rejected gathers, announcements, waits and syncs in any order."""
-    waiting = []
+    pending = {c: [] for c in caches}
     for _ in range(steps):
+        c = rng.choice(caches)
+        waiting = pending[c]
         c.L.model_caller_busy(rng.randint(0, 1))
         kind = rng.random()
         if kind < 0.1:
@@ -125,7 +127,7 @@ def random_calls(c, rng, steps):
             assert c.L.lsmgnn_sync(c.h) == lsmgnn.OK
             for _, outs in waiting:
                 c.read(outs)
-            waiting = []
+            waiting.clear()
         else:
             n = rng.choice([0, 1, 250, 1024, 1025, 3000] + ([60_000] if c.max_batch > 60_000 else []))
             unique = n and rng.randint(1, n)
@@ -148,8 +150,18 @@ def random_calls(c, rng, steps):
 @pytest.mark.parametrize("seed", range(8))
 def test_no_unordered_accesses(fresh, kind, seed):
     c = Cache(fresh, **KINDS[kind])
-    random_calls(c, random.Random(seed), 200)
+    random_calls([c], random.Random(seed), 200)
     c.close()
+    check(fresh)
+
+
+@pytest.mark.parametrize("seed", range(8))
+def test_no_unordered_accesses_between_caches(fresh, seed):
+    """Several caches, which share their device's streams: with and without a ring, one with queues."""
+    caches = [Cache(fresh, **KINDS[k]) for k in ("no ring", "ring", "no ring", "queues")]
+    random_calls(caches, random.Random(seed), 400)
+    for c in caches:
+        c.close()
     check(fresh)
 
 
