@@ -230,6 +230,15 @@ struct DevState {
   uint64_t stage_rows;   // rows per staging buffer: min(max_batch, V)
 };
 
+// How many of a cache's accepted gathers moved their rows on the meta stream
+// alone, how many of those had their metadata done by one block, how many had
+// their hit copy on the dma stream beside the next gather's metadata, and how
+// many left it to the next call; the rest were blocking gathers, or queued
+// their copies themselves, over the three streams.
+struct Routes {
+  uint64_t one_stream, one_block, overlapped, deferred;
+};
+
 // kHostEarly / kHostLate: the host fetch of the host-fetch list's first
 // n_early entries, and of the rest
 enum class CopyMode { kHbmToOut, kHostLate, kCacheToStage, kOutToCache, kHostEarly };
@@ -328,3 +337,7 @@ void launch_probe(const DevState &d, uint64_t n, uint64_t t, Scratch &sc, Counte
 uint64_t set_of_host(uint64_t x, uint64_t num_sets);
 
 }  // namespace lsm
+
+// The routes a cache's gathers took since its create, for tests (exported, not
+// part of the public C ABI).
+extern "C" void lsm_cache_routes(const struct lsmgnn_cache *c, lsm::Routes *out);

@@ -211,6 +211,7 @@ struct lsmgnn_cache {
   DedupResult *dd = nullptr, *dd_dev = nullptr;
   uint32_t dd_tag = 0;           // of the last dedup queued
   Recent recent[2];              // the last two gathers accounted that had requests
+  lsm::Routes routes{};
   Flight fl[2];
   PerfSet ps[kPerfSets];
   hipStream_t meta = nullptr, host = nullptr, dma = nullptr;  // the device's shared streams
@@ -981,6 +982,10 @@ lsmgnn_status issue_gather(lsmgnn_cache *c, const int64_t *ids, uint64_t n, cons
     nf.pf_ready = true;
     if (hipGetLastError() != hipSuccess) return fail_device(c);
   }
+  c->routes.one_stream += serial;
+  c->routes.one_block += tiny;
+  c->routes.overlapped += overlap;
+  c->routes.deferred += defer;
   if (an.on) c->n_adv = k + 1;
   c->t = t + 1;
   *n_unique = U;
@@ -1349,6 +1354,8 @@ lsmgnn_status lsmgnn_export_state(lsmgnn_cache *c, uint32_t *tags, uint32_t *rin
   if (t) *t = c->t;
   return LSMGNN_OK;
 }
+
+void lsm_cache_routes(const lsmgnn_cache *c, lsm::Routes *out) { *out = c->routes; }
 
 lsmgnn_status lsmgnn_expand(const void *rows, const int64_t *inverse, uint64_t n, uint64_t row_bytes, void *out,
                             void *stream) {

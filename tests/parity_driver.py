@@ -9,6 +9,7 @@ exactly.
 """
 from __future__ import annotations
 
+import ctypes
 import sys
 import time
 
@@ -57,6 +58,19 @@ class Store:
         s._alloc(pinned)
         s.np[:] = rng.integers(0, 256, (num_nodes, row_bytes), dtype=np.uint8)
         return s
+
+
+class _Routes(ctypes.Structure):
+    _fields_ = [(f, ctypes.c_uint64) for f in ("one_stream", "one_block", "overlapped", "deferred")]
+
+
+def routes(cache):
+    """How many of the cache's gathers took each of the library's schedules."""
+    r = _Routes()
+    f = lsmgnn.lib().lsm_cache_routes
+    f.argtypes, f.restype = [ctypes.c_void_p, ctypes.POINTER(_Routes)], None
+    f(cache._h, ctypes.byref(r))
+    return {name: getattr(r, name) for name, _ in _Routes._fields_}
 
 
 def compare_state(cache, orc, where=""):
@@ -148,9 +162,10 @@ def run_parity(store: Store, static, num_sets, victim_rows, lookahead, batches, 
         for k, v in o_tot.items():
             if k != "batch" and tot[k] != v:
                 raise AssertionError(f"{label}: total {k}: gpu {tot[k]} oracle {v}")
+    ways = routes(cache)
     cache.close()
     orc.close()
-    return dict(total=tot, seconds=time.time() - t0)
+    return dict(total=tot, seconds=time.time() - t0, routes=ways)
 
 
 def device_store(store: Store, device=0):
@@ -173,7 +188,7 @@ class _Lane:
 
     def __init__(self, store, static, num_sets, victim_rows, lookahead, batches, rows, store_gpu, label,
                  combined, near_threshold, device, row_sample=0, policy="hybrid", victim_mode="fifo",
-                 refresh_period=1, mixed_seed=None):
+                 refresh_period=1, mixed_seed=None, reject_seed=None):
         import torch
         self.torch = torch
         self.store, self.row_sample = store, row_sample
@@ -181,8 +196,11 @@ class _Lane:
         # mixed_seed: each gather goes through the blocking call (then a
         # separate advance) or the pipelined one, by a seeded coin
         self.mixed = None if mixed_seed is None else np.random.default_rng(mixed_seed)
+        # reject_seed: by a seeded coin, a pipelined call with an ID out of range
+        # before the gather; nothing may ever write its output
+        self.reject = None if reject_seed is None else np.random.default_rng(reject_seed)
         dev = torch.device("cuda", device)
-        self.mb = max(1, max(len(b) for b in batches))
+        self.mb = max(1, max(len(b) for b in batches)) + (self.reject is not None)
         self.L, self.batches, self.rows, self.store_gpu, self.label = lookahead, batches, rows, store_gpu, label
         self.combined = combined
         self.cache = lsmgnn.FeatureCache(store.num_nodes, store.row_bytes, store.buf, static, num_sets, victim_rows,
@@ -208,8 +226,19 @@ class _Lane:
             self.cache.advance(self.db[j])
             self.orc.advance(batches[j])
         self.pending = []
+        self.rejected_out = None
+        if self.reject is not None:
+            self.rejected_out = torch.full((self.mb * store.row_bytes,), 0xa5, dtype=torch.uint8, device=dev)
+            self.rejected_ids = torch.empty(self.mb, dtype=torch.int64, device=dev)
 
     def issue(self, b):
+        if self.reject is not None and self.reject.random() < 0.4:
+            bad = self.torch.cat([self.db[b], self.torch.full((1,), self.store.num_nodes, device=self.db[b].device)])
+            try:
+                self.cache.gather_async(bad, self.rejected_out, self.rejected_ids)
+                raise AssertionError(f"{self.label} gather {b}: an ID out of range was accepted")
+            except lsmgnn.LsmgnnError as e:
+                assert e.code == lsmgnn.E_RANGE
         out, uq, inv, oc = self.bufs[b % 3]
         L = self.L
         nxt = self.db[b + L + 1] if b + L + 1 < len(self.batches) else None
@@ -280,6 +309,9 @@ class _Lane:
         for k in COUNT_KEYS:
             assert tot_gpu[k] == tot_orc[k], (self.label, k, tot_gpu[k], tot_orc[k])
         compare_state(self.cache, self.orc, f"{self.label} end")
+        if self.rejected_out is not None:
+            assert bool((self.rejected_out == 0xa5).all()), f"{self.label}: a rejected call's output was written"
+        self.routes = routes(self.cache)
         self.cache.close()
         self.orc.close()
         return tot_gpu
@@ -306,28 +338,29 @@ def _run_lanes(lanes, nb, state_every, label):
 
 def run_async_parity(store: Store, static, num_sets, victim_rows, lookahead, batches, rows="all", store_gpu=None,
                      state_every=0, label="async", combined=True, near_threshold=0, device=0, row_sample=0,
-                     policy="hybrid", victim_mode="fifo", refresh_period=1):
+                     policy="hybrid", victim_mode="fifo", refresh_period=1, reject_seed=None):
     """One cache in the launch configuration of bench.py, against the oracle:
     unique IDs, inverse, outcomes and rows of every gather (rows as in
     run_parity), counters as totals, the cache and ring state every
     `state_every` gathers and at the end."""
     ln = _Lane(store, static, num_sets, victim_rows, lookahead, batches, rows, store_gpu, label, combined,
-               near_threshold, device, row_sample, policy, victim_mode, refresh_period)
+               near_threshold, device, row_sample, policy, victim_mode, refresh_period, reject_seed=reject_seed)
     totals, seconds = _run_lanes([ln], len(batches), state_every, label)
-    return dict(total=totals[0], seconds=seconds)
+    return dict(total=totals[0], seconds=seconds, routes=ln.routes)
 
 
 def run_mixed_parity(store: Store, static, num_sets, victim_rows, lookahead, batches, seed, state_every=0,
-                     label="mixed", near_threshold=0, policy="hybrid", victim_mode="fifo", refresh_period=1):
+                     label="mixed", near_threshold=0, policy="hybrid", victim_mode="fifo", refresh_period=1,
+                     reject_seed=None):
     """Blocking and pipelined gathers interleaved on one cache (a seeded coin
     per gather), with no call in between that waits for the library's
     streams except the checks' own waits: every gather's unique IDs, inverse,
     outcomes and rows, the counters as totals, the state every `state_every`
     gathers and at the end."""
     ln = _Lane(store, static, num_sets, victim_rows, lookahead, batches, "all", None, label, True, near_threshold,
-               0, 0, policy, victim_mode, refresh_period, mixed_seed=seed)
+               0, 0, policy, victim_mode, refresh_period, mixed_seed=seed, reject_seed=reject_seed)
     totals, seconds = _run_lanes([ln], len(batches), state_every, label)
-    return dict(total=totals[0], seconds=seconds)
+    return dict(total=totals[0], seconds=seconds, routes=ln.routes)
 
 
 def run_typed_async_parity(stores, statics, shapes, type_batches, rows=50, stores_gpu=None, state_every=0,
@@ -339,7 +372,7 @@ def run_typed_async_parity(stores, statics, shapes, type_batches, rows=50, store
                    type_batches[t], rows, None if stores_gpu is None else stores_gpu[t], f"{label} type {t}", True,
                    shapes[t].near_threshold, device) for t in range(len(stores))]
     totals, seconds = _run_lanes(lanes, len(type_batches[0]), state_every, label)
-    return dict(totals=totals, seconds=seconds)
+    return dict(totals=totals, seconds=seconds, routes=[ln.routes for ln in lanes])
 
 
 def config_stream(cfg, batches=None):

@@ -514,7 +514,8 @@ def test_blocking_gathers_back_to_back(seed):
     """Blocking gathers with no call in between that waits for the library's
     internal streams (counters are compared as totals at the end): each
     gather's fills, the ring writes and the next gather's staging are ordered
-    by the library's events alone.  Rows, unique IDs, inverse and outcomes
+    by the library's events alone (with pinned rows this small by one stream;
+    tests/test_gpu_streams.py has wide ones).  Rows, unique IDs, inverse and outcomes
     after every gather; the final cache and ring state.  Odd seeds use a
     pageable store, every fourth the victim queues."""
     n, S, V, L, T, stat, batches = _long_case(200 + seed)
@@ -529,11 +530,13 @@ def test_blocking_gathers_back_to_back(seed):
 
 @pytest.mark.parametrize("seed", range(8))
 def test_blocking_and_pipelined_gathers_interleaved(seed):
-    """The two entry points alternate by a seeded coin on one cache: a blocking
-    gather's fills run on the host-link stream, a pipelined gather's on the
-    dma stream, and each gather's ring write must still follow its own host
-    fetch.  Odd seeds use a pageable store, every fourth the victim queues,
-    every third an update period of 2."""
+    """The two entry points alternate by a seeded coin on one cache: where the
+    three streams are used (odd seeds, a pageable store, and every fourth, the
+    victim queues) a blocking gather's fills run on the host-link stream, a
+    pipelined gather's on the dma stream, and each gather's ring write must
+    still follow its own host fetch.  Small rows in pinned memory (the other
+    seeds) move on one stream; tests/test_gpu_streams.py has wide ones.  Every
+    third seed has an update period of 2."""
     n, S, V, L, T, stat, batches = _long_case(300 + seed)
     mode = "queues" if seed % 4 == 3 else "fifo"
     if mode == "queues":
