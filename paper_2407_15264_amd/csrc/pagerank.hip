@@ -115,10 +115,25 @@ struct Max {
   __device__ uint32_t operator()(uint32_t a, uint32_t b) const { return a > b ? a : b; }
 };
 
+// The last row of [lo, hi) that begins at or before entry e, by one wave's
+// 64-way search of the offsets; row lo does.
+__device__ __forceinline__ uint64_t last_row_from(const int64_t *off, uint64_t lo, uint64_t hi, uint64_t e) {
+  while (hi - lo > 1) {
+    const uint64_t step = (hi - lo + 63) / 64, at = lo + (threadIdx.x & 63u) * step;
+    const uint64_t m = __ballot(at < hi && (uint64_t)off[at] <= e);  // lane 0 always
+    const uint64_t k = 63u - (uint32_t)__clzll((long long)m);
+    lo += k * step;
+    hi = lo + step < hi ? lo + step : hi;
+  }
+  return lo;
+}
+
 // The source node of each entry of the block's tile: the tile's first row by a
-// 64-way search of the offsets, the rows that start inside it marked at their
-// first entry, and a maximum scan over the marks.  (A thread per row, writing
-// its entries one by one, took 2.3 ms where one row holds tens of thousands.)
+// search of the offsets, the rows that start inside it marked at their first
+// entry, and a maximum scan over the marks.  (A thread per row, writing its
+// entries one by one, took 2.3 ms where one row holds tens of thousands.)
+// 256 rows without entries in a row are followed by a search for the next one
+// that has some: walked, a run of 10 M of them took its block 26 ms.
 __global__ __launch_bounds__(kBlock) void k_sources(const int64_t *off, uint64_t N, uint64_t E, uint32_t *src) {
   __shared__ uint32_t mark[kTile];
   __shared__ uint64_t first;
@@ -127,24 +142,25 @@ __global__ __launch_bounds__(kBlock) void k_sources(const int64_t *off, uint64_t
     const uint64_t e0 = b * kTile, e1 = e0 + kTile < E ? e0 + kTile : E;
     for (uint32_t i = threadIdx.x; i < kTile; i += kBlock) mark[i] = 0;
     if (threadIdx.x < 64) {
-      // the largest r with off[r] <= e0: off[lo] <= e0 < off[hi]
-      uint64_t lo = 0, hi = N;
-      while (hi - lo > 1) {
-        const uint64_t step = (hi - lo + 63) / 64, at = lo + threadIdx.x * step;
-        const uint64_t m = __ballot(at < hi && (uint64_t)off[at] <= e0);  // lane 0 always
-        const uint64_t k = 63u - (uint32_t)__clzll((long long)m);
-        lo += k * step;
-        hi = lo + step < hi ? lo + step : hi;
-      }
-      if (threadIdx.x == 0) first = lo;
+      const uint64_t r = last_row_from(off, 0, N, e0);
+      if (threadIdx.x == 0) first = r;
     }
     __syncthreads();
     const uint64_t r0 = first;
-    for (uint64_t rb = r0 + 1;; rb += kBlock) {
+    for (uint64_t rb = r0 + 1;;) {
       const uint64_t r = rb + threadIdx.x;
-      const bool in = r < N && (uint64_t)off[r] < e1;
-      if (in) atomicMax(&mark[(uint64_t)off[r] - e0], (uint32_t)r);
+      const uint64_t o = r < N ? (uint64_t)off[r] : E;
+      const bool in = o < e1, filled = in && (uint64_t)off[r + 1] > o;
+      if (filled) mark[o - e0] = (uint32_t)r;
       if (__syncthreads_or(!in)) break;
+      rb += kBlock;
+      if (__syncthreads_or(filled)) continue;
+      if (threadIdx.x < 64) {
+        const uint64_t next = last_row_from(off, rb - 1, N, (uint64_t)off[rb - 1]);
+        if (threadIdx.x == 0) first = next;
+      }
+      __syncthreads();
+      rb = first;
     }
     uint32_t v[kTileItems], top = threadIdx.x == 0 ? (uint32_t)r0 : 0u;
 #pragma unroll

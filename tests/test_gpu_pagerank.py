@@ -168,6 +168,48 @@ def test_rows_concentrated():
     _check_with_dangling(offsets, adj, 0.85, 4, "rows far apart")
 
 
+@pytest.mark.parametrize("run", [255, 256, 257, 511, 513, 5000, 100_000])
+def test_runs_of_empty_rows(run):
+    """Runs of rows without entries of about as many rows as a block looks at together, between rows with a few."""
+    n = 6 * run + 4000
+    deg = np.random.default_rng(run).integers(0, 4, n)
+    for k in range(6):
+        at = k * (run + 600) + int(k > 2) * 17
+        deg[at:at + run] = 0
+    offsets = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    adj = np.random.default_rng(run + 1).integers(0, n, int(offsets[-1])).astype(np.uint32)
+    log(f"case: pagerank, runs of {run} empty rows")
+    _check_with_dangling(offsets, adj, 0.85, 4, f"runs of {run}")
+
+
+def test_time_of_a_long_run_of_empty_rows():
+    """Ten million rows without entries between the others cost about what they cost after them: they are searched
+    past, not walked by one block (which took 20 times as long)."""
+    n, empty, entries = 12_000_000, 10_000_000, 4_000_000
+    g = torch.Generator(device="cuda").manual_seed(3)
+    deg = torch.bincount(torch.randint(0, n - empty, (entries,), generator=g, device="cuda"), minlength=n - empty)
+    none = torch.zeros(empty, dtype=deg.dtype, device="cuda")
+    adj = torch.randint(0, n, (entries,), generator=g, device="cuda", dtype=torch.int32)
+    start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+
+    def milliseconds(degrees):
+        offsets = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+        offsets[1:] = torch.cumsum(degrees, 0)
+        best = float("inf")
+        for _ in range(5):
+            start.record()
+            lsmgnn.pagerank_scores(offsets, adj, iterations=1)
+            stop.record()
+            stop.synchronize()
+            best = min(best, start.elapsed_time(stop))
+        return best
+
+    after = milliseconds(torch.cat([deg, none]))
+    between = milliseconds(torch.cat([deg[: deg.numel() // 2], none, deg[deg.numel() // 2:]]))
+    log(f"case: pagerank, 10 M empty rows after the others {after:.2f} ms, between them {between:.2f} ms")
+    assert between < 4 * after
+
+
 def test_without_memory_for_the_sort():
     """With too little device memory for the sorted entries the shares are pushed instead, with the same result."""
     log("case: pagerank without memory for the sort")
