@@ -1157,17 +1157,29 @@ constexpr uint32_t kFusedScanMax = 4096;
 // Where the resolve finds the enqueue counts of the chunks.
 enum : int { kScanNone, kScanCounts, kScanOffsets };
 
+// The first enqueue of each of nb <= kFusedScanMax chunks, from their counts,
+// into LDS.
+__device__ __forceinline__ void chunk_offsets(const uint32_t *cnt, uint32_t nb, uint32_t *offs) {
+  const uint32_t per = (nb + kBlock - 1) / kBlock, j0 = threadIdx.x * per, j1 = j0 + per < nb ? j0 + per : nb;
+  uint32_t sum = 0, tot;
+  for (uint32_t j = j0; j < j1; ++j) sum += cnt[j];
+  uint32_t run = block_exclusive_scan(sum, tot);
+  for (uint32_t j = j0; j < j1; ++j) {
+    offs[j] = run;
+    run += cnt[j];
+  }
+  __syncthreads();
+}
+
 // Whether at most V lines were sent to the ring from the fill of unique index
 // e up to, not including, that of u > e (the entry e made is then still there
-// at u's turn).  before: u's rank among the enqueues of its chunk.
-__device__ __forceinline__ bool at_most_enqueued(const Scratch &sc, uint64_t V, uint32_t e, uint32_t u, int scan,
-                                                 uint32_t before) {
+// at u's turn).  before: u's rank among the enqueues of its chunk; first: each
+// chunk's first enqueue.
+__device__ __forceinline__ bool at_most_enqueued(const Scratch &sc, uint64_t V, uint32_t e, uint32_t u,
+                                                 const uint32_t *first, uint32_t before) {
   const uint32_t ce = e / kScanChunk, cu = u / kScanChunk;
   if (ce == cu) return count_enqueues(sc.flags, e, u) <= V;
-  uint64_t c = (uint64_t)before + count_enqueues(sc.flags, e, (ce + 1) * kScanChunk);
-  if (scan == kScanOffsets) return c + (sc.scan_part[cu] - sc.scan_part[ce + 1]) <= V;
-  for (uint32_t j = ce + 1; j < cu && c <= V; ++j) c += sc.scan_part[j];
-  return c <= V;
+  return (uint64_t)before + count_enqueues(sc.flags, e, (ce + 1) * kScanChunk) + (first[cu] - first[ce + 1]) <= V;
 }
 
 // ------------------------------------------------------------ victim queues
@@ -1315,9 +1327,16 @@ __global__ __launch_bounds__(kBlock) void k_qplace(const DevState d, Scratch sc,
 // scattered record of every evicted line requested later in the batch (which
 // the walk now knows by itself), a blocking gather of 9 K requests took 171 us
 // against 160.
+//
+// A batch that enqueues more than V may have pushed out an entry it made
+// itself before its line is requested.  A block that meets such a request
+// first scans all chunks' counts into LDS: gathers of 1 M unique IDs with 50 K
+// enqueues for a ring of 2000 took 1046 us where each such request added up
+// the counts between by itself, now 682.
 __device__ __forceinline__ void resolve(const DevState &d, const Scratch &sc, uint64_t t, uint8_t *outcome, int scan,
                                         Counters *cn) {
   static_assert(kScanChunk == kBlock, "one chunk of enqueue flags per block pass");
+  __shared__ uint32_t offs[kFusedScanMax];
   const uint32_t U = cn->n_unique;
   const uint64_t tail0 = d.tail[0], tail_prev = d.tail[1];
   uint32_t enq_total = scan == kScanOffsets ? cn->enq_total : 0u;
@@ -1355,6 +1374,11 @@ __device__ __forceinline__ void resolve(const DevState &d, const Scratch &sc, ui
       rank = ranks[0];
       enq_before = off + rank;
       if (u < U) sc.enq_before[u] = enq_before;
+      if (scan == kScanCounts && enq_total > d.V) {
+        const uint32_t e = u < U && sc.kind[u] == kKindFill ? sc.this_enq[u] : kEmpty;
+        if (__syncthreads_or(e != kEmpty && u - e > d.V))
+          chunk_offsets(sc.scan_part, (U + kScanChunk - 1) / kScanChunk, offs);
+      }
     }
     const uint64_t tail_end = tail0 + enq_total;
     if (u < U) {
@@ -1390,7 +1414,8 @@ __device__ __forceinline__ void resolve(const DevState &d, const Scratch &sc, ui
         const uint32_t e = d.V ? sc.this_enq[u] : kEmpty;
         const bool same_batch = e != kEmpty;
         if (same_batch) {
-          live = enq_total <= d.V || u - e <= d.V || at_most_enqueued(sc, d.V, e, u, scan, rank);
+          live = enq_total <= d.V || u - e <= d.V ||
+                 at_most_enqueued(sc, d.V, e, u, scan == kScanOffsets ? sc.scan_part : offs, rank);
         } else if (d.V) {
           const uint64_t vp = d.vpos[x];
           if (vp) {

@@ -70,6 +70,19 @@ def test_ring_liveness_within_a_batch(victim):
     run_parity(store, stat, sets, victim, 5, batches, rows="all", label=f"V={victim}")
 
 
+@pytest.mark.parametrize("victim", [300, 4000, 20_000])
+@pytest.mark.parametrize("nodes", [65_281, 65_536, 65_537, 131_073])
+def test_ring_liveness_across_chunks(nodes, victim):
+    """The same over hundreds of chunks of enqueue counts, at the sizes where a thread takes one more of them: every
+    node in every batch, so that each line evicted before its turn is requested later."""
+    log(f"case: same-batch ring liveness, {nodes} unique IDs, V={victim}")
+    rng = np.random.default_rng(nodes + victim)
+    batches = [rng.permutation(nodes) for _ in range(5)]
+    store = Store.random_bytes(nodes, 16, 8)
+    stat = rng.integers(0, 3, nodes).astype(np.uint32)
+    run_parity(store, stat, nodes // 20, victim, 3, batches, rows="all", label=f"{nodes} IDs, V={victim}")
+
+
 @pytest.mark.parametrize("requests", [(1 << 20) - 255, (1 << 20) + 1])
 def test_enqueue_scan_limit(requests):
     """Request lists on both sides of the size beyond which the chunks' enqueue counts are scanned by their own kernel."""
