@@ -2136,10 +2136,13 @@ void launch_window_rollback(const int64_t *ids, uint64_t n, uint64_t N, uint32_t
 // output of a gather), for the n requests in their original order.  Item w =
 // (request i, 16-byte vector v), in tiles as the list copies take them; the
 // inverse entry is a broadcast load.  Bound by HBM bandwidth.  The output is
-// written once, with the non-temporal hint, so that it does not displace the
-// rows, which requests repeat: 203 K requests of 4 KiB 279 -> 239 us, 123 K of 1
-// KiB 36.4 -> 34.5, 900 K of 2 KiB 581 -> 574; with the hint on the loads too
-// 277, 42 and 629.
+// written once, with the non-temporal hint, so that it does not take the place
+// of rows in the last-level cache: rows that are still there (those of the
+// gather before, if nothing else ran) or that several requests name.  203 K
+// requests of 190 K distinct 4 KiB rows: 316 -> 296 us with the rows just
+// written, 320 -> 280 with the same call repeated, 348 -> 346 after 1 GiB of
+// other writes; 900 K requests of 235 K 2 KiB rows 626 -> 562, 627 -> 546 and
+// 662 -> 598.  With the hint on the loads too, repeated rows are 10-40 % slower.
 template <bool kPow2>
 __global__ __launch_bounds__(kBlock) void k_expand(const uint8_t *rows, const int64_t *inv, uint64_t n, uint64_t R,
                                                    uint32_t nvec, uint32_t vshift, uint8_t *out) {
