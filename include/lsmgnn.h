@@ -173,7 +173,10 @@ typedef struct {
    runtime copy of the staged evicted rows), not the staging kernel.  A
    gather's host fetch is two launches (the misses known at batch start, then
    the remaining host rows), both counted; its time excludes the wait between
-   them. */
+   them.  Without profiling, a gather expected to fetch at most 1 MiB from host
+   memory moves its rows in one launch; timed, it moves each kind in launches of
+   its own, so these figures, gather_ms among them, say what the rows cost that
+   way and not what such a call takes untimed. */
 typedef struct {
   double hbm_copy_ms;   uint64_t hbm_copy_launches;   uint64_t hbm_copy_rows;   /* cache -> out */
   double host_fetch_ms; uint64_t host_fetch_launches; uint64_t host_fetch_rows; /* store/ring -> out */
@@ -336,7 +339,7 @@ lsmgnn_status lsmgnn_pagerank_scores(const int64_t *offsets, const uint32_t *adj
    (copied).  The graph is checked once (offsets from 0, non-decreasing, every
    degree below 2^32, every entry < num_nodes).  Work memory in HBM: about 9
    bytes per node (the frontier and its samples' places, a byte map rounded up
-   to 16 KiB, the per-chunk sums).
+   to 4 KiB, above 2^24 nodes to 16, the per-chunk sums).
    Errors: E_INVAL (NULL pointers, num_nodes 0 or above 2^32 - 1, hops or a
    fanout out of range); E_RANGE (a malformed graph); E_NOMEM; E_DEVICE.
 
